@@ -29,8 +29,8 @@
 //
 // FP32 runs exactly the operations of that earlier form in its order, element by element (each
 // multiply-add fused or not as written below), so FP32 codes are the same bit for bit; FP64
-// multiplies by stored reciprocals of L's diagonal and folds the step's coefficient into the
-// refresh terms.
+// keeps L^{-1} instead of L (w = L^{-1} g and v = L^{-T} w are then products with no chain from one
+// entry to the next) and folds the step's coefficient into the refresh terms.
 #pragma once
 
 #include "sdl_internal.h"
@@ -43,6 +43,8 @@ struct GCfg {
   using T = T_;
   static constexpr int LR = LR_, LC = LC_, RI = RI_, CJ = CJ_, SM = SM_;
   static constexpr int G = LR * LC, NS = kWave / G, E = RI * CJ, P1 = LR * RI, P2 = LC * CJ;
+  // waves per SIMD the registers must allow
+  static constexpr int WPE = E <= 16 ? 4 : 2;
   // table rows start on the boundary that a lane's run of RI (CJ) elements is read at
   __host__ __device__ static constexpr int run_align(int n) {
     const int b = n * (int)sizeof(T);
@@ -58,7 +60,7 @@ struct GCfg {
 // the space shared by W (first correlation) and L (step loop)
 struct GLay {
   int d1, d2, g1, g2, tab, lds, stride;  // lds: offset of W / L inside a signal's space
-  int ld1, ld2, ldd;                     // row strides of G1 and W, of G2 and D2, of D1 (odd)
+  int ld1, ld2, ldd;                     // strides of G1 and W, of G2 and D2, of D1 (odd)
   int slack;                             // elements a run of the last row may read past the end
 };
 template <class C>
@@ -67,13 +69,13 @@ __host__ __device__ inline GLay group_layout(int m1, int m2, int n1, int n2, int
   auto up4 = [](int v) { return (v + 3) & ~3; };
   l.ld1 = C::ld1(n1);
   l.ld2 = C::ld2(n2);
-  l.ldd = n1 | 1;
+  l.ldd = m1 | 1;
   l.slack = C::P1 > C::P2 ? C::P1 : C::P2;
   int o = 0;
   l.d2 = o; o += up4(m2 * l.ld2);
   l.g1 = o; o += up4(n1 * l.ld1);
   l.g2 = o; o += up4(n2 * l.ld2);
-  l.d1 = o; o += up4(m1 * l.ldd);
+  l.d1 = o; o += up4(n1 * l.ldd);
   l.tab = o;
   l.lds = up4(m1 * m2);
   const int w = m2 * l.ld1, f = s * (s | 1);
@@ -161,11 +163,23 @@ __device__ __forceinline__ void downward(int n, F&& f) {
     for (int l = n - 1; l >= 0; --l) f(l);
   }
 }
+// lane L's value of v, within each row of sixteen lanes
+template <int L, typename U>
+__device__ inline U bcast16(U v) {
+  if constexpr (sizeof(U) == 4) {
+    return __builtin_bit_cast(U, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + L, 0xF, 0xF, true));
+  } else {  // row_newbcast:L
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + L, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + L, 0xF, 0xF, true);
+    return __builtin_bit_cast(U, ((long long)hi << 32) | (unsigned int)lo);
+  }
+}
 // lane l's value of v, within each signal's lanes
 template <class C, class L, typename U>
 __device__ inline U from_lane(U v, L l) {
   if constexpr (C::G == 16) {
-    return dpp<0x150 + L::value>(v, v);  // row_newbcast:l
+    return bcast16<L::value>(v);
   } else {
     return lane_read(v, l);
   }
@@ -213,18 +227,37 @@ __device__ inline void signal_argmax(T& v, int& code) {
   }
 }
 
+// N contiguous elements of a table row; the run starts on the widest boundary its size allows
 template <int N, typename T>
-__device__ inline void load_run(const T* p, T* out) {  // N contiguous elements (N-element aligned rows)
-  constexpr int bytes = N * (int)sizeof(T), al = bytes % 16 == 0 ? 16 : (bytes % 8 == 0 ? 8 : 4);
-  const T* q = (const T*)__builtin_assume_aligned(p, al);
+__device__ inline void load_run(const T* p, T* out) {
+  constexpr int bytes = N * (int)sizeof(T), W = (bytes % 16 == 0 ? 16 : bytes % 8 == 0 ? 8 : 4) / (int)sizeof(T);
+  if constexpr (W <= 1) {
 #pragma unroll
-  for (int i = 0; i < N; ++i) out[i] = q[i];
+    for (int i = 0; i < N; ++i) out[i] = p[i];
+  } else {
+    typedef T V __attribute__((ext_vector_type(W)));
+#pragma unroll
+    for (int i = 0; i < N; i += W) {
+      const V v = *reinterpret_cast<const V*>(p + i);
+#pragma unroll
+      for (int u = 0; u < W; ++u) out[i + u] = v[u];
+    }
+  }
 }
+
+// 1 / sqrt(x) of a positive normal x: the hardware's estimate (relative error below 2^-22) and one
+// third-order correction y (1 + e/2 + 3 e^2/8), e = 1 - x y^2
+__device__ inline double rsqrt64(double x) {
+  const double y = __builtin_amdgcn_rsq(x), e = gfma(-(x * y), y, 1.0);
+  return gfma(y * e, gfma(0.375, e, 0.5), y);
+}
+__device__ inline float rsqrt64(float x) { return x; }  // never called
 
 constexpr int kGroupMaxWaves = 8;  // per workgroup
 
 template <class C>
-__global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArgs<typename C::T> a) {
+__global__ void __launch_bounds__(kWave* kGroupMaxWaves) __attribute__((amdgpu_waves_per_eu(C::WPE)))
+    omp_group_kernel(OmpArgs<typename C::T> a) {
 #pragma clang fp contract(off)
   using T = typename C::T;
   constexpr int RI = C::RI, CJ = C::CJ, E = C::E, P1 = C::P1, P2 = C::P2, G = C::G, NS = C::NS;
@@ -234,12 +267,12 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
   const int m1 = a.m1, m2 = a.m2, n1 = a.n1, n2 = a.n2, s = a.s, M = m1 * m2;
   const GLay lay = group_layout<C>(m1, m2, n1, n2, s);
   const int ld1 = lay.ld1, ld2 = lay.ld2, ldd = lay.ldd;
-  T* sD1 = sm + lay.d1;  // D1[p, i] at p ldd + i
+  T* sD1 = sm + lay.d1;  // D1[p, i] at i ldd + p
   T* sD2 = sm + lay.d2;  // D2[q, j] at q ld2 + j
   T* sG1 = sm + lay.g1;  // G1[i, i'] at i' ld1 + i
   T* sG2 = sm + lay.g2;  // G2[j, j'] at j' ld2 + j
   const int tid = threadIdx.x, wv = tid / kWave, lane = tid % kWave, wpb = blockDim.x / kWave;
-  for (int e = tid; e < m1 * n1; e += blockDim.x) sD1[(e % m1) * ldd + e / m1] = a.D1[e];
+  for (int e = tid; e < m1 * n1; e += blockDim.x) sD1[(e / m1) * ldd + e % m1] = a.D1[e];
   for (int e = tid; e < m2 * n2; e += blockDim.x) sD2[(e % m2) * ld2 + e / m2] = a.D2[e];
   for (int e = tid; e < n1 * n1; e += blockDim.x) sG1[(e / n1) * ld1 + e % n1] = a.G1[e];
   for (int e = tid; e < n2 * n2; e += blockDim.x) sG2[(e / n2) * ld2 + e % n2] = a.G2[e];
@@ -249,7 +282,7 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
   const unsigned long long gmask = G == 64 ? ~0ull : ((1ull << (G % 64)) - 1ull) << (g * G);
   T* ys = sm + lay.tab + (size_t)(wv * NS + g) * lay.stride;
   T* Ws = ys + lay.lds;  // W[i, q] at q ld1 + i
-  T* Lr = Ws;            // L[k, q], q <= k, at k ldl + q (after W is read)
+  T* Lr = Ws;            // L[k, q] (FP64: L^{-1}[k, q]), q <= k, at k ldl + q (after W is read)
   const int ldl = s | 1;
   const int ls = l < s ? l : 0;  // a row / column of L that exists
   const T* rG1 = sG1 + sr * RI;  // this lane's rows and columns of the tables
@@ -287,6 +320,7 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
       const int i0 = l % (P1 < G ? P1 : G), qo = P1 < G ? l / P1 : 0;
       if (qo < QI) {
         for (int i = i0; i < n1; i += G) {
+          const T* d1 = sD1 + i * ldd;
           for (int q0 = qo; q0 < m2; q0 += 4 * QI) {
             T v[4] = {0, 0, 0, 0};
             const T* y[4];
@@ -295,9 +329,9 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
               const int q = q0 + u * QI;
               y[u] = ys + m1 * (q < m2 ? q : m2 - 1);
             }
-#pragma unroll 2
+#pragma unroll 4
             for (int p = 0; p < m1; ++p) {
-              const T d = sD1[p * ldd + i];
+              const T d = d1[p];
 #pragma unroll
               for (int u = 0; u < 4; ++u) v[u] = gfma(d, y[u][p], v[u]);
             }
@@ -322,16 +356,22 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
 #pragma unroll
         for (int ri = 0; ri < RI; ++ri) al[cj * RI + ri] = gfma(wi[ri], dj[cj], al[cj * RI + ri]);
     }
+    // opaque copies: the compares stay here instead of living in scalar registers throughout
+    int rows = n1 - sr * RI, cols = n2 - sc * CJ;
+    asm volatile("" : "+v"(rows), "+v"(cols));
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-      al[e] = sr * RI + e % RI < n1 && sc * CJ + e / RI < n2 ? al[e] : T(__builtin_nanf(""));
+    for (int e = 0; e < E; ++e) al[e] = e % RI < rows && e / RI < cols ? al[e] : T(__builtin_nanf(""));
     group_sync();  // W is read: L takes its place
+    if constexpr (F64) {
+      for (int e = l; e < s * ldl; e += G) Lr[e] = 0;
+      group_sync();
+    }
 
     const T thr = T(a.stop_rel) * ynorm;
     bool active = valid, early = false;
     int nt = 0;                     // atoms of this signal
     int my_code = -1, my_off = 0;   // support element l: its code, its rows of G1 and G2
-    T my_x = 0, my_d = 1;           // its coefficient; L[l, l] (FP64: 1 / L[l, l])
+    T my_x = 0, my_d = 1;           // its coefficient; L[l, l] (FP32)
     int t = 0;
 #pragma unroll 1
     for (; t < s; ++t) {
@@ -355,20 +395,20 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
             const T v = al[cj * RI + ri];
             const bool take = gabs(v) > gabs(bs);
             bs = take ? v : bs;
-            be = take ? (cj << 8 | ri) : be;
+            be = take ? cj * RI + ri : be;
           }
-        code = base_code + be;
+        code = base_code + ((be / RI) << 8 | (be % RI));
         signal_argmax<C>(bs, code);
         // a chosen atom's correlation is zero up to rounding after the re-fit, so it comes up
         // again only when every correlation is at rounding level: only then is the support masked
         const bool again = active && ((__ballot(l < t && my_code == code) & gmask) != 0ull);
         if (__ballot(again) == 0ull) break;
-        upward<C>(t, [&](auto q) __attribute__((always_inline)) {
-          const int cq = from_lane<C>(my_code, q);
+#pragma unroll 1
+        for (int q = 0; q < t; ++q) {
+          const int cq = __shfl(my_code, g * G + q, kWave) - base_code;
 #pragma unroll
-          for (int e = 0; e < E; ++e)
-            al[e] = again && base_code + ((e / RI) << 8 | (e % RI)) == cq ? T(__builtin_nanf("")) : al[e];
-        });
+          for (int e = 0; e < E; ++e) al[e] = again && ((e / RI) << 8 | (e % RI)) == cq ? T(__builtin_nanf("")) : al[e];
+        }
       }
       const bool small_corr = !(gabs(bs) > thr);
       early |= active && small_corr;
@@ -382,16 +422,25 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
       const T gaa = a1 * a2;
       // new Cholesky row: L w = G_{S,a}, lane k < t holding entry k
       const int mc = l < t ? my_code : 0;
-      const T b0 = g1a[mc & 255] * g2a[mc >> 8];
-      T b = b0, w = 0, ww = 0;
-      upward<C>(t, [&](auto q) __attribute__((always_inline)) {
-        const T f = F64 ? b * my_d : b / my_d;
-        const T wq = from_lane<C>(f, q);
-        ww = gfma(wq, wq, ww);
-        w = l == q ? wq : w;
-        const T nb = gfma(-Lr[ls * ldl + q], wq, b);
-        b = l > q && l < t ? nb : b;
-      });
+      T b = g1a[mc & 255] * g2a[mc >> 8], w = 0, ww = 0, v = 0;
+      if constexpr (F64) {
+        upward<C>(t, [&](auto q) __attribute__((always_inline)) { w = gfma(Lr[ls * ldl + q], from_lane<C>(b, q), w); });
+        w = l < t ? w : T(0);
+        // and v = L^{-T} w (rows and columns of L^{-1} not yet written are zero)
+        upward<C>(t, [&](auto q) __attribute__((always_inline)) {
+          const T wq = from_lane<C>(w, q);
+          ww = gfma(wq, wq, ww);
+          v = gfma(Lr[q * ldl + ls], wq, v);
+        });
+      } else {
+        upward<C>(t, [&](auto q) __attribute__((always_inline)) {
+          const T wq = from_lane<C>(b / my_d, q);
+          ww = gfma(wq, wq, ww);
+          w = l == q ? wq : w;
+          const T nb = gfma(-Lr[ls * ldl + q], wq, b);
+          b = l > q && l < t ? nb : b;
+        });
+      }
       T d2 = gfma(a1, a2, -ww);
       if constexpr (!F64) {
         const bool small = active && d2 < T(a.pivot_fp64) * gaa;
@@ -414,19 +463,18 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
       early |= active && dep;
       active = active && !dep;
       if (__ballot(active) == 0ull) break;
-      // v = L^{-T} w, lane k < t holding entry k
-      T v = 0;
+      T cst;
       if constexpr (F64) {
-        T bb = w;
-        downward<C>(t, [&](auto q) __attribute__((always_inline)) {
-          const T vq = from_lane<C>(bb * my_d, q);
-          v = l == q ? vq : v;
-          const T nb = gfma(-Lr[q * ldl + ls], vq, bb);
-          bb = l < q ? nb : bb;
-        });
+        const T r = rsqrt64(d2);
+        cst = bs * (r * r);
+        if (active) {
+          if (l < t) Lr[t * ldl + l] = -(v * r);
+          if (l == t) Lr[t * ldl + l] = r;
+        }
       } else {
-        // entry q subtracts its products in increasing order of the row, so it starts once
-        // entry q + 1 is known: a serial chain (its lanes all compute it)
+        // v = L^{-T} w, lane k < t holding entry k.  Entry q subtracts its products in increasing
+        // order of the row, so it starts once entry q + 1 is known: a serial chain (every lane
+        // computes it)
         downward<C>(t, [&](auto q) __attribute__((always_inline)) {
           T acc = from_lane<C>(w, q);
           upward<C>(t, [&](auto r) __attribute__((always_inline)) {
@@ -435,17 +483,17 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
           acc = acc / from_lane<C>(my_d, q);
           v = l == q ? acc : v;
         });
-      }
-      const T cst = bs / d2;
-      renergy = gfma(-cst, bs, renergy);
-      const T dl = sqrt(d2);
-      if (active) {
-        if (l < t) {
-          Lr[t * ldl + l] = w;
-          my_x = gfma(-cst, v, my_x);
+        cst = bs / d2;
+        const T dl = sqrt(d2);
+        if (active) {
+          if (l < t) Lr[t * ldl + l] = w;
+          if (l == t) my_d = dl;
         }
+      }
+      renergy = gfma(-cst, bs, renergy);
+      if (active) {
+        if (l < t) my_x = gfma(-cst, v, my_x);
         if (l == t) {
-          my_d = F64 ? T(1) / dl : dl;
           my_x = cst;
           my_code = code;
           my_off = off_a;
@@ -496,7 +544,7 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
     }
     // explicit residual Y - sum_q x_q d1_{i_q} d2_{j_q}^T (x_q = 0 beyond a signal's atoms)
     const int mi = my_code < 0 ? 0 : my_code & 255, mj = my_code < 0 ? 0 : my_code >> 8;
-    const int my_pix = mi | (mj << 16);
+    const int my_pix = mi * ldd | (mj << 16);
     T rp[4] = {0, 0, 0, 0};
     for (int e0 = 0; e0 < M; e0 += kWave) {
       T r[NS];
@@ -505,7 +553,7 @@ __global__ void __launch_bounds__(kWave* kGroupMaxWaves) omp_group_kernel(OmpArg
       for (int u = 0; u < NS; ++u) {
         const int e = e0 + G * u + l < M ? e0 + G * u + l : M - 1;
         const int q = (int)(((unsigned)e * inv_m1) >> 20);
-        p1[u] = (e - q * m1) * ldd;
+        p1[u] = e - q * m1;
         p2[u] = q * ld2;
         r[u] = ys[e];
       }
