@@ -11,4 +11,9 @@ hipError_t launch_omp_generic<double>(const OmpArgs<double>& a, hipStream_t st) 
   return group_launch<double>(a, st);
 }
 
+int omp_generic_cost_f64(int m1, int m2, int n1, int n2, int s) {
+  const GroupVariant* v = pick<double>(m1, m2, n1, n2, s);
+  return v ? v->lanes * v->elems : 0;
+}
+
 }  // namespace sdl

@@ -34,8 +34,27 @@ GroupVariant variant() {
 #define SDL_GROUP64(X) \
   X(2, 2) X(2, 4) X(4, 2) X(2, 8) X(8, 2) X(4, 4) X(4, 6) X(6, 4) X(4, 8) X(8, 4) X(6, 6) X(8, 8)
 
+// A 4 x 16 lane grid for a narrow dictionary against a wide one: FP64 n-dimensional problems whose
+// later modes are collapsed into one Kronecker factor.
+#define SDL_GROUP64W(X) X(3, 2) X(3, 3) X(3, 4) X(3, 5) X(4, 4) X(4, 6)
+
 template <typename T>
 const GroupVariant* variants(int* n) {
+  if constexpr (sizeof(T) == 8) {
+    static const GroupVariant v[] = {
+#define X(R_, C_) variant<GCfg<T, 4, 4, R_, C_, 8>>(), variant<GCfg<T, 4, 4, R_, C_, 16>>(),
+        SDL_GROUP16(X)
+#undef X
+#define X(R_, C_) variant<GCfg<T, 8, 8, R_, C_, 32>>(),
+        SDL_GROUP64(X)
+#undef X
+#define X(R_, C_) variant<GCfg<T, 4, 16, R_, C_, 32>>(),
+        SDL_GROUP64W(X)
+#undef X
+    };
+    *n = (int)(sizeof(v) / sizeof(v[0]));
+    return v;
+  }
   static const GroupVariant v[] = {
 #define X(R_, C_) variant<GCfg<T, 4, 4, R_, C_, 8>>(), variant<GCfg<T, 4, 4, R_, C_, 16>>(),
       SDL_GROUP16(X)

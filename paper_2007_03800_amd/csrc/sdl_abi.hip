@@ -1040,25 +1040,46 @@ struct TPlan {
   void* Gc[kTensorMaxModes];
   double *part, *stage, *sums, *w, *rpart;
   int rows, rblk, nent;
-  // FP32 shapes coded by the two-mode one-wave kernel: modes 2.. collapsed into one Kronecker
-  // factor Dk (mk x nk, FP64 master, compute-type copy and Grams)
-  bool collapsed;
-  int mk, nk;
-  double *Dk64, *Gk64;
-  void *Dkc, *Gkc;
+  // Problems coded by a two-mode kernel: modes 0 .. split-1 and split .. form one Kronecker factor
+  // each (mk x nk; FP64 master, compute-type copy and Grams; a factor of one mode is that mode's own
+  // buffers).  split = 0: the n-mode kernel.
+  int split;
+  int mk[2], nk[2];
+  double *Dk64[2], *Gk64[2];
+  void *Dkc[2], *Gkc[2];
   size_t bytes;
 };
 
-bool tensor_collapsed(const sdl_tensor_problem* p, size_t elem) {
-  if (elem != 4) return false;
-  int64_t mk = 1, nk = 1;
-  for (int d = 1; d < p->nmodes; ++d) {
-    mk *= p->m[d];
-    nk *= p->n[d];
+int64_t tensor_elems(const int32_t* v, int nm) {
+  int64_t e = 1;
+  for (int d = 0; d < nm; ++d) e *= v[d];
+  return e;
+}
+
+// Where the modes are cut for a two-mode kernel, 0 if none takes the problem.  FP32: only the shapes
+// compiled in omp_wave.hip, cut after the first mode (other FP32 shapes keep the n-mode kernel, whose
+// rounding order a precomputed Kronecker Gram would change).  FP64: the cut whose kernel keeps the
+// fewest correlations per signal (8x8x4 signals with 12x12x6 atoms are
+// cut 12 | 72).
+int tensor_split(const sdl_tensor_problem* p, size_t elem) {
+  int best = 0, best_cost = 0;
+  for (int c = 1; c < p->nmodes; ++c) {
+    const int64_t m1 = tensor_elems(p->m, c), n1 = tensor_elems(p->n, c);
+    const int64_t m2 = tensor_elems(p->m + c, p->nmodes - c), n2 = tensor_elems(p->n + c, p->nmodes - c);
+    // the dictionary preparation stages a factor in LDS at (m + 1) x n doubles
+    const int64_t most = (int64_t)(SDL_MAX_M + 1) * SDL_MAX_N;
+    if ((m1 + 1) * n1 > most || (m2 + 1) * n2 > most || m1 > 256 || n1 > 256) continue;
+    if (elem == 4) {
+      if (c == 1 && omp_wave_collapsed_supported((int)m1, (int)m2, (int)n1, (int)n2, p->s)) return 1;
+      continue;
+    }
+    const int cost = omp_generic_cost_f64((int)m1, (int)m2, (int)n1, (int)n2, p->s);
+    if (cost > 0 && (best == 0 || cost < best_cost)) {
+      best = c;
+      best_cost = cost;
+    }
   }
-  // the dictionary preparation stages the factor in LDS at (mk + 1) x nk doubles
-  if ((mk + 1) * nk > (int64_t)(SDL_MAX_M + 1) * SDL_MAX_N) return false;
-  return omp_wave_collapsed_supported(p->m[0], (int)mk, p->n[0], (int)nk, p->s);
+  return best;
 }
 
 void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* base, TPlan* tp) {
@@ -1076,20 +1097,23 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
     const int e = p->n[d] * p->n[d] + p->m[d] * p->n[d];
     nent = e > nent ? e : nent;
   }
-  tp->collapsed = tensor_collapsed(p, elem);
-  tp->mk = tp->nk = 1;
-  for (int d = 1; d < p->nmodes; ++d) {
-    tp->mk *= p->m[d];
-    tp->nk *= p->n[d];
-  }
-  if (tp->collapsed) {
-    tp->Dk64 = b.take<double>((size_t)tp->mk * tp->nk);
-    tp->Gk64 = b.take<double>((size_t)tp->nk * tp->nk);
-    tp->Dkc = b.take<char>(elem * tp->mk * tp->nk);
-    tp->Gkc = b.take<char>(elem * tp->nk * tp->nk);
-  } else {
-    tp->Dk64 = tp->Gk64 = nullptr;
-    tp->Dkc = tp->Gkc = nullptr;
+  tp->split = tensor_split(p, elem);
+  for (int f = 0; f < 2; ++f) {
+    const int q0 = f == 0 ? 0 : tp->split, q1 = f == 0 ? tp->split : p->nmodes;
+    tp->mk[f] = (int)tensor_elems(p->m + q0, q1 - q0);
+    tp->nk[f] = (int)tensor_elems(p->n + q0, q1 - q0);
+    tp->Dk64[f] = tp->Gk64[f] = nullptr;
+    tp->Dkc[f] = tp->Gkc[f] = nullptr;
+    if (tp->split == 0) continue;
+    if (q1 - q0 == 1) {
+      tp->Dkc[f] = tp->Dc[q0];
+      tp->Gkc[f] = tp->Gc[q0];
+      continue;
+    }
+    tp->Dk64[f] = b.take<double>((size_t)tp->mk[f] * tp->nk[f]);
+    tp->Gk64[f] = b.take<double>((size_t)tp->nk[f] * tp->nk[f]);
+    tp->Dkc[f] = b.take<char>(elem * tp->mk[f] * tp->nk[f]);
+    tp->Gkc[f] = b.take<char>(elem * tp->nk[f] * tp->nk[f]);
   }
   tp->rows = tensor_sums_rows(p->N);
   tp->nent = nent;
@@ -1101,12 +1125,6 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
   tp->rpart = b.take<double>((size_t)tp->rblk);
   tp->bytes = b.off + 256;
   tp->pl.bytes = tp->bytes;
-}
-
-int64_t tensor_elems(const int32_t* v, int nm) {
-  int64_t e = 1;
-  for (int d = 0; d < nm; ++d) e *= v[d];
-  return e;
 }
 
 int validate_tensor(const sdl_tensor_problem* p, const Opt& o, bool update) {
@@ -1200,45 +1218,49 @@ int tensor_update_mode(const sdl_tensor_problem* p, const TPlan& tp, const Opt& 
   return SDL_OK;
 }
 
-// sparse coding of every signal: the two-mode one-wave kernel on (D_1, D_n (x) ... (x) D_2) for the
-// collapsed FP32 shapes (the same atoms in the same order: a = i_1 + n_1 j', j' = i_2 + n_2 (...)),
-// else the n-mode kernel
+// sparse coding of every signal: a two-mode kernel on the two Kronecker factors where the problem is
+// cut in two (the same atoms in the same order: a = j + n1 j', j and j' the indices within the
+// factors), else the n-mode kernel
 template <typename T>
 int tensor_code(const sdl_tensor_problem* p, const TPlan& tp, const Opt& o, hipStream_t st) {
-  if constexpr (sizeof(T) == 4) {
-    if (tp.collapsed) {
-      TensorArgs<double> dd{};
-      dd.nmodes = p->nmodes;
-      for (int d = 0; d < kTensorMaxModes; ++d) {
-        dd.m[d] = d < p->nmodes ? p->m[d] : 1;
-        dd.n[d] = d < p->nmodes ? p->n[d] : 1;
-        dd.D[d] = d < p->nmodes ? p->D[d] : nullptr;
-      }
-      HIP_TRY(launch_kron_tail(dd, tp.Dk64, st));
-      HIP_TRY(launch_dict_prep<float>(tp.Dk64, tp.mk, tp.nk, (float*)tp.Dkc, tp.Gk64, (float*)tp.Gkc, st));
-      OmpArgs<float> a{};
-      a.m1 = p->m[0]; a.m2 = tp.mk; a.n1 = p->n[0]; a.n2 = tp.nk; a.s = p->s; a.N = p->N;
-      a.Y = (const float*)p->Y;
-      a.Yh = nullptr;
-      a.D1 = (const float*)tp.Dc[0];
-      a.D2 = (const float*)tp.Dkc;
-      a.G1 = (const float*)tp.Gc[0];
-      a.G2 = (const float*)tp.Gkc;
-      a.supp = p->supp;
-      a.coef = (float*)p->coef;
-      a.res2 = (float*)p->res2;
-      a.stop_rel = o.stop_rel; a.dep_eps = o.dep_eps; a.pivot_fp64 = o.pivot_fp64; a.err2 = o.err2;
-      a.tie_band = o.tie_band;
-      a.counters = tp.pl.counters;
-      a.sums_side = 0;
-      a.sums_part = nullptr;
-      a.index = nullptr;
-      a.count = nullptr;
-      HIP_TRY(launch_omp_wave_collapsed(a, st));
-      return SDL_OK;
-    }
+  if (p->N == 0 || tp.split == 0) {
+    HIP_TRY(launch_tensor_omp<T>(tensor_args<T>(p, tp, o), st));
+    return SDL_OK;
   }
-  HIP_TRY(launch_tensor_omp<T>(tensor_args<T>(p, tp, o), st));
+  TensorArgs<double> dd{};
+  dd.nmodes = p->nmodes;
+  for (int d = 0; d < kTensorMaxModes; ++d) {
+    dd.m[d] = d < p->nmodes ? p->m[d] : 1;
+    dd.n[d] = d < p->nmodes ? p->n[d] : 1;
+    dd.D[d] = d < p->nmodes ? p->D[d] : nullptr;
+  }
+  for (int f = 0; f < 2; ++f) {
+    if (!tp.Dk64[f]) continue;
+    HIP_TRY(launch_kron(dd, f == 0 ? 0 : tp.split, f == 0 ? tp.split : p->nmodes, tp.Dk64[f], st));
+    HIP_TRY(launch_dict_prep<T>(tp.Dk64[f], tp.mk[f], tp.nk[f], (T*)tp.Dkc[f], tp.Gk64[f], (T*)tp.Gkc[f], st));
+  }
+  OmpArgs<T> a{};
+  a.m1 = tp.mk[0]; a.m2 = tp.mk[1]; a.n1 = tp.nk[0]; a.n2 = tp.nk[1]; a.s = p->s; a.N = p->N;
+  a.Y = (const T*)p->Y;
+  a.Yh = nullptr;
+  a.D1 = (const T*)tp.Dkc[0];
+  a.D2 = (const T*)tp.Dkc[1];
+  a.G1 = (const T*)tp.Gkc[0];
+  a.G2 = (const T*)tp.Gkc[1];
+  a.supp = p->supp;
+  a.coef = (T*)p->coef;
+  a.res2 = (T*)p->res2;
+  a.stop_rel = o.stop_rel; a.dep_eps = o.dep_eps; a.pivot_fp64 = o.pivot_fp64; a.err2 = o.err2;
+  a.tie_band = o.tie_band;
+  a.counters = tp.pl.counters;
+  a.sums_side = 0;
+  a.sums_part = nullptr;
+  a.index = nullptr;
+  a.count = nullptr;
+  if constexpr (sizeof(T) == 4)
+    HIP_TRY(launch_omp_wave_collapsed(a, st));
+  else
+    HIP_TRY(launch_omp_generic<T>(a, st));
   return SDL_OK;
 }
 

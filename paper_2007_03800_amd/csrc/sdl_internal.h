@@ -147,6 +147,10 @@ hipError_t autotune_problem(const OmpArgs<float>& a, hipStream_t st, int reps, i
 bool tuned_config(int m1, int m2, int n1, int n2, int s, int* lr, int* lc, int* wpe, int* mfma, double* ms);
 // Counter bumped whenever a kernel choice (autotuned or forced) changes.
 long tuning_epoch();
+// FP64: correlations (padding included) the variant picked for this two-mode shape keeps per signal,
+// 0 if none fits; sizes may exceed the two-mode limits (collapsed n-dimensional problems, at most
+// 4096 signal elements)
+int omp_generic_cost_f64(int m1, int m2, int n1, int n2, int s);
 size_t omp_generic_lds_bytes(int m1, int m2, int n1, int n2, int s, size_t elem);
 hipError_t omp_generic_init_device();
 
@@ -250,8 +254,8 @@ hipError_t launch_ortho_mfma(const OmpArgs<float>& a, hipStream_t st);
 // collapsed into one Kronecker factor (FP32 shapes compiled in omp_wave.hip)
 bool omp_wave_collapsed_supported(int m1, int m2, int n1, int n2, int s);
 hipError_t launch_omp_wave_collapsed(const OmpArgs<float>& a, hipStream_t st);
-// Dk = D_nm-1 (x) ... (x) D_1 (mode 0 excluded): prod_{d>=1} m[d] x prod_{d>=1} n[d], FP64
-hipError_t launch_kron_tail(const TensorArgs<double>& d, double* Dk, hipStream_t st);
+// Dk = D_q1-1 (x) ... (x) D_q0 (modes q0 .. q1-1): prod m[d] x prod n[d], FP64
+hipError_t launch_kron(const TensorArgs<double>& d, int q0, int q1, double* Dk, hipStream_t st);
 // Denoising driver (denoise.hip): overlapping patches of a row-major image as column-major
 // signals, and the image rebuilt as the average of the coded patches covering each pixel.
 template <typename T>

@@ -417,12 +417,12 @@ __global__ void __launch_bounds__(kWave) tensor_sums_kernel(TensorArgs<T> a, int
   for (int e = lane; e < nent; e += kWave) part[(size_t)blockIdx.x * nent + e] = acc[e];
 }
 
-// Dk[p', j'] = prod_{d>=1} D_d[p_d, i_d] with p' = p_1 + m_1 (p_2 + ...), j' = i_1 + n_1 (i_2 + ...)
-__global__ void kron_tail_kernel(TensorArgs<double> d, double* Dk, int mk, int nk) {
+// Dk[p', j'] = prod_{q0 <= d < q1} D_d[p_d, i_d] with p' = p_q0 + m_q0 (...), j' = i_q0 + n_q0 (...)
+__global__ void kron_kernel(TensorArgs<double> d, int q0, int q1, double* Dk, int mk, int nk) {
   for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < mk * nk; e += gridDim.x * blockDim.x) {
     int p = e % mk, j = e / mk;
     double v = 1.0;
-    for (int q = 1; q < d.nmodes; ++q) {
+    for (int q = q0; q < q1; ++q) {
       const int pq = p % d.m[q], iq = j % d.n[q];
       p /= d.m[q];
       j /= d.n[q];
@@ -432,29 +432,47 @@ __global__ void kron_tail_kernel(TensorArgs<double> d, double* Dk, int mk, int n
   }
 }
 
-// FP32 mode-d sums on the matrix cores, for n_d <= 16 and m_d <= 16: the signals' W_k(d) and
+// Mode-d sums on the matrix cores, for n_d <= 16 and m_d <= 16: the signals' W_k(d) and
 // Y_k(d) concatenated along their columns form the contraction A = Wcat Wcat^T, B = Ycat Wcat^T,
-// run four columns at a time with the 16x16x4 FP32 MFMA (lane l supplies row l % 16 of column
+// run four columns at a time with the 16x16x4 MFMA (lane l supplies row l % 16 of column
 // l / 16 of the slice, which is both operands' value for the A sum).  One wave per workgroup
-// strides over the signals, accumulating in FP32; its tiles are written as one FP64 partial row.
+// strides over the signals, accumulating in T; its tiles are written as one FP64 partial row.
+// The FP64 form adds a column's entries to its own LDS column instead of selecting among sixteen
+// registers per entry.
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+template <typename T>
+struct SumsMfma;
+template <>
+struct SumsMfma<float> {
+  using V = f32x4_t;
+  static __device__ inline V step(float a, float b, V c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ inline int row(int lane, int v) { return 4 * (lane / 16) + v; }
+};
+template <>
+struct SumsMfma<double> {
+  using V = f64x4_t;
+  static __device__ inline V step(double a, double b, V c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static __device__ inline int row(int lane, int v) { return lane / 16 + 4 * v; }
+};
 constexpr int kSumsLdw = 17;  // W column stride (odd: the lanes' columns fall in different banks)
 
-__host__ __device__ inline size_t sums_mfma_lds_bytes(int nm, const int* m, const int* n, int mode) {
+__host__ __device__ inline size_t sums_mfma_lds_bytes(int nm, const int* m, const int* n, int mode, size_t elem) {
   int M = 1, dsz = 0;
   for (int d = 0; d < nm; ++d) {
     M *= m[d];
     dsz += m[d] * n[d];
   }
   const int mo = M / m[mode], mo4 = (mo + 3) / 4 * 4;
-  return sizeof(float) * ((size_t)dsz + M + (size_t)kSumsLdw * mo4) + 2 * sizeof(int) * (size_t)mo4 +
-         2 * sizeof(int) * SDL_MAX_S + 32;
+  return elem * ((size_t)dsz + M + (size_t)kSumsLdw * mo4 + SDL_MAX_S) + 2 * sizeof(int) * (size_t)mo4 +
+         sizeof(int) * SDL_MAX_S + 32;
 }
 
-template <int NM>
-__global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<float> a, int mode, double* part) {
+template <typename T, int NM>
+__global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<T> a, int mode, double* part) {
+  using MF = SumsMfma<T>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* sm = reinterpret_cast<float*>(smem_raw);
+  T* sm = reinterpret_cast<T*>(smem_raw);
   constexpr int nm = NM;
   const int s = a.s, lane = threadIdx.x;
   int m[kTensorMaxModes], n[kTensorMaxModes], stride[kTensorMaxModes];
@@ -465,7 +483,7 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
     stride[d] = M;
     M *= m[d];
   }
-  const float* Ds[kTensorMaxModes];
+  const T* Ds[kTensorMaxModes];
   int off = 0;
 #pragma unroll
   for (int d = 0; d < nm; ++d) {
@@ -475,12 +493,12 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
     dsz = off;
   }
   const int na = n[mode], mr = m[mode], mo = M / mr, mo4 = (mo + 3) / 4 * 4;
-  float* ys = sm + dsz;
-  float* W = ys + M;  // W[i + kSumsLdw c], i < 16, c < mo4 (rows >= na and columns >= mo stay 0)
-  int* cidx = reinterpret_cast<int*>(W + kSumsLdw * mo4);
+  T* ys = sm + dsz;
+  T* W = ys + M;  // W[i + kSumsLdw c], i < 16, c < mo4 (rows >= na and columns >= mo stay 0)
+  T* tcv = W + kSumsLdw * mo4;  // the signal's code, decoded (below)
+  unsigned* tpk = reinterpret_cast<unsigned*>(tcv + SDL_MAX_S);
+  int* cidx = reinterpret_cast<int*>(tpk + SDL_MAX_S);
   int* cbase = cidx + mo4;
-  unsigned* tpk = reinterpret_cast<unsigned*>(cbase + mo4);  // the signal's code, decoded (below)
-  float* tcv = reinterpret_cast<float*>(tpk + SDL_MAX_S);
   for (int c = lane; c < mo4; c += kWave) {
     int r = c, packed = 0, base = 0;
 #pragma unroll
@@ -494,8 +512,10 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
     cidx[c] = packed;
     cbase[c] = c < mo ? base : -1;
   }
+  if constexpr (sizeof(T) == 8)
+    for (int e = lane; e < kSumsLdw * mo4; e += kWave) W[e] = T(0);
   const int r16 = lane % 16, kq = lane / 16;
-  f32x4_t accA = {0.f, 0.f, 0.f, 0.f}, accB = {0.f, 0.f, 0.f, 0.f};
+  typename MF::V accA = {0, 0, 0, 0}, accB = {0, 0, 0, 0};
   for (int64_t k = blockIdx.x; k < a.N; k += gridDim.x) {
     __syncthreads();
     for (int e = lane; e < M; e += kWave) ys[e] = a.Y[k * M + e];
@@ -504,7 +524,7 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
     if (lane < s) {
       const int at = a.supp[k * s + lane];
       unsigned pk = 0u;
-      float cv = 0.f;
+      T cv = 0;
       if (at >= 0) {
         int r = at;
 #pragma unroll
@@ -518,16 +538,15 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
       tcv[lane] = cv;
     }
     __syncthreads();
-    for (int c = lane; c < mo4; c += kWave) {
-      float col[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) col[i] = 0.f;
-      if (c < mo) {
+    if constexpr (sizeof(T) == 8) {
+      for (int c = lane; c < mo; c += kWave) {
+        T* wc = W + kSumsLdw * c;
+        for (int i = 0; i < na; ++i) wc[i] = T(0);
         const int packed = cidx[c];
         for (int t = 0; t < s; ++t) {
           const unsigned pk = tpk[t];
-          float v = tcv[t];
-          if (pk == 0u && v == 0.f) continue;
+          T v = tcv[t];
+          if (pk == 0u && v == T(0)) continue;
           int id = 0;
 #pragma unroll
           for (int d = 0; d < nm; ++d) {
@@ -535,30 +554,52 @@ __global__ void __launch_bounds__(kWave) tensor_sums_mfma_kernel(TensorArgs<floa
             if (d == mode) id = i;
             else v *= Ds[d][((packed >> (8 * d)) & 0xFF) + m[d] * i];
           }
-          // selection order within the column: the same sums as adding element by element
-#pragma unroll
-          for (int i = 0; i < 16; ++i) col[i] += (i == id) ? v : 0.f;
+          wc[id] += v;
         }
       }
+    } else {
+      for (int c = lane; c < mo4; c += kWave) {
+        float col[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) W[i + kSumsLdw * c] = col[i];
+        for (int i = 0; i < 16; ++i) col[i] = 0.f;
+        if (c < mo) {
+          const int packed = cidx[c];
+          for (int t = 0; t < s; ++t) {
+            const unsigned pk = tpk[t];
+            float v = tcv[t];
+            if (pk == 0u && v == 0.f) continue;
+            int id = 0;
+#pragma unroll
+            for (int d = 0; d < nm; ++d) {
+              const int i = (int)((pk >> (8 * d)) & 0xFFu);
+              if (d == mode) id = i;
+              else v *= Ds[d][((packed >> (8 * d)) & 0xFF) + m[d] * i];
+            }
+            // selection order within the column: the same sums as adding element by element
+#pragma unroll
+            for (int i = 0; i < 16; ++i) col[i] += (i == id) ? v : 0.f;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) W[i + kSumsLdw * c] = col[i];
+      }
     }
     __syncthreads();
     for (int c0 = 0; c0 < mo4; c0 += 4) {
       const int c = c0 + kq;
-      const float wv = W[r16 + kSumsLdw * c];
+      const T wv = W[r16 + kSumsLdw * c];
       const int cb = cbase[c];
-      const float yv = (r16 < mr && cb >= 0) ? ys[cb + r16 * stride[mode]] : 0.f;
-      accA = __builtin_amdgcn_mfma_f32_16x16x4f32(wv, wv, accA, 0, 0, 0);
-      accB = __builtin_amdgcn_mfma_f32_16x16x4f32(yv, wv, accB, 0, 0, 0);
+      const T yv = (r16 < mr && cb >= 0) ? ys[cb + r16 * stride[mode]] : T(0);
+      accA = MF::step(wv, wv, accA);
+      accB = MF::step(yv, wv, accB);
     }
   }
-  // tile element (4 kq + v, r16): A[i][j] with i = 4 kq + v, j = r16; B[p][j] likewise
+  // tile element (row(lane, v), r16): A[i][j] with i = row, j = r16; B[p][j] likewise
   const int nent = na * na + mr * na;
   double* row = part + (size_t)blockIdx.x * nent;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const int i = 4 * kq + v, j = r16;
+    const int i = MF::row(lane, v), j = r16;
     if (i < na && j < na) row[i + na * j] = (double)accA[v];
     if (i < mr && j < na) row[na * na + i + mr * j] = (double)accB[v];
   }
@@ -609,24 +650,22 @@ hipError_t launch_tensor_omp(const TensorArgs<T>& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-bool tensor_sums_mfma_ok(int nmodes, const int* m, const int* n, int mode) {
-  return n[mode] <= 16 && m[mode] <= 16 && sums_mfma_lds_bytes(nmodes, m, n, mode) <= 64 * 1024;
+bool tensor_sums_mfma_ok(int nmodes, const int* m, const int* n, int mode, size_t elem) {
+  return n[mode] <= 16 && m[mode] <= 16 && sums_mfma_lds_bytes(nmodes, m, n, mode, elem) <= 64 * 1024;
 }
 
 template <typename T>
 hipError_t launch_tensor_sums(const TensorArgs<T>& a, int mode, double* part, hipStream_t st) {
   const int rows = tensor_sums_rows(a.N);
-  if constexpr (sizeof(T) == 4) {
-    if (tensor_sums_mfma_ok(a.nmodes, a.m, a.n, mode)) {
-      const size_t lds = sums_mfma_lds_bytes(a.nmodes, a.m, a.n, mode);
-      if (a.nmodes == 2)
-        hipLaunchKernelGGL((tensor_sums_mfma_kernel<2>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
-      else if (a.nmodes == 3)
-        hipLaunchKernelGGL((tensor_sums_mfma_kernel<3>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
-      else
-        hipLaunchKernelGGL((tensor_sums_mfma_kernel<4>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
-      return hipGetLastError();
-    }
+  if (tensor_sums_mfma_ok(a.nmodes, a.m, a.n, mode, sizeof(T))) {
+    const size_t lds = sums_mfma_lds_bytes(a.nmodes, a.m, a.n, mode, sizeof(T));
+    if (a.nmodes == 2)
+      hipLaunchKernelGGL((tensor_sums_mfma_kernel<T, 2>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
+    else if (a.nmodes == 3)
+      hipLaunchKernelGGL((tensor_sums_mfma_kernel<T, 3>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
+    else
+      hipLaunchKernelGGL((tensor_sums_mfma_kernel<T, 4>), dim3((unsigned)rows), dim3(kWave), lds, st, a, mode, part);
+    return hipGetLastError();
   }
   const size_t lds = sums_lds_bytes(a.nmodes, a.m, a.n, mode, sizeof(T));
   if (a.nmodes == 2)
@@ -649,13 +688,13 @@ hipError_t launch_tensor_rescale(const TensorArgs<T>& a, int mode, const double*
   return hipGetLastError();
 }
 
-hipError_t launch_kron_tail(const TensorArgs<double>& d, double* Dk, hipStream_t st) {
+hipError_t launch_kron(const TensorArgs<double>& d, int q0, int q1, double* Dk, hipStream_t st) {
   int mk = 1, nk = 1;
-  for (int q = 1; q < d.nmodes; ++q) {
+  for (int q = q0; q < q1; ++q) {
     mk *= d.m[q];
     nk *= d.n[q];
   }
-  hipLaunchKernelGGL(kron_tail_kernel, dim3((unsigned)((mk * nk + 255) / 256)), dim3(256), 0, st, d, Dk, mk, nk);
+  hipLaunchKernelGGL(kron_kernel, dim3((unsigned)((mk * nk + 255) / 256)), dim3(256), 0, st, d, q0, q1, Dk, mk, nk);
   return hipGetLastError();
 }
 
