@@ -44,6 +44,8 @@ struct sdl_proposer {
   float* Z2 = nullptr;
   void* H2 = nullptr;
   float* Z3 = nullptr;
+  int64_t zcap = 0;  // rows of Zl, the logits of the fused forward pass
+  float* Zl = nullptr;
   void* dZ3 = nullptr;
   void* dZ2 = nullptr;
   void* dZ1 = nullptr;
@@ -170,6 +172,43 @@ int train_step(sdl_proposer* P, const float* Y, const int32_t* supp, const int32
   return SDL_OK;
 }
 
+// Buffers for the logits of up to B signals at a time (with a fused forward pass only the logits
+// are stored).
+bool fused_forward(const sdl_proposer* P) { return !P->fp32 && mlp_forward_supported(P->M, P->H, P->A); }
+
+int ensure_logits(sdl_proposer* P, int64_t B) {
+  if (!fused_forward(P)) return ensure_batch(P, B);
+  if (B <= P->zcap) return SDL_OK;
+  ST(dalloc(&P->Zl, (size_t)B * P->A));
+  P->zcap = B;
+  return SDL_OK;
+}
+
+// Logits of n signals into out (n rows; out = nullptr: the network's own buffer); *where points at
+// them.  The unfused path needs ensure_batch for n rounded up to 64 and leaves them in P->Z3.
+int logits_of(sdl_proposer* P, const float* Y, int64_t n, float* out, const float** where, hipStream_t st) {
+  if (fused_forward(P)) {
+    const __bf16* pc = (const __bf16*)P->pc;
+    float* z = out ? out : P->Zl;
+    const MlpForwardArgs g{Y, n, pc + P->off[0], pc + P->off[2], pc + P->off[4], P->p + P->off[1], P->p + P->off[3],
+                           P->p + P->off[5], z, P->H, P->A};
+    HT(launch_mlp_forward(g, st));
+    *where = z;
+    return SDL_OK;
+  }
+  const int64_t B = (n + 63) / 64 * 64;
+  if (P->fp32) {
+    HT(launch_prep_input<float>(Y, nullptr, n, P->M, (float*)P->X, nullptr, st));
+    ST(forward<float>(P, B, false, st));
+  } else {
+    HT(launch_prep_input<__bf16>(Y, nullptr, n, P->M, (__bf16*)P->X, nullptr, st));
+    ST(forward<__bf16>(P, B, false, st));
+  }
+  if (out) HT(hipMemcpyAsync(out, P->Z3, sizeof(float) * n * P->A, hipMemcpyDeviceToDevice, st));
+  *where = P->Z3;
+  return SDL_OK;
+}
+
 int copy_params(sdl_proposer* P, hipStream_t st) {
   if (P->fp32)
     HT(launch_copy_params<float>(P->p, (float*)P->pc, P->np, st));
@@ -198,6 +237,7 @@ int sdl_proposer_create(int32_t m1, int32_t m2, int32_t n1, int32_t n2, int32_t 
   if (M % 64 || A % 64 || hidden % 64 || M > 64)
     return abi_fail(SDL_E_UNSUPPORTED, "the proposal network needs m1*m2 = 64, n1*n2 and hidden multiples of 64");
   if (!propose_supported(n1, n2, 1)) return abi_fail(SDL_E_UNSUPPORTED, "no proposal kernel for this atom count");
+  HT(mlp_init_device());
   sdl_proposer* P = new sdl_proposer();
   P->m1 = m1; P->m2 = m2; P->n1 = n1; P->n2 = n2; P->H = hidden; P->M = M; P->A = A;
   P->fp32 = fp32_check ? 1 : 0;
@@ -244,7 +284,7 @@ int sdl_proposer_create(int32_t m1, int32_t m2, int32_t n1, int32_t n2, int32_t 
 
 void sdl_proposer_destroy(sdl_proposer* P) {
   if (!P) return;
-  void* bufs[] = {P->p, P->m, P->v, P->g, P->pc, P->X, P->Z1, P->H1, P->Z2, P->H2, P->Z3, P->dZ3, P->dZ2, P->dZ1,
+  void* bufs[] = {P->p, P->m, P->v, P->g, P->pc, P->X, P->Z1, P->H1, P->Z2, P->H2, P->Z3, P->Zl, P->dZ3, P->dZ2, P->dZ1,
                   P->loss_part, P->loss, P->idx, P->accept, P->list, P->blk, P->count, P->Dc1, P->Dc2, P->G1c,
                   P->G2c, P->G64, P->ctr};
   for (void* b : bufs)
@@ -402,18 +442,10 @@ int sdl_proposer_logits(sdl_proposer* P, const float* Y, int64_t N, float* logit
   if (N < 0) return abi_fail(SDL_E_INVAL, "N < 0");
   hipStream_t st = (hipStream_t)stream;
   const int64_t chunk = 65536;
-  ST(ensure_batch(P, chunk));
+  if (!fused_forward(P)) ST(ensure_batch(P, chunk));
   for (int64_t k0 = 0; k0 < N; k0 += chunk) {
-    const int64_t n = std::min(chunk, N - k0);
-    const int64_t B = (n + 63) / 64 * 64;
-    if (P->fp32) {
-      HT(launch_prep_input<float>(Y + k0 * P->M, nullptr, n, P->M, (float*)P->X, nullptr, st));
-      ST(forward<float>(P, B, false, st));
-    } else {
-      HT(launch_prep_input<__bf16>(Y + k0 * P->M, nullptr, n, P->M, (__bf16*)P->X, nullptr, st));
-      ST(forward<__bf16>(P, B, false, st));
-    }
-    HT(hipMemcpyAsync(logits + k0 * P->A, P->Z3, sizeof(float) * n * P->A, hipMemcpyDeviceToDevice, st));
+    const float* z;
+    ST(logits_of(P, Y + k0 * P->M, std::min(chunk, N - k0), logits + k0 * P->A, &z, st));
   }
   return SDL_OK;
 }
@@ -424,6 +456,9 @@ int sdl_proposer_logits(sdl_proposer* P, const float* Y, int64_t N, float* logit
 
 namespace sdl {
 
+// Signals proposed for at a time.
+constexpr int64_t kLearnedChunk = 65536;
+
 int learned_prepare(sdl_proposer* P, int64_t N) {
   if (N > P->ncap) {
     ST(dalloc(&P->accept, (size_t)N));
@@ -432,7 +467,7 @@ int learned_prepare(sdl_proposer* P, int64_t N) {
     ST(dalloc(&P->count, 1));
     P->ncap = N;
   }
-  return ensure_batch(P, 65536);
+  return ensure_logits(P, std::min<int64_t>(N > 0 ? (N + 63) / 64 * 64 : 64, kLearnedChunk));
 }
 
 // Proposal + least squares for all signals, then the register-resident 2D-OMP on the
@@ -450,22 +485,15 @@ int learned_code(sdl_proposer* P, const sdl_problem& r, double tau, int32_t* acc
                  hipStream_t st, int64_t* nfallback_host) {
   ST(learned_prepare(P, r.N));
   int32_t* accept = accept_out ? accept_out : P->accept;
-  const int64_t chunk = 65536;
-  ST(ensure_batch(P, chunk));
+  const int64_t chunk = kLearnedChunk;
   const float* Y = (const float*)r.Y;
   for (int64_t k0 = 0; k0 < r.N; k0 += chunk) {
     const int64_t n = std::min(chunk, r.N - k0);
-    const int64_t B = (n + 63) / 64 * 64;
-    if (P->fp32) {
-      HT(launch_prep_input<float>(Y + k0 * P->M, nullptr, n, P->M, (float*)P->X, nullptr, st));
-      ST(forward<float>(P, B, false, st));
-    } else {
-      HT(launch_prep_input<__bf16>(Y + k0 * P->M, nullptr, n, P->M, (__bf16*)P->X, nullptr, st));
-      ST(forward<__bf16>(P, B, false, st));
-    }
+    const float* z = nullptr;
+    ST(logits_of(P, Y + k0 * P->M, n, nullptr, &z, st));
     ProposeArgs pa;
     pa.m1 = r.m1; pa.m2 = r.m2; pa.n1 = r.n1; pa.n2 = r.n2; pa.s = r.s; pa.N = n;
-    pa.logits = P->Z3;
+    pa.logits = z;
     pa.Y = Y + k0 * P->M;
     pa.D1 = omp.D1; pa.D2 = omp.D2; pa.G1 = omp.G1; pa.G2 = omp.G2;
     pa.supp = r.supp + k0 * r.s;

@@ -259,6 +259,128 @@ __global__ void __launch_bounds__(256) gemm_nt_bf16_kernel(GemmArgs g) {
   }
 }
 
+// The whole network for inference in one kernel (BF16): normalisation, three layers, GELU, logits.
+// A workgroup of eight waves carries 64 signals through all layers with the activations in LDS (one
+// buffer: a layer's results wait in registers, already activated and rounded, until every wave has
+// read its inputs), so only the signals are read and only the logits written; the weights (0.9 MB at
+// 512 units) are read from L2 as MFMA fragments, 16 contiguous bytes a lane, the next slice in flight
+// while the current one multiplies.  A wave owns the 16-column tiles w, w + 8, ... of a layer.
+// What bounds it: the vector-ALU instructions of erff (about 45 a value, 2 x 512 values a signal);
+// two workgroups share a CU so that one's products run beside the other's GELUs.  Same operations as
+// the layer-by-layer kernels in the same order, bit for bit: 65,536 signals, 512 units: 60 + 142 +
+// 70 us for the three layers and 17 us for the normalisation before.
+constexpr int kFwdRows = 64, kFwdWaves = 8;
+
+template <int NT>
+__global__ void __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(4)))
+    mlp_forward_kernel(MlpForwardArgs g) {
+  extern __shared__ __align__(16) unsigned char fwd_smem[];
+  __bf16* act = reinterpret_cast<__bf16*>(fwd_smem);
+  const int H = g.H, ld = H + 8;  // 16-byte aligned rows, spread over the banks
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = threadIdx.x % 64;
+  const int r16 = lane % 16, kq = lane / 16;
+  const int64_t row0 = (int64_t)blockIdx.x * kFwdRows;
+  // x = vec(Y) / ||Y||_F: a wave normalises eight signals, lane p holding pixel p
+  constexpr int RW = kFwdRows / kFwdWaves;
+  float y[RW];
+#pragma unroll
+  for (int u = 0; u < RW; ++u) {
+    const int64_t r = row0 + w * RW + u;
+    y[u] = r < g.N ? g.Y[r * 64 + lane] : 0.f;
+  }
+#pragma unroll
+  for (int u = 0; u < RW; ++u) {
+#pragma clang fp contract(off)
+    float q = y[u] * y[u];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+    const float inv = q > 0.f ? rsqrtf(q) : 0.f;
+    act[(w * RW + u) * ld + lane] = (__bf16)(y[u] * inv);
+  }
+  __syncthreads();
+  auto products = [&](const __bf16* W, int K, int ntiles, f32x4(&acc)[4][NT]) __attribute__((always_inline)) {
+    const __bf16* pb[NT];  // uniform: the tiles' first rows (a tile past the last reads the first)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int nt = w + kFwdWaves * j;
+      pb[j] = W + (size_t)(16 * (nt < ntiles ? nt : 0)) * K;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    unsigned ob = (unsigned)(r16 * K + 8 * kq);  // this lane's place in a tile
+    const __bf16* pa = act + r16 * ld + 8 * kq;
+    bf16x8 b[2][NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[0][j] = *reinterpret_cast<const bf16x8*>(pb[j] + ob);
+    for (int k0 = 0; k0 < K; k0 += 64) {  // K is a multiple of 64: two slices a turn
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = k0 + 32 * u;
+        if (k + 32 < K) {
+#pragma unroll
+          for (int j = 0; j < NT; ++j) b[1 - u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + (ob + k + 32));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(pa + 16 * i * ld + k);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[u][j], acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  };
+  auto hidden = [&](const __bf16* W, const float* bias, int K) __attribute__((always_inline)) {
+    f32x4 acc[4][NT];
+    products(W, K, H / 16, acc);
+    unsigned h[4][NT][2];  // the rounded results, in pairs
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int nt = w + kFwdWaves * j;
+      const float bj = bias[16 * (nt < H / 16 ? nt : 0) + r16];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          const __bf16 lo = (__bf16)gelu(acc[i][j][2 * v] + bj), hi = (__bf16)gelu(acc[i][j][2 * v + 1] + bj);
+          h[i][j][v] = __builtin_bit_cast(unsigned short, lo) | (unsigned)__builtin_bit_cast(unsigned short, hi) << 16;
+          asm volatile("" : "+v"(h[i][j][v]));  // finished here, not after the barrier
+        }
+    }
+    __syncthreads();  // every wave has read the layer's inputs
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int nt = w + kFwdWaves * j;
+      if (nt >= H / 16) continue;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          act[(16 * i + 4 * kq + v) * ld + 16 * nt + r16] =
+              __builtin_bit_cast(__bf16, (unsigned short)(h[i][j][v / 2] >> (16 * (v % 2))));
+    }
+    __syncthreads();
+  };
+  hidden(g.W1, g.b1, 64);
+  hidden(g.W2, g.b2, H);
+  f32x4 acc[4][NT];
+  for (int t0 = 0; t0 < g.A / 16; t0 += kFwdWaves * NT) {
+    products(g.W3 + (size_t)16 * t0 * H, H, g.A / 16 - t0, acc);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int nt = w + kFwdWaves * j + t0;
+      if (nt >= g.A / 16) continue;
+      const float bj = g.b3[16 * nt + r16];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t r = row0 + 16 * i + 4 * kq + v;
+          if (r < g.N) g.logits[r * g.A + 16 * nt + r16] = acc[i][j][v] + bj;
+        }
+    }
+  }
+}
+
 // X[b][p] = Y_{idx(b)}[p] / ||Y_{idx(b)}||_F in the compute type (vec order = column-major)
 template <typename T>
 __global__ void prep_input_kernel(const float* Y, const int32_t* idx, int64_t B, int M, T* X, float* ynorm2) {
@@ -366,6 +488,29 @@ hipError_t launch_gemm(const GemmArgs& g, int opA, int opB, hipStream_t st) {
   else if (opA == 1 && opB == 0) hipLaunchKernelGGL((gemm_kernel<T, 1, 0>), grid, dim3(256), 0, st, g);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+bool mlp_forward_supported(int M, int H, int A) { return M == 64 && H % 64 == 0 && H <= 512 && A % 16 == 0; }
+
+hipError_t launch_mlp_forward(const MlpForwardArgs& g, hipStream_t st) {
+  if (g.N <= 0) return hipSuccess;
+  const dim3 grid((unsigned)((g.N + kFwdRows - 1) / kFwdRows)), block(64 * kFwdWaves);
+  const size_t lds = sizeof(__bf16) * (size_t)kFwdRows * (g.H + 8);
+  const int nt = (g.H / 16 + kFwdWaves - 1) / kFwdWaves;
+  switch (nt) {
+    case 1: hipLaunchKernelGGL(mlp_forward_kernel<1>, grid, block, lds, st, g); break;
+    case 2: hipLaunchKernelGGL(mlp_forward_kernel<2>, grid, block, lds, st, g); break;
+    case 3: hipLaunchKernelGGL(mlp_forward_kernel<3>, grid, block, lds, st, g); break;
+    case 4: hipLaunchKernelGGL(mlp_forward_kernel<4>, grid, block, lds, st, g); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t mlp_init_device() {
+  // 64 rows of 520 units: just above the default LDS limit
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_forward_kernel<4>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
 }
 
 template <typename T>

@@ -22,6 +22,20 @@ struct GemmArgs {
   float* Z;           // kEpiBiasGelu: pre-activation out (optional); kEpiGeluGrad: pre-activation in
 };
 
+// Logits of N signals (BF16 weights, inference): one kernel for the whole network where
+// mlp_forward_supported; call mlp_init_device once per device first.
+struct MlpForwardArgs {
+  const float* Y;  // N x 64
+  int64_t N;
+  const __bf16 *W1, *W2, *W3;  // (H x 64), (H x H), (A x H), row-major
+  const float *b1, *b2, *b3;
+  float* logits;  // N x A
+  int H, A;
+};
+bool mlp_forward_supported(int M, int H, int A);
+hipError_t launch_mlp_forward(const MlpForwardArgs& g, hipStream_t st);
+hipError_t mlp_init_device();
+
 template <typename T>
 hipError_t launch_gemm(const GemmArgs& g, int opA, int opB, hipStream_t st);
 template <typename T>
