@@ -33,6 +33,7 @@
 // entry to the next) and folds the step's coefficient into the refresh terms.
 #pragma once
 
+#include "lanes.h"
 #include "sdl_internal.h"
 
 namespace sdl {
@@ -96,32 +97,6 @@ __device__ inline void group_sync() {  // LDS written by this wave is visible to
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int CTRL, int ROWS = 0xF>
-__device__ inline int dpp32(int old, int v) {
-  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xF, false);
-}
-template <int CTRL, int ROWS = 0xF, typename U>
-__device__ inline U dpp(U old, U v) {
-  if constexpr (sizeof(U) == 4) {
-    return __builtin_bit_cast(U, dpp32<CTRL, ROWS>(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v)));
-  } else {
-    const long long o = __builtin_bit_cast(long long, old), b = __builtin_bit_cast(long long, v);
-    const int lo = dpp32<CTRL, ROWS>((int)o, (int)b);
-    const int hi = dpp32<CTRL, ROWS>((int)(o >> 32), (int)(b >> 32));
-    return __builtin_bit_cast(U, ((long long)hi << 32) | (unsigned int)lo);
-  }
-}
-template <typename U>
-__device__ inline U lane_read(U v, int l) {  // l uniform
-  if constexpr (sizeof(U) == 4) {
-    return __builtin_bit_cast(U, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-  } else {
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __builtin_bit_cast(U, ((long long)hi << 32) | (unsigned int)lo);
-  }
-}
-
 // calls f(integral_constant l) or f(int l) for l = l0 .. n-1 in order: compile-time indices where a
 // lane broadcast needs them (G = 16), a runtime loop otherwise.  n is uniform over the wave.
 template <int V>
@@ -161,18 +136,6 @@ __device__ __forceinline__ void downward(int n, F&& f) {
   } else {
 #pragma unroll 1
     for (int l = n - 1; l >= 0; --l) f(l);
-  }
-}
-// lane L's value of v, within each row of sixteen lanes
-template <int L, typename U>
-__device__ inline U bcast16(U v) {
-  if constexpr (sizeof(U) == 4) {
-    return __builtin_bit_cast(U, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x150 + L, 0xF, 0xF, true));
-  } else {  // row_newbcast:L
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x150 + L, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x150 + L, 0xF, 0xF, true);
-    return __builtin_bit_cast(U, ((long long)hi << 32) | (unsigned int)lo);
   }
 }
 // lane l's value of v, within each signal's lanes

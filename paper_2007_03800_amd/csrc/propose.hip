@@ -1,15 +1,23 @@
 // Learned support proposal, inference side: logits -> s atoms -> least squares.
 //
-// Sixteen lanes share a signal (four signals per wave): each lane holds every 16th
-// logit, s rounds of a group arg-max (ties -> smallest atom index) pick the atoms in
-// decreasing logit order, then the group solves the least-squares problem on them with
-// the same Gram entries G1[i,i'] G2[j,j'] as 2D-OMP (Cholesky in FP32 registers,
-// redundantly per lane), forms the residual explicitly and flags the proposal as
-// accepted when ||r||^2 <= tau * ||Y||^2.  Rejected signals are listed (ascending) for
-// the 2D-OMP fallback by a deterministic three-pass compaction.
+// Sixteen lanes (one DPP row) share a signal, four signals per wave: each lane holds every 16th
+// logit, s rounds of a row maximum (ties -> smallest atom index) pick the atoms in decreasing logit
+// order, then the row solves the least-squares problem on them with the same Gram entries
+// G1[i,i'] G2[j,j'] as 2D-OMP: lane t holds row t of the Gram matrix and turns it into row t of its
+// Cholesky factor a column at a time, the column's entries reaching the other lanes by row
+// broadcasts.  The residual is formed explicitly and the proposal accepted when
+// ||r||^2 <= tau * ||Y||^2.  Rejected signals are listed (ascending) for the 2D-OMP fallback by a
+// deterministic three-pass compaction.
+//
+// What bounds it: vector-ALU issue, about half of it the scans of the s rounds.  The earlier form
+// factored the Gram matrix redundantly in every lane, with LDS permutes for every reduction and an
+// integer division per table index; every entry is still computed by the same operations in the
+// same order (written out below, so that a product and a subtraction fuse where they did), bit for
+// bit.
 #include <limits.h>
 #include <math.h>
 
+#include "lanes.h"
 #include "mlp_internal.h"
 
 namespace sdl {
@@ -17,14 +25,42 @@ namespace {
 
 constexpr int kGroup = 16;
 
-__device__ inline float group16_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < kGroup; o <<= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+__device__ inline float row16_sum(float v) {
+  v += dpp<kDppXor1>(v, v);
+  v += dpp<kDppXor2>(v, v);
+  v += dpp<kDppHalfMirror>(v, v);
+  return v + dpp<kDppMirror>(v, v);
+}
+__device__ inline float row16_max(float v) {
+  v = fmaxf(v, dpp<kDppXor1>(v, v));
+  v = fmaxf(v, dpp<kDppXor2>(v, v));
+  v = fmaxf(v, dpp<kDppHalfMirror>(v, v));
+  return fmaxf(v, dpp<kDppMirror>(v, v));
+}
+__device__ inline int row16_min(int v) {
+  v = min(v, dpp<kDppXor1>(v, v));
+  v = min(v, dpp<kDppXor2>(v, v));
+  v = min(v, dpp<kDppHalfMirror>(v, v));
+  return min(v, dpp<kDppMirror>(v, v));
+}
+
+// f(IntC<0>) ... f(IntC<N - 1>)
+template <int V>
+struct IntC {
+  static constexpr int value = V;
+  __device__ constexpr operator int() const { return V; }
+};
+template <int L, int N, class F>
+__device__ __forceinline__ void each(F&& f) {
+  if constexpr (L < N) {
+    f(IntC<L>{});
+    each<L + 1, N>(f);
+  }
 }
 
 template <int VPL, int SMAX>
 __global__ void __launch_bounds__(256) propose_kernel(ProposeArgs a) {
+#pragma clang fp contract(off)
   extern __shared__ __align__(16) float sm[];
   const int m1 = a.m1, m2 = a.m2, n1 = a.n1, n2 = a.n2, s = a.s, M = m1 * m2, A = n1 * n2;
   float* sG1 = sm;
@@ -39,125 +75,125 @@ __global__ void __launch_bounds__(256) propose_kernel(ProposeArgs a) {
   const int sub = threadIdx.x % kGroup;
   const int64_t k = (int64_t)blockIdx.x * (blockDim.x / kGroup) + threadIdx.x / kGroup;
   const bool valid = k < a.N;
+  // a / n1 of an atom (a < 256) and e / m1 of a pixel (e < 64) by multiplication
+  const int inv_n1 = 65536 / n1 + 1, inv_m1 = 65536 / m1 + 1;
 
   float v[VPL];
 #pragma unroll
   for (int u = 0; u < VPL; ++u) v[u] = valid ? a.logits[k * A + sub + kGroup * u] : -INFINITY;
-  int sel[SMAX];
-#pragma unroll
-  for (int t = 0; t < SMAX; ++t) {
-    sel[t] = 0;
+  int si[SMAX], sj[SMAX];  // the chosen atoms
+  int mi = 0, mj = 0;      // lane t: the t-th
+  each<0, SMAX>([&](auto t) __attribute__((always_inline)) {
+    si[t] = sj[t] = 0;
     if (t < s) {
-      float bv = -INFINITY;
-      int ba = INT_MAX;
+      float bv = v[0];
 #pragma unroll
-      for (int u = 0; u < VPL; ++u) {
-        const bool c = v[u] > bv;
-        bv = c ? v[u] : bv;
-        ba = c ? sub + kGroup * u : ba;
-      }
+      for (int u = 1; u < VPL; ++u) bv = fmaxf(bv, v[u]);
+      bv = row16_max(bv);
+      int bu = INT_MAX;  // the smallest u that holds it
 #pragma unroll
-      for (int o = 1; o < kGroup; o <<= 1) {
-        const float ov = __shfl_xor(bv, o, kWave);
-        const int oa = __shfl_xor(ba, o, kWave);
-        const bool c = ov > bv || (ov == bv && oa < ba);
-        bv = c ? ov : bv;
-        ba = c ? oa : ba;
-      }
-      sel[t] = ba < A ? ba : 0;
+      for (int u = VPL - 1; u >= 0; --u) bu = v[u] == bv ? u : bu;
+      // (-infinity is a logit already taken, and NaN never the largest: no atom is left then)
+      const bool any = bv > -INFINITY;
+      const int ba = row16_min(any && bu != INT_MAX ? sub + kGroup * bu : INT_MAX);
+      const int own = (ba & (kGroup - 1)) == sub && ba != INT_MAX ? ba / kGroup : -1;
 #pragma unroll
-      for (int u = 0; u < VPL; ++u) v[u] = (sub + kGroup * u == ba) ? -INFINITY : v[u];
+      for (int u = 0; u < VPL; ++u) v[u] = u == own ? -INFINITY : v[u];
+      const int at = ba < A ? ba : 0;
+      sj[t] = (at * inv_n1) >> 16;
+      si[t] = at - n1 * sj[t];
+      mi = sub == t ? si[t] : mi;
+      mj = sub == t ? sj[t] : mj;
     }
-  }
+  });
   // least squares on the proposed support
   const float* y = a.Y + (valid ? k : 0) * M;
   float yl[4];
+  int pix1[4], pix2[4];
   float yy = 0.f;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     const int e = sub + kGroup * w;
     yl[w] = (valid && e < M) ? y[e] : 0.f;
-    yy += yl[w] * yl[w];
+    yy = __builtin_fmaf(yl[w], yl[w], yy);
+    const int ec = e < M ? e : 0;
+    pix2[w] = (ec * inv_m1) >> 16;
+    pix1[w] = ec - m1 * pix2[w];
   }
-  yy = group16_sum(yy);
-  float cs[SMAX], x[SMAX];
-#pragma unroll
-  for (int t = 0; t < SMAX; ++t) {
-    cs[t] = 0.f;
+  yy = row16_sum(yy);
+  float b = 0.f;  // lane t: the correlation of atom t
+  each<0, SMAX>([&](auto t) __attribute__((always_inline)) {
     if (t < s) {
-      const int i = sel[t] % n1, j = sel[t] / n1;
+      const float *d1 = sD1 + m1 * si[t], *d2 = sD2 + m2 * sj[t];
       float c = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int e = sub + kGroup * w;
-        if (e < M) c += yl[w] * sD1[e % m1 + m1 * i] * sD2[e / m1 + m2 * j];
-      }
-      cs[t] = group16_sum(c);
+      for (int w = 0; w < 4; ++w) c = __builtin_fmaf(yl[w] * d1[pix1[w]], d2[pix2[w]], c);
+      c = row16_sum(c);
+      b = sub == t ? c : b;
     }
-  }
-  // Cholesky of the support Gram matrix (packed lower triangle), then L L^T x = cs
-  float L[SMAX * (SMAX + 1) / 2];
-  bool ok = valid;
+  });
+  // Cholesky of the support Gram matrix: lane t turns row t of the Gram matrix into row t of L
+  float p1[SMAX], p2[SMAX], L[SMAX], diag[SMAX];
 #pragma unroll
-  for (int t = 0; t < SMAX; ++t) {
+  for (int u = 0; u < SMAX; ++u) {
+    p1[u] = sG1[mi + n1 * si[u]];
+    p2[u] = sG2[mj + n2 * sj[u]];
+    L[u] = p1[u] * p2[u];
+  }
+  bool bad = !valid;
+  each<0, SMAX>([&](auto l) __attribute__((always_inline)) {
+    diag[l] = 1.f;
+    if (l < s) {
+      const float d = bcast16<l.value>(L[l]);
+      bad = bad || (sub == l && !(L[l] > 1e-6f * (p1[l] * p2[l])));
+      diag[l] = d > 0.f ? sqrtf(d) : 1.f;
+      L[l] = L[l] / diag[l];
+      each<l.value + 1, SMAX>([&](auto u) __attribute__((always_inline)) {
+        const float o = bcast16<u.value>(L[l]);
+        L[u] = l == 0 ? __builtin_fmaf(p1[u], p2[u], -(L[l] * o)) : __builtin_fmaf(-L[l], o, L[u]);
+      });
+    }
+  });
+  // L L^T x = c: forward a column at a time, back a row at a time
+  float x[SMAX];
+  each<0, SMAX>([&](auto l) __attribute__((always_inline)) {
+    x[l] = 0.f;
+    if (l < s) {
+      x[l] = bcast16<l.value>(b) / diag[l];
+      b = __builtin_fmaf(-L[l], x[l], b);
+    }
+  });
+  each<0, SMAX>([&](auto r) __attribute__((always_inline)) {
+    constexpr int t = SMAX - 1 - r.value;
     if (t < s) {
-      const int it = sel[t] % n1, jt = sel[t] / n1;
-#pragma unroll
-      for (int u = 0; u <= t; ++u) {
-        const int iu = sel[u] % n1, ju = sel[u] / n1;
-        float g = sG1[it + n1 * iu] * sG2[jt + n2 * ju];
-#pragma unroll
-        for (int l = 0; l < u; ++l) g -= L[t * (t + 1) / 2 + l] * L[u * (u + 1) / 2 + l];
-        if (u < t) {
-          L[t * (t + 1) / 2 + u] = g / L[u * (u + 1) / 2 + u];
-        } else {
-          const float gaa = sG1[it + n1 * it] * sG2[jt + n2 * jt];
-          ok = ok && g > 1e-6f * gaa;
-          L[t * (t + 1) / 2 + t] = g > 0.f ? sqrtf(g) : 1.f;
-        }
-      }
+      float q = x[t];
+      each<t + 1, SMAX>([&](auto l) __attribute__((always_inline)) {
+        const float o = bcast16<l.value>(L[t]);
+        if (l < s) q = __builtin_fmaf(-o, x[l], q);
+      });
+      x[t] = q / diag[t];
     }
-  }
-#pragma unroll
-  for (int t = 0; t < SMAX; ++t) {
-    x[t] = 0.f;
+  });
+  float rr = 0.f, mx = 0.f;
+  float r[4] = {yl[0], yl[1], yl[2], yl[3]};
+  each<0, SMAX>([&](auto t) __attribute__((always_inline)) {
     if (t < s) {
-      float b = cs[t];
+      const float *d1 = sD1 + m1 * si[t], *d2 = sD2 + m2 * sj[t];
 #pragma unroll
-      for (int l = 0; l < t; ++l) b -= L[t * (t + 1) / 2 + l] * x[l];
-      x[t] = b / L[t * (t + 1) / 2 + t];
+      for (int w = 0; w < 4; ++w) r[w] = __builtin_fmaf(-(x[t] * d1[pix1[w]]), d2[pix2[w]], r[w]);
+      mx = sub == t ? x[t] : mx;
     }
-  }
+  });
 #pragma unroll
-  for (int t = SMAX - 1; t >= 0; --t) {
-    if (t < s) {
-      float b = x[t];
-#pragma unroll
-      for (int l = t + 1; l < SMAX; ++l)
-        if (l < s) b -= L[l * (l + 1) / 2 + t] * x[l];
-      x[t] = b / L[t * (t + 1) / 2 + t];
-    }
-  }
-  float rr = 0.f;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const int e = sub + kGroup * w;
-    if (e < M) {
-      float r = yl[w];
-#pragma unroll
-      for (int t = 0; t < SMAX; ++t)
-        if (t < s) r -= x[t] * sD1[e % m1 + m1 * (sel[t] % n1)] * sD2[e / m1 + m2 * (sel[t] / n1)];
-      rr += r * r;
-    }
-  }
-  rr = group16_sum(rr);
+  for (int w = 0; w < 4; ++w)
+    if (sub + kGroup * w < M) rr = __builtin_fmaf(r[w], r[w], rr);
+  rr = row16_sum(rr);
+  const unsigned long long bads = __ballot(bad) >> (threadIdx.x % kWave / kGroup * kGroup);
+  const bool ok = (bads & ((1u << kGroup) - 1u)) == 0;
   if (valid) {
-#pragma unroll
-    for (int t = 0; t < SMAX; ++t) {
-      if (t < s && t % kGroup == sub) {
-        a.supp[k * s + t] = sel[t];
-        a.coef[k * s + t] = ok ? x[t] : 0.f;
-      }
+    if (sub < s) {
+      a.supp[k * s + sub] = mi + n1 * mj;
+      a.coef[k * s + sub] = ok ? mx : 0.f;
     }
     if (sub == 0) {
       if (a.res2) a.res2[k] = rr;
@@ -182,15 +218,32 @@ __global__ void __launch_bounds__(kCompact) compact_count_kernel(const int32_t* 
   }
 }
 
-__global__ void compact_scan_kernel(int32_t* blkcount, int nblk, int32_t* count) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Exclusive sums of the block counts (one workgroup, kCompact counts a pass; one lane walking them
+// took 92 us at 977 blocks).
+__global__ void __launch_bounds__(kCompact) compact_scan_kernel(int32_t* blkcount, int nblk, int32_t* count) {
+  __shared__ int ws[kCompact / kWave];
+  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
   int run = 0;
-  for (int b = 0; b < nblk; ++b) {
-    const int c = blkcount[b];
-    blkcount[b] = run;
-    run += c;
+  for (int b0 = 0; b0 < nblk; b0 += kCompact) {
+    const int b = b0 + (int)threadIdx.x;
+    const int c = b < nblk ? blkcount[b] : 0;
+    int inc = c;  // inclusive within the wave
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int up = __shfl_up(inc, o, kWave);
+      if (lane >= o) inc += up;
+    }
+    if (lane == kWave - 1) ws[w] = inc;
+    __syncthreads();
+    int base = run;
+    for (int q = 0; q < kCompact / kWave; ++q) {
+      if (q < w) base += ws[q];
+      run += ws[q];
+    }
+    if (b < nblk) blkcount[b] = base + inc - c;
+    __syncthreads();
   }
-  *count = run;
+  if (threadIdx.x == 0) *count = run;
 }
 
 __global__ void __launch_bounds__(kCompact) compact_write_kernel(const int32_t* accept, int64_t N, const int32_t* offs,
@@ -238,7 +291,7 @@ hipError_t launch_compact_rejected(const int32_t* accept, int64_t N, int32_t* bl
   const int nblk = compact_blocks(N);
   if (nblk == 0) return hipSuccess;
   hipLaunchKernelGGL(compact_count_kernel, dim3(nblk), dim3(kCompact), 0, st, accept, N, blkcount);
-  hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(64), 0, st, blkcount, nblk, count);
+  hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(kCompact), 0, st, blkcount, nblk, count);
   hipLaunchKernelGGL(compact_write_kernel, dim3(nblk), dim3(kCompact), 0, st, accept, N, blkcount, list);
   return hipGetLastError();
 }
