@@ -44,6 +44,7 @@ struct sdl_proposer {
   float* Z2 = nullptr;
   void* H2 = nullptr;
   float* Z3 = nullptr;
+  float* part = nullptr;  // kGradSplits gradients (BF16)
   int64_t zcap = 0;  // rows of Zl, the logits of the fused forward pass
   float* Zl = nullptr;
   void* dZ3 = nullptr;
@@ -102,7 +103,10 @@ int dalloc(F** ptr, size_t n) {
   return SDL_OK;
 }
 
+constexpr int kGradSplits = 8;  // partial gradients at most (one per 256 signals of the batch)
+
 int ensure_batch(sdl_proposer* P, int64_t B) {
+  if (!P->fp32 && !P->part) ST(dalloc(&P->part, (size_t)kGradSplits * P->np));
   if (B <= P->cap) return SDL_OK;
   const int64_t c = B;
   ST(dalloc((char**)&P->X, (size_t)c * P->M * P->elem));
@@ -140,24 +144,51 @@ int forward(sdl_proposer* P, int64_t B, bool keep, hipStream_t st) {
   return SDL_OK;
 }
 
-// gradient of the mean BCE into P->g for the batch rows idx (or 0..B-1), loss into P->loss
-template <typename T>
-int backward(sdl_proposer* P, const int32_t* supp, const int32_t* idx, int s, int64_t B, hipStream_t st) {
-  const T* pc = (const T*)P->pc;
+// gradient of the mean BCE into P->g for the batch rows idx (or 0..B-1), loss into P->loss (FP32 check
+// mode)
+int backward_f32(sdl_proposer* P, const int32_t* supp, const int32_t* idx, int s, int64_t B, hipStream_t st) {
+  const float* pc = (const float*)P->pc;
   const int H = P->H, M = P->M, A = P->A;
   float* g = P->g;
-  HT(launch_bce_grad<T>(P->Z3, supp, idx, B, A, s, (T*)P->dZ3, P->loss_part, P->loss, st));
+  HT(launch_bce_grad<float>(P->Z3, supp, idx, B, A, s, (float*)P->dZ3, P->loss_part, P->loss, st));
   // layer 3
-  ST(gemm<T>(P->dZ3, 1, P->H2, 0, g + P->off[4], A, H, (int)B, A, H, H, kEpiStoreF32, nullptr, nullptr, st));
-  HT(launch_bias_grad<T>((const T*)P->dZ3, B, A, g + P->off[5], st));
-  ST(gemm<T>(P->dZ3, 0, pc + P->off[4], 0, P->dZ2, (int)B, H, A, A, H, H, kEpiGeluGrad, nullptr, P->Z2, st));
+  ST(gemm<float>(P->dZ3, 1, P->H2, 0, g + P->off[4], A, H, (int)B, A, H, H, kEpiStoreF32, nullptr, nullptr, st));
+  HT(launch_bias_grad((const float*)P->dZ3, B, A, g + P->off[5], st));
+  ST(gemm<float>(P->dZ3, 0, pc + P->off[4], 0, P->dZ2, (int)B, H, A, A, H, H, kEpiGeluGrad, nullptr, P->Z2, st));
   // layer 2
-  ST(gemm<T>(P->dZ2, 1, P->H1, 0, g + P->off[2], H, H, (int)B, H, H, H, kEpiStoreF32, nullptr, nullptr, st));
-  HT(launch_bias_grad<T>((const T*)P->dZ2, B, H, g + P->off[3], st));
-  ST(gemm<T>(P->dZ2, 0, pc + P->off[2], 0, P->dZ1, (int)B, H, H, H, H, H, kEpiGeluGrad, nullptr, P->Z1, st));
+  ST(gemm<float>(P->dZ2, 1, P->H1, 0, g + P->off[2], H, H, (int)B, H, H, H, kEpiStoreF32, nullptr, nullptr, st));
+  HT(launch_bias_grad((const float*)P->dZ2, B, H, g + P->off[3], st));
+  ST(gemm<float>(P->dZ2, 0, pc + P->off[2], 0, P->dZ1, (int)B, H, H, H, H, H, kEpiGeluGrad, nullptr, P->Z1, st));
   // layer 1
-  ST(gemm<T>(P->dZ1, 1, P->X, 0, g + P->off[0], H, M, (int)B, H, M, M, kEpiStoreF32, nullptr, nullptr, st));
-  HT(launch_bias_grad<T>((const T*)P->dZ1, B, H, g + P->off[1], st));
+  ST(gemm<float>(P->dZ1, 1, P->X, 0, g + P->off[0], H, M, (int)B, H, M, M, kEpiStoreF32, nullptr, nullptr, st));
+  HT(launch_bias_grad((const float*)P->dZ1, B, H, g + P->off[1], st));
+  return SDL_OK;
+}
+
+// The same for BF16 (operands of the launches on the matrix cores): each layer's weight gradient runs
+// beside the gradient it passes down, split over the batch into S partials that hold every
+// parameter's share (the bias gradients are the row sums of the same operands).
+int backward_bf16(sdl_proposer* P, const int32_t* supp, const int32_t* idx, int s, int64_t B, hipStream_t st) {
+  const __bf16* pc = (const __bf16*)P->pc;
+  const int H = P->H, M = P->M, A = P->A;
+  const int S = (int)std::min<int64_t>(kGradSplits, std::max<int64_t>(1, B / 256));
+  float* part = P->part;
+  HT(launch_bce_grad<__bf16>(P->Z3, supp, idx, B, A, s, (__bf16*)P->dZ3, P->loss_part, nullptr, st));
+  auto wgrad = [&](const void* dZ, const void* in, int layer, int rows, int cols) {
+    return GemmJob{{dZ, in, part + P->off[2 * layer], rows, cols, (int)B, rows, cols, cols, kEpiStoreF32, nullptr, nullptr},
+                   1, 0, part + P->off[2 * layer + 1], S, P->np};
+  };
+  auto dgrad = [&](const void* dZ, int layer, int rows, int cols, void* out, float* Z) {
+    return GemmJob{{dZ, pc + P->off[2 * layer], out, (int)B, cols, rows, rows, cols, cols, kEpiGeluGrad, nullptr, Z},
+                   0, 0, nullptr, 1, 0};
+  };
+  const GemmJob l3[2] = {dgrad(P->dZ3, 2, A, H, P->dZ2, P->Z2), wgrad(P->dZ3, P->H2, 2, A, H)};
+  HT(launch_gemm_batch(l3, 2, st));
+  const GemmJob l2[2] = {dgrad(P->dZ2, 1, H, H, P->dZ1, P->Z1), wgrad(P->dZ2, P->H1, 1, H, H)};
+  HT(launch_gemm_batch(l2, 2, st));
+  const GemmJob l1[1] = {wgrad(P->dZ1, P->X, 0, H, M)};
+  HT(launch_gemm_batch(l1, 1, st));
+  HT(launch_gather_grad(part, S, P->np, P->g, P->loss_part, B, A, P->loss, st));
   return SDL_OK;
 }
 
@@ -166,7 +197,10 @@ int train_step(sdl_proposer* P, const float* Y, const int32_t* supp, const int32
                hipStream_t st) {
   HT(launch_prep_input<T>(Y, idx, B, P->M, (T*)P->X, nullptr, st));
   ST(forward<T>(P, B, true, st));
-  ST(backward<T>(P, supp, idx, s, B, st));
+  if constexpr (sizeof(T) == 2)
+    ST(backward_bf16(P, supp, idx, s, B, st));
+  else
+    ST(backward_f32(P, supp, idx, s, B, st));
   P->step += 1;
   HT(launch_adam<T>(P->p, P->m, P->v, P->g, (T*)P->pc, P->np, lr, P->step, st));
   return SDL_OK;
@@ -284,7 +318,7 @@ int sdl_proposer_create(int32_t m1, int32_t m2, int32_t n1, int32_t n2, int32_t 
 
 void sdl_proposer_destroy(sdl_proposer* P) {
   if (!P) return;
-  void* bufs[] = {P->p, P->m, P->v, P->g, P->pc, P->X, P->Z1, P->H1, P->Z2, P->H2, P->Z3, P->Zl, P->dZ3, P->dZ2, P->dZ1,
+  void* bufs[] = {P->p, P->m, P->v, P->g, P->pc, P->X, P->Z1, P->H1, P->Z2, P->H2, P->Z3, P->Zl, P->part, P->dZ3, P->dZ2, P->dZ1,
                   P->loss_part, P->loss, P->idx, P->accept, P->list, P->blk, P->count, P->Dc1, P->Dc2, P->G1c,
                   P->G2c, P->G64, P->ctr};
   for (void* b : bufs)
@@ -323,11 +357,11 @@ int sdl_proposer_gradient(sdl_proposer* P, const float* Y, const int32_t* supp, 
   if (P->fp32) {
     HT(launch_prep_input<float>(Y, nullptr, B, P->M, (float*)P->X, nullptr, st));
     ST(forward<float>(P, B, true, st));
-    ST(backward<float>(P, supp, nullptr, s, B, st));
+    ST(backward_f32(P, supp, nullptr, s, B, st));
   } else {
     HT(launch_prep_input<__bf16>(Y, nullptr, B, P->M, (__bf16*)P->X, nullptr, st));
     ST(forward<__bf16>(P, B, true, st));
-    ST(backward<__bf16>(P, supp, nullptr, s, B, st));
+    ST(backward_bf16(P, supp, nullptr, s, B, st));
   }
   HT(hipStreamSynchronize(st));
   if (grad_host) HT(hipMemcpy(grad_host, P->g, sizeof(float) * P->np, hipMemcpyDeviceToHost));

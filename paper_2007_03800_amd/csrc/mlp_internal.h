@@ -36,6 +36,21 @@ bool mlp_forward_supported(int M, int H, int A);
 hipError_t launch_mlp_forward(const MlpForwardArgs& g, hipStream_t st);
 hipError_t mlp_init_device();
 
+// Up to three independent BF16 GEMMs in one launch (operand pointers 16-byte aligned; M, N and K
+// multiples of 64).  ksplit > 1: K split over that many workgroups per tile, split q's result
+// part_stride * q floats after C (kEpiStoreF32 without bias); rowsum: A's row sums over k, likewise.
+struct GemmJob {
+  GemmArgs g;
+  int opA, opB;
+  float* rowsum;
+  int ksplit;
+  int64_t part_stride;
+};
+hipError_t launch_gemm_batch(const GemmJob* jobs, int n, hipStream_t st);
+// g = the S partials (n floats each) added in order; *loss = the B loss parts' sum / (B A)
+hipError_t launch_gather_grad(const float* part, int S, int64_t n, float* g, const double* loss_part, int64_t B, int A,
+                              double* loss, hipStream_t st);
+
 template <typename T>
 hipError_t launch_gemm(const GemmArgs& g, int opA, int opB, hipStream_t st);
 template <typename T>
@@ -43,8 +58,7 @@ hipError_t launch_prep_input(const float* Y, const int32_t* idx, int64_t B, int 
 template <typename T>
 hipError_t launch_bce_grad(const float* Z, const int32_t* supp, const int32_t* idx, int64_t B, int A, int s, T* dZ,
                            double* loss_part, double* loss, hipStream_t st);
-template <typename T>
-hipError_t launch_bias_grad(const T* dZ, int64_t B, int N, float* db, hipStream_t st);
+hipError_t launch_bias_grad(const float* dZ, int64_t B, int N, float* db, hipStream_t st);
 template <typename T>
 hipError_t launch_adam(float* p, float* m, float* v, const float* g, T* pc, int64_t n, float lr, int step,
                        hipStream_t st);
