@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(kWave* kOWaves) ortho_code_kernel(OmpArgs<T> a
 // leaves the dictionary unchanged and sets the singular status.
 template <typename T>
 __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restrict__ src, int nrow, int ld, int n,
-                                                           double* D, T* Dc, double* G64, T* Gc, int* status,
+                                                           double* D, T* Dc, T* Gc, int* status,
                                                            unsigned long long* counters) {
   __shared__ double W[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];  // column-major n x n
   __shared__ double V[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];
@@ -345,7 +345,6 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     for (int c = 0; c < n; ++c) {
       double v = 0.0;
       for (int r = 0; r < n; ++r) v += Dn[r + n * x] * Dn[r + n * c];
-      G64[x + n * c] = v;
       Gc[x + n * c] = (T)v;
     }
 }
@@ -375,9 +374,9 @@ hipError_t launch_ortho_code(const OmpArgs<T>& a, hipStream_t st) {
 }
 
 template <typename T>
-hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, double* G64, T* Gc,
+hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, T* Gc,
                              int* status, unsigned long long* counters, hipStream_t st) {
-  hipLaunchKernelGGL(procrustes_kernel<T>, dim3(1), dim3(kWave), 0, st, src, nrow, ld, n, D, Dc, G64, Gc, status,
+  hipLaunchKernelGGL(procrustes_kernel<T>, dim3(1), dim3(kWave), 0, st, src, nrow, ld, n, D, Dc, Gc, status,
                      counters);
   return hipGetLastError();
 }
@@ -393,9 +392,9 @@ hipError_t ortho_init_device() {
 
 template hipError_t launch_ortho_code<float>(const OmpArgs<float>&, hipStream_t);
 template hipError_t launch_ortho_code<double>(const OmpArgs<double>&, hipStream_t);
-template hipError_t launch_procrustes<float>(const double*, int, int, int, double*, float*, double*, float*, int*,
+template hipError_t launch_procrustes<float>(const double*, int, int, int, double*, float*, float*, int*,
                                              unsigned long long*, hipStream_t);
-template hipError_t launch_procrustes<double>(const double*, int, int, int, double*, double*, double*, double*, int*,
+template hipError_t launch_procrustes<double>(const double*, int, int, int, double*, double*, double*, int*,
                                               unsigned long long*, hipStream_t);
 
 }  // namespace sdl

@@ -258,8 +258,6 @@ int validate(const sdl_problem* p, int32_t nprob, const Opt& o, bool need_codes_
 struct PBuf {
   void* Dc1;  // compute-type copies
   void* Dc2;
-  double* G1_64;
-  double* G2_64;
   void* G1c;
   void* G2c;
   double* part;   // workgroup / wave partial rows of the TMOD sums
@@ -275,6 +273,8 @@ struct Plan {
   int* status;
   unsigned long long* counters;
   int* iter;     // per-problem RMSE counters
+  int* done;     // per-problem workgroup counters of the residual sums (null: codes only)
+  int nprob = 1;
   bool ybf16 = false;  // signals are bfloat16 (SDL_BF16, SDL_MIXED_BF16)
   double* trace; // device trace
   size_t bytes;
@@ -288,14 +288,18 @@ void layout(const sdl_problem* p, int nprob, size_t elem, int K, void* base, Pla
   pl->status = b.take<int>(4);
   pl->counters = b.take<unsigned long long>(kNumCounters);
   pl->iter = b.take<int>(nprob > 0 ? nprob : 1);
+  pl->done = codes_only ? nullptr : b.take<int>(nprob > 0 ? nprob : 1);
+  pl->nprob = nprob > 0 ? nprob : 1;
   pl->trace = b.take<double>((size_t)(nprob > 0 ? nprob : 1) * (K + 1));
   for (int q = 0; q < nprob; ++q) {
     const sdl_problem& r = p[q];
     PBuf& x = pl->pb[q];
     x.Dc1 = b.take<char>(elem * r.m1 * r.n1);
     x.Dc2 = b.take<char>(elem * r.m2 * r.n2);
-    x.G1_64 = b.take<double>((size_t)r.n1 * r.n1);
-    x.G2_64 = b.take<double>((size_t)r.n2 * r.n2);
+    // 8 bytes per Gram entry beside its compute-type copy: part of the size that the interface states
+    // for a problem's scratch, so what fits a given buffer stays as it was
+    b.take<double>((size_t)r.n1 * r.n1);
+    b.take<double>((size_t)r.n2 * r.n2);
     x.G1c = b.take<char>(elem * r.n1 * r.n1);
     x.G2c = b.take<char>(elem * r.n2 * r.n2);
     if (codes_only) {
@@ -456,10 +460,31 @@ int run_omp(const sdl_problem& r, const PBuf& b, const Opt& o, const Plan& pl, i
 }
 
 template <typename T>
-int run_prep(const sdl_problem& r, const PBuf& b, Launcher& L) {
+PrepJob<T> prep_job(const double* D, int mr, int na, void* Dc, void* Gc) {
+  PrepJob<T> j{};
+  j.nfac = 1;
+  j.m[0] = mr;
+  j.n[0] = na;
+  j.F[0] = D;
+  j.Dc = (T*)Dc;
+  j.Gc = (T*)Gc;
+  return j;
+}
+
+// The start of a call, one launch: its status words and counters zeroed and the dictionaries of its
+// problems prepared (with skip_empty only those of problems with signals).
+template <typename T>
+int start_call(const sdl_problem* p, int nprob, const Plan& pl, bool skip_empty, Launcher& L) {
+  std::vector<PrepJob<T>> jobs;
+  for (int q = 0; q < nprob; ++q) {
+    if (skip_empty && p[q].N == 0) continue;
+    jobs.push_back(prep_job<T>(p[q].D1, p[q].m1, p[q].n1, pl.pb[q].Dc1, pl.pb[q].G1c));
+    jobs.push_back(prep_job<T>(p[q].D2, p[q].m2, p[q].n2, pl.pb[q].Dc2, pl.pb[q].G2c));
+  }
+  int* const zero[] = {pl.status, (int*)pl.counters, pl.iter, pl.done};
+  const int nzero[] = {4, 2 * kNumCounters, pl.nprob, pl.done ? pl.nprob : 0};
   SDL_TRY(L.begin(4));
-  HIP_TRY(launch_dict_prep<T>(r.D1, r.m1, r.n1, (T*)b.Dc1, b.G1_64, (T*)b.G1c, L.st));
-  HIP_TRY(launch_dict_prep<T>(r.D2, r.m2, r.n2, (T*)b.Dc2, b.G2_64, (T*)b.G2c, L.st));
+  HIP_TRY(launch_call_prep<T>(jobs.data(), (int)jobs.size(), zero, nzero, 4, L.st));
   return L.end();
 }
 
@@ -484,10 +509,10 @@ int run_reduce_solve(int side, const sdl_problem& r, const PBuf& b, const Plan& 
     // Remark 1: the orthogonal Procrustes update from the B block of the reduced sums
     SDL_TRY(L.begin(3));
     if (side == 1)
-      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n1, r.D1, (T*)b.Dc1, b.G1_64, (T*)b.G1c, pl.status, pl.counters,
+      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n1, r.D1, (T*)b.Dc1, (T*)b.G1c, pl.status, pl.counters,
                                    L.st));
     else
-      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n2, r.D2, (T*)b.Dc2, b.G2_64, (T*)b.G2c, pl.status, pl.counters,
+      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n2, r.D2, (T*)b.Dc2, (T*)b.G2c, pl.status, pl.counters,
                                    L.st));
     return L.end();
   }
@@ -495,10 +520,10 @@ int run_reduce_solve(int side, const sdl_problem& r, const PBuf& b, const Plan& 
   if (rmse_q >= 0) ro = RmseOut{pl.trace, pl.iter + rmse_q, rmse_q * (K + 1), nent, (double)r.N * r.m1 * r.m2};
   SDL_TRY(L.begin(3));
   if (side == 1)
-    HIP_TRY(launch_tmod_solve<T>(src, nrow, ld, b.sums, r.m1, r.n1, r.D1, (T*)b.Dc1, b.G1_64, (T*)b.G1c, b.w,
+    HIP_TRY(launch_tmod_solve<T>(src, nrow, ld, b.sums, r.m1, r.n1, r.D1, (T*)b.Dc1, (T*)b.G1c, b.w,
                                  pl.status, pl.counters, ro, L.st));
   else
-    HIP_TRY(launch_tmod_solve<T>(src, nrow, ld, b.sums, r.m2, r.n2, r.D2, (T*)b.Dc2, b.G2_64, (T*)b.G2c, b.w,
+    HIP_TRY(launch_tmod_solve<T>(src, nrow, ld, b.sums, r.m2, r.n2, r.D2, (T*)b.Dc2, (T*)b.G2c, b.w,
                                  pl.status, pl.counters, ro, L.st));
   return L.end();
 }
@@ -558,17 +583,9 @@ int run_update(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, co
 template <typename T>
 int run_rmse(const sdl_problem& r, const PBuf& b, const Plan& pl, int q, int K, Launcher& L) {
   SDL_TRY(L.begin(5));
-  HIP_TRY(launch_rmse<T>((const T*)r.res2, r.N, (double)r.N * r.m1 * r.m2, b.rpart, b.rblk, pl.trace, 1,
+  HIP_TRY(launch_rmse<T>((const T*)r.res2, r.N, (double)r.N * r.m1 * r.m2, b.rpart, b.rblk, pl.done + q, pl.trace, 1,
                          q * (K + 1), pl.iter + q, L.st));
   return L.end();
-}
-
-int begin_call(hipStream_t st, Ctx* ctx, const Plan& pl, int nprob) {
-  (void)ctx;
-  HIP_TRY(launch_fill_int(pl.status, 4, 0, st));
-  HIP_TRY(launch_fill_int((int*)pl.counters, 2 * kNumCounters, 0, st));
-  HIP_TRY(launch_fill_int(pl.iter, nprob > 0 ? nprob : 1, 0, st));
-  return SDL_OK;
 }
 
 template <typename T>
@@ -627,14 +644,13 @@ int sparse_code_impl(const sdl_problem* p, int nprob, const Opt& o, hipStream_t 
   pl.ybf16 = o.prec == SDL_BF16 || o.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, o.timing != 0 && o.stats != nullptr, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, nprob));
+  SDL_TRY(start_call<T>(p, nprob, pl, true, L));
   if (o.check_finite) {
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
   for (int q = 0; q < nprob; ++q) {
     if (p[q].N == 0) continue;
-    SDL_TRY(run_prep<T>(p[q], pl.pb[q], L));
     SDL_TRY(run_omp<T>(p[q], pl.pb[q], o, pl, 0, L));
   }
   return finish_call(st, ctx, pl, o, marks, false);
@@ -691,14 +707,13 @@ int sparse_code_noalloc_impl(const sdl_problem* p, int nprob, const Opt& o, hipS
   pl.ybf16 = o.prec == SDL_BF16 || o.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, false, nullptr, &marks};
-  SDL_TRY(begin_call(st, nullptr, pl, nprob));
+  SDL_TRY(start_call<T>(p, nprob, pl, true, L));
   if (o.check_finite) {
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, nullptr, pl, o, marks, true));
   }
   for (int q = 0; q < nprob; ++q) {
     if (p[q].N == 0) continue;
-    SDL_TRY(run_prep<T>(p[q], pl.pb[q], L));
     SDL_TRY(run_omp<T>(p[q], pl.pb[q], o, pl, 0, L));
   }
   return finish_call(st, nullptr, pl, o, marks, false);
@@ -716,13 +731,12 @@ int tmod_update_impl(sdl_problem* p, int nprob, uint32_t sides, const Opt& o, hi
   pl.ybf16 = o.prec == SDL_BF16 || o.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, o.timing != 0 && o.stats != nullptr, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, nprob));
+  SDL_TRY(start_call<T>(p, nprob, pl, false, L));
   if (o.check_finite) {
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
   for (int q = 0; q < nprob; ++q) {
-    SDL_TRY(run_prep<T>(p[q], pl.pb[q], L));
     if (sides & 1u) SDL_TRY(run_update<T>(1, p[q], pl.pb[q], pl, o, true, L));
     if (sides & 2u) SDL_TRY(run_update<T>(2, p[q], pl.pb[q], pl, o, true, L));
   }
@@ -743,7 +757,7 @@ int sparse_code_sums_impl(const sdl_problem* p, int side, double* sums, const Op
   pl.ybf16 = o.prec == SDL_BF16 || o.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, o.timing != 0 && o.stats != nullptr, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, 1));
+  SDL_TRY(start_call<T>(p, 1, pl, true, L));
   if (o.check_finite) {
     SDL_TRY(run_check_finite<T>(p, 1, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
@@ -756,7 +770,6 @@ int sparse_code_sums_impl(const sdl_problem* p, int side, double* sums, const Op
     HIP_TRY(launch_fill_double(sums, nent + 1, 0.0, st));
     return finish_call(st, ctx, pl, o, marks, false);
   }
-  SDL_TRY(run_prep<T>(r, b, L));
   hipError_t e;
   const double* src = nullptr;
   if (o.prec != SDL_MIXED_BF16 && use_fast<T>(r, o)) {
@@ -776,7 +789,7 @@ int sparse_code_sums_impl(const sdl_problem* p, int side, double* sums, const Op
     const int nrow = launch_reduce_stage1(b.part, nblk, nent, b.stage, &src, st, &e);
     HIP_TRY(e);
     HIP_TRY(launch_reduce_final(src, nrow, nent, nent, sums, st));
-    HIP_TRY(launch_sum_res2<T>((const T*)r.res2, r.N, b.rpart, b.rblk, sums + nent, st));
+    HIP_TRY(launch_sum_res2<T>((const T*)r.res2, r.N, b.rpart, b.rblk, pl.done, sums + nent, st));
     SDL_TRY(L.end());
   }
   return finish_call(st, ctx, pl, o, marks, false);
@@ -934,12 +947,11 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
   std::vector<std::pair<int, int>> marks;
   const bool timing = o.timing != 0 && o.stats != nullptr;
   Launcher L{st, timing, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, nprob));
+  SDL_TRY(start_call<T>(p, nprob, pl, false, L));
   if (o.check_finite) {
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
-  for (int q = 0; q < nprob; ++q) SDL_TRY(run_prep<T>(p[q], pl.pb[q], L));
   const bool graph = o.use_graph && !timing && K > 1;
   if (graph) {
     if (!ctx->side) {
@@ -1036,16 +1048,14 @@ int time_median(hipStream_t st, int reps, double* out, F f) {
 struct TPlan {
   Plan pl;  // status, counters, iteration counter, RMSE trace
   void* Dc[kTensorMaxModes];
-  double* G64[kTensorMaxModes];
   void* Gc[kTensorMaxModes];
   double *part, *stage, *sums, *w, *rpart;
   int rows, rblk, nent;
   // Problems coded by a two-mode kernel: modes 0 .. split-1 and split .. form one Kronecker factor
-  // each (mk x nk; FP64 master, compute-type copy and Grams; a factor of one mode is that mode's own
+  // each (mk x nk; compute-type copy and Gram; a factor of one mode is that mode's own
   // buffers).  split = 0: the n-mode kernel.
   int split;
   int mk[2], nk[2];
-  double *Dk64[2], *Gk64[2];
   void *Dkc[2], *Gkc[2];
   size_t bytes;
 };
@@ -1087,11 +1097,11 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
   tp->pl.status = b.take<int>(4);
   tp->pl.counters = b.take<unsigned long long>(kNumCounters);
   tp->pl.iter = b.take<int>(1);
+  tp->pl.done = b.take<int>(1);
   tp->pl.trace = b.take<double>((size_t)K + 1);
   int nmax = 1, nent = 1;
   for (int d = 0; d < p->nmodes; ++d) {
     tp->Dc[d] = b.take<char>(elem * p->m[d] * p->n[d]);
-    tp->G64[d] = b.take<double>((size_t)p->n[d] * p->n[d]);
     tp->Gc[d] = b.take<char>(elem * p->n[d] * p->n[d]);
     nmax = p->n[d] > nmax ? p->n[d] : nmax;
     const int e = p->n[d] * p->n[d] + p->m[d] * p->n[d];
@@ -1102,7 +1112,6 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
     const int q0 = f == 0 ? 0 : tp->split, q1 = f == 0 ? tp->split : p->nmodes;
     tp->mk[f] = (int)tensor_elems(p->m + q0, q1 - q0);
     tp->nk[f] = (int)tensor_elems(p->n + q0, q1 - q0);
-    tp->Dk64[f] = tp->Gk64[f] = nullptr;
     tp->Dkc[f] = tp->Gkc[f] = nullptr;
     if (tp->split == 0) continue;
     if (q1 - q0 == 1) {
@@ -1110,8 +1119,6 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
       tp->Gkc[f] = tp->Gc[q0];
       continue;
     }
-    tp->Dk64[f] = b.take<double>((size_t)tp->mk[f] * tp->nk[f]);
-    tp->Gk64[f] = b.take<double>((size_t)tp->nk[f] * tp->nk[f]);
     tp->Dkc[f] = b.take<char>(elem * tp->mk[f] * tp->nk[f]);
     tp->Gkc[f] = b.take<char>(elem * tp->nk[f] * tp->nk[f]);
   }
@@ -1192,10 +1199,29 @@ TensorArgs<T> tensor_args(const sdl_tensor_problem* p, const TPlan& tp, const Op
   return a;
 }
 
+// The dictionaries' compute-type copies and Grams, modes q0 .. q1-1 as one Kronecker factor
 template <typename T>
-int tensor_prep(const sdl_tensor_problem* p, const TPlan& tp, hipStream_t st) {
-  for (int d = 0; d < p->nmodes; ++d)
-    HIP_TRY(launch_dict_prep<T>(p->D[d], p->m[d], p->n[d], (T*)tp.Dc[d], tp.G64[d], (T*)tp.Gc[d], st));
+PrepJob<T> tensor_prep_job(const sdl_tensor_problem* p, int q0, int q1, void* Dc, void* Gc) {
+  PrepJob<T> j{};
+  j.nfac = q1 - q0;
+  for (int d = q0; d < q1; ++d) {
+    j.m[d - q0] = p->m[d];
+    j.n[d - q0] = p->n[d];
+    j.F[d - q0] = p->D[d];
+  }
+  j.Dc = (T*)Dc;
+  j.Gc = (T*)Gc;
+  return j;
+}
+
+// The start of a call, one launch: status words and counters zeroed, every mode's dictionary prepared
+template <typename T>
+int tensor_start(const sdl_tensor_problem* p, const TPlan& tp, hipStream_t st) {
+  PrepJob<T> jobs[kTensorMaxModes];
+  for (int d = 0; d < p->nmodes; ++d) jobs[d] = tensor_prep_job<T>(p, d, d + 1, tp.Dc[d], tp.Gc[d]);
+  int* const zero[] = {tp.pl.status, (int*)tp.pl.counters, tp.pl.iter, tp.pl.done};
+  const int nzero[] = {4, 2 * kNumCounters, 1, 1};
+  HIP_TRY(launch_call_prep<T>(jobs, p->nmodes, zero, nzero, 4, st));
   return SDL_OK;
 }
 
@@ -1212,7 +1238,7 @@ int tensor_update_mode(const sdl_tensor_problem* p, const TPlan& tp, const Opt& 
   const int nrow = launch_reduce_stage1(tp.part, tp.rows, nent, tp.stage, &src, st, &e);
   HIP_TRY(e);
   const RmseOut none{nullptr, nullptr, 0, 0, 0.0};
-  HIP_TRY(launch_tmod_solve<T>(src, nrow, nent, tp.sums, mr, na, p->D[d], (T*)tp.Dc[d], tp.G64[d], (T*)tp.Gc[d],
+  HIP_TRY(launch_tmod_solve<T>(src, nrow, nent, tp.sums, mr, na, p->D[d], (T*)tp.Dc[d], (T*)tp.Gc[d],
                                tp.w, tp.pl.status, tp.pl.counters, none, st));
   if (rescale) HIP_TRY(launch_tensor_rescale<T>(a, d, tp.w, st));
   return SDL_OK;
@@ -1227,18 +1253,13 @@ int tensor_code(const sdl_tensor_problem* p, const TPlan& tp, const Opt& o, hipS
     HIP_TRY(launch_tensor_omp<T>(tensor_args<T>(p, tp, o), st));
     return SDL_OK;
   }
-  TensorArgs<double> dd{};
-  dd.nmodes = p->nmodes;
-  for (int d = 0; d < kTensorMaxModes; ++d) {
-    dd.m[d] = d < p->nmodes ? p->m[d] : 1;
-    dd.n[d] = d < p->nmodes ? p->n[d] : 1;
-    dd.D[d] = d < p->nmodes ? p->D[d] : nullptr;
-  }
+  PrepJob<T> jobs[2];
+  int nj = 0;
   for (int f = 0; f < 2; ++f) {
-    if (!tp.Dk64[f]) continue;
-    HIP_TRY(launch_kron(dd, f == 0 ? 0 : tp.split, f == 0 ? tp.split : p->nmodes, tp.Dk64[f], st));
-    HIP_TRY(launch_dict_prep<T>(tp.Dk64[f], tp.mk[f], tp.nk[f], (T*)tp.Dkc[f], tp.Gk64[f], (T*)tp.Gkc[f], st));
+    const int q0 = f == 0 ? 0 : tp.split, q1 = f == 0 ? tp.split : p->nmodes;
+    if (q1 - q0 > 1) jobs[nj++] = tensor_prep_job<T>(p, q0, q1, tp.Dkc[f], tp.Gkc[f]);
   }
+  HIP_TRY(launch_call_prep<T>(jobs, nj, nullptr, nullptr, 0, st));
   OmpArgs<T> a{};
   a.m1 = tp.mk[0]; a.m2 = tp.mk[1]; a.n1 = tp.nk[0]; a.n2 = tp.nk[1]; a.s = p->s; a.N = p->N;
   a.Y = (const T*)p->Y;
@@ -1282,12 +1303,11 @@ int tensor_impl(const sdl_tensor_problem* p, int call, int mode, int K, double* 
   SDL_TRY_WS(ensure_ws(ctx, tp.bytes, st));
   tensor_ws_layout(p, sizeof(T), K, ctx->ws, &tp);
   std::vector<std::pair<int, int>> marks;
-  SDL_TRY(begin_call(st, ctx, tp.pl, 1));
+  SDL_TRY(tensor_start<T>(p, tp, st));
   if (o.check_finite) {
     SDL_TRY(tensor_check_finite<T>(p, tp, st));
     SDL_TRY(finish_call(st, ctx, tp.pl, o, marks, true));
   }
-  SDL_TRY(tensor_prep<T>(p, tp, st));
   const double denom = (double)p->N * (double)tensor_elems(p->m, p->nmodes);
   if (call == 0) {
     SDL_TRY(tensor_code<T>(p, tp, o, st));
@@ -1302,13 +1322,15 @@ int tensor_impl(const sdl_tensor_problem* p, int call, int mode, int K, double* 
     for (int d = 0; d < p->nmodes; ++d) {
       SDL_TRY(tensor_code<T>(p, tp, o, st));
       if (d == 0 && p->res2)
-        HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.trace, 1, 0, tp.pl.iter, st));
+        HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.done, tp.pl.trace, 1,
+                               0, tp.pl.iter, st));
       SDL_TRY(tensor_update_mode<T>(p, tp, o, d, false, st));
     }
   if (p->N > 0) {
     SDL_TRY(tensor_code<T>(p, tp, o, st));
     if (p->res2)
-      HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.trace, 1, 0, tp.pl.iter, st));
+      HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.done, tp.pl.trace, 1,
+                               0, tp.pl.iter, st));
   }
   int rc = finish_call(st, ctx, tp.pl, o, marks, true);
   if (trace && (rc == SDL_OK || rc == SDL_E_SINGULAR)) {
@@ -1330,9 +1352,9 @@ int patches_to_image_impl(const sdl_problem* p, int H, int W, const Opt& o, void
   void* wsb = nullptr;
   SDL_TRY(acquire_ws(ctx, o, pl.bytes, st, &wsb));
   layout(p, 1, sizeof(T), 0, wsb, &pl);
-  std::vector<std::pair<int, int>> marks;
-  Launcher L{st, false, ctx, &marks};
-  SDL_TRY(run_prep<T>(p[0], pl.pb[0], L));
+  const PrepJob<T> jobs[] = {prep_job<T>(p->D1, p->m1, p->n1, pl.pb[0].Dc1, pl.pb[0].G1c),
+                             prep_job<T>(p->D2, p->m2, p->n2, pl.pb[0].Dc2, pl.pb[0].G2c)};
+  HIP_TRY(launch_call_prep<T>(jobs, 2, nullptr, nullptr, 0, st));
   HIP_TRY(launch_patches_to_image<T>(p->supp, (const T*)p->coef, (const T*)pl.pb[0].Dc1, (const T*)pl.pb[0].Dc2, H, W,
                                      p->m1, p->m2, p->n1, p->n2, p->s, (T*)image, st));
   return SDL_OK;
@@ -1523,10 +1545,9 @@ int sdl_autotune(const sdl_problem* p, int32_t nprob, int32_t reps, const sdl_op
   pl.ybf16 = opt.prec == SDL_BF16 || opt.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, false, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, nprob));
+  SDL_TRY(start_call<float>(p, nprob, pl, true, L));
   for (int q = 0; q < nprob; ++q) {
     if (p[q].N == 0 || !omp_fast_supported<float>(p[q].m1, p[q].m2, p[q].n1, p[q].n2, p[q].s)) continue;
-    SDL_TRY(run_prep<float>(p[q], pl.pb[q], L));
     OmpArgs<float> a = omp_args<float>(p[q], pl.pb[q], opt, pl);
     // timed as the learning loop runs it: with the D1-update sums epilogue
     a.sums_side = 1;
@@ -1647,10 +1668,9 @@ int sdl_learned_sparse_code(sdl_proposer* P, const sdl_problem* p, int32_t nprob
   pl.ybf16 = opt.prec == SDL_BF16 || opt.prec == SDL_MIXED_BF16;
   std::vector<std::pair<int, int>> marks;
   Launcher L{st, false, ctx, &marks};
-  SDL_TRY(begin_call(st, ctx, pl, nprob));
+  SDL_TRY(start_call<float>(p, nprob, pl, true, L));
   for (int q = 0; q < nprob; ++q) {
     if (p[q].N == 0) continue;
-    SDL_TRY(run_prep<float>(p[q], pl.pb[q], L));
     // accepted and fallback counts accumulate in the call's device counters (read by finish_call)
     SDL_TRY(learned_code(P, p[q], opt.tau, accept, omp_args<float>(p[q], pl.pb[q], opt, pl), st, nullptr));
   }

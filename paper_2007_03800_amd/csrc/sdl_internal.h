@@ -111,7 +111,7 @@ bool ortho_supported(int m1, int m2, int n1, int n2, int s);
 template <typename T>
 hipError_t launch_ortho_code(const OmpArgs<T>& a, hipStream_t st);
 template <typename T>
-hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, double* G64, T* Gc,
+hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, T* Gc,
                              int* status, unsigned long long* counters, hipStream_t st);
 hipError_t ortho_init_device();
 // SDL_MIXED_BF16 sparse coding (omp_mixed.hip): correlations D1^T R D2 on the BF16 matrix
@@ -179,9 +179,10 @@ int launch_reduce_stage1(const double* part, int P, int ld, double* stage, const
 int reduce_stage_rows(int P);
 // The last stage alone: out[e] = row-order sum of the nrow rows at src (stride ld), e < n.
 hipError_t launch_reduce_final(const double* src, int nrow, int ld, int n, double* out, hipStream_t st);
-// *out = sum of res2[0 .. N-1] in a fixed order (nblk = rmse_num_blocks(N) partials in part).
+// *out = sum of res2[0 .. N-1] in a fixed order (nblk = rmse_num_blocks(N) partials in part;
+// *done: zero, left zero).
 template <typename T>
-hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, double* out, hipStream_t st);
+hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, int* done, double* out, hipStream_t st);
 hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st);
 // Optional RMSE output of the solve kernel: trace[*counter + offset] = sqrt(sums[idx] / denom), then ++*counter.
 struct RmseOut {
@@ -197,26 +198,36 @@ struct RmseOut {
 // device).
 template <typename T>
 hipError_t launch_tmod_solve(const double* src, int nrow, int ld, double* sums, int mr, int na, double* D, T* Dc,
-                             double* G64, T* Gc, double* w, int* status, unsigned long long* counters,
+                             T* Gc, double* w, int* status, unsigned long long* counters,
                              const RmseOut& r, hipStream_t st);
 hipError_t tmod_solve_init_device();
 // Measurement aids (probe.hip): best copy rate (read + write, GB/s) and arithmetic peaks
 // (kind 0 FP32 FMA, 1 FP32 MFMA 16x16x4, 2 FP32 MFMA 4x4x1, 3 FP64 FMA; TFLOP/s).
 hipError_t probe_hbm_copy(void* dst, const void* src, size_t bytes, int reps, hipStream_t st, double* gbs);
 hipError_t probe_peak(int kind, float* sink, int reps, hipStream_t st, double* tflops);
+// One dictionary to prepare: D = F[nfac-1] (x) ... (x) F[0] (F[d] m[d] x n[d], FP64), its compute-type
+// copy Dc and Gram matrix Gc.  (prod m + 1) prod n is at most (SDL_MAX_M + 1) SDL_MAX_N.
 template <typename T>
-hipError_t launch_dict_prep(const double* D, int mr, int na, T* Dc, double* G64, T* Gc, hipStream_t st);
+struct PrepJob {
+  int nfac, m[4], n[4];
+  const double* F[4];
+  T *Dc, *Gc;
+};
+constexpr int kMaxPrepJobs = 8;  // dictionaries per launch
+constexpr int kMaxPrepZero = 4;  // ranges of ints set to zero
+// The n dictionaries, and nz ranges of nzero[z] ints at zero[z] set to zero.
+template <typename T>
+hipError_t launch_call_prep(const PrepJob<T>* jobs, int n, int* const* zero, const int* nzero, int nz, hipStream_t st);
 template <typename T>
 hipError_t launch_rescale(int side, int n1, int s, int64_t N, const int32_t* supp, T* coef, const double* w,
                           hipStream_t st);
 int rmse_num_blocks(int64_t N);
 template <typename T>
-hipError_t launch_rmse(const T* res2, int64_t N, double denom, double* part, int nblk, double* trace,
+hipError_t launch_rmse(const T* res2, int64_t N, double denom, double* part, int nblk, int* done, double* trace,
                        int stride, int offset, int* counter, hipStream_t st);
 template <typename T>
 hipError_t launch_check_finite(const T* x, int64_t n, int* status, hipStream_t st);
 hipError_t launch_check_finite_bf16(const uint16_t* x, int64_t n, int* status, hipStream_t st);
-hipError_t launch_fill_int(int* p, int n, int v, hipStream_t st);
 // n-dimensional signals (Remark 3, tensor.hip): m[d] x n[d] dictionaries per mode, atom
 // a = i_0 + n_0 (i_1 + n_1 (...)); entries of m and n beyond nmodes are 1.
 constexpr int kTensorMaxModes = 4;
@@ -254,8 +265,6 @@ hipError_t launch_ortho_mfma(const OmpArgs<float>& a, hipStream_t st);
 // collapsed into one Kronecker factor (FP32 shapes compiled in omp_wave.hip)
 bool omp_wave_collapsed_supported(int m1, int m2, int n1, int n2, int s);
 hipError_t launch_omp_wave_collapsed(const OmpArgs<float>& a, hipStream_t st);
-// Dk = D_q1-1 (x) ... (x) D_q0 (modes q0 .. q1-1): prod m[d] x prod n[d], FP64
-hipError_t launch_kron(const TensorArgs<double>& d, int q0, int q1, double* Dk, hipStream_t st);
 // Denoising driver (denoise.hip): overlapping patches of a row-major image as column-major
 // signals, and the image rebuilt as the average of the coded patches covering each pixel.
 template <typename T>

@@ -417,21 +417,6 @@ __global__ void __launch_bounds__(kWave) tensor_sums_kernel(TensorArgs<T> a, int
   for (int e = lane; e < nent; e += kWave) part[(size_t)blockIdx.x * nent + e] = acc[e];
 }
 
-// Dk[p', j'] = prod_{q0 <= d < q1} D_d[p_d, i_d] with p' = p_q0 + m_q0 (...), j' = i_q0 + n_q0 (...)
-__global__ void kron_kernel(TensorArgs<double> d, int q0, int q1, double* Dk, int mk, int nk) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < mk * nk; e += gridDim.x * blockDim.x) {
-    int p = e % mk, j = e / mk;
-    double v = 1.0;
-    for (int q = q0; q < q1; ++q) {
-      const int pq = p % d.m[q], iq = j % d.n[q];
-      p /= d.m[q];
-      j /= d.n[q];
-      v *= d.D[q][pq + d.m[q] * iq];
-    }
-    Dk[e] = v;
-  }
-}
-
 // Mode-d sums on the matrix cores, for n_d <= 16 and m_d <= 16: the signals' W_k(d) and
 // Y_k(d) concatenated along their columns form the contraction A = Wcat Wcat^T, B = Ycat Wcat^T,
 // run four columns at a time with the 16x16x4 MFMA (lane l supplies row l % 16 of column
@@ -685,16 +670,6 @@ hipError_t launch_tensor_rescale(const TensorArgs<T>& a, int mode, const double*
   for (int d = 0; d < mode; ++d) div *= a.n[d];
   hipLaunchKernelGGL(tensor_rescale_kernel<T>, dim3((unsigned)((n_el + 255) / 256)), dim3(256), 0, st, n_el, div,
                      a.n[mode], a.supp, a.coef, w);
-  return hipGetLastError();
-}
-
-hipError_t launch_kron(const TensorArgs<double>& d, int q0, int q1, double* Dk, hipStream_t st) {
-  int mk = 1, nk = 1;
-  for (int q = q0; q < q1; ++q) {
-    mk *= d.m[q];
-    nk *= d.n[q];
-  }
-  hipLaunchKernelGGL(kron_kernel, dim3((unsigned)((mk * nk + 255) / 256)), dim3(256), 0, st, d, q0, q1, Dk, mk, nk);
   return hipGetLastError();
 }
 

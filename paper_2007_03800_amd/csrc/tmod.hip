@@ -66,7 +66,7 @@ constexpr int kDirectRows = 2 * kChunk;  // up to this many partial rows the sol
 template <typename T>
 __global__ void __launch_bounds__(kSolveThreads)
     tmod_solve_kernel(const double* __restrict__ src, int nrow, int ld, double* sums, int mr, int na, double* D,
-                      T* Dc, double* G64, T* Gc, double* w, int* status, unsigned long long* counters, RmseOut r,
+                      T* Dc, T* Gc, double* w, int* status, unsigned long long* counters, RmseOut r,
                       int sums_in_lds) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int tid = threadIdx.x;
@@ -94,29 +94,70 @@ __global__ void __launch_bounds__(kSolveThreads)
     r.trace[(size_t)it + r.offset] = r.denom > 0 ? sqrt(rs[r.idx] / r.denom) : 0.0;
     *r.counter = it + 1;
   }
-  solve_update_block<T>(rs, mr, na, D, Dc, G64, Gc, w, status, counters,
+  solve_update_block<T>(rs, mr, na, D, Dc, Gc, w, status, counters,
                         smem_raw + (sums_in_lds ? solve_sums_lds_bytes(ld) : 0), tid, blockDim.x);
 }
 
-// The dictionary's compute-type copy and its Gram matrix (FP64 and compute type), with D
-// staged in LDS at an odd column stride first: the Gram entries then read LDS without bank
-// conflicts instead of global memory.
+// What a call needs before its first sparse coding, in one launch: every dictionary's compute-type
+// copy and Gram matrix, and the call's status words and counters set to zero (five launches of about
+// 1.5 us each and their gaps before, a third of a 64-signal call).  A dictionary may be given as the
+// Kronecker product of several modes' (n-dimensional problems).  Workgroups of one dictionary each
+// stage it in LDS at an odd column stride, so that the Gram entries read LDS without bank conflicts,
+// and share the Gram matrix (512 entries each, at most kPrepParts of them).
+constexpr int kPrepParts = 8;
+
 template <typename T>
-__global__ void dict_prep_kernel(const double* D, int mr, int na, T* Dc, double* G64, T* Gc) {
+struct PrepBatch {
+  PrepJob<T> j[kMaxPrepJobs];
+  int first[kMaxPrepJobs + 1];
+  int* zero[kMaxPrepZero];
+  int nzero[kMaxPrepZero];
+};
+
+template <typename T>
+__global__ void __launch_bounds__(256) call_prep_kernel(PrepBatch<T> b) {
   __shared__ double sD[(SDL_MAX_M + 1) * SDL_MAX_N];
-  const int ldd = mr + 1, tid = threadIdx.x, nt = blockDim.x;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  if ((int)blockIdx.x >= b.first[kMaxPrepJobs]) {
+#pragma unroll
+    for (int z = 0; z < kMaxPrepZero; ++z)
+      for (int i = tid; i < b.nzero[z]; i += nt) b.zero[z][i] = 0;
+    return;
+  }
+  int which = 0;
+  while (which < kMaxPrepJobs - 1 && (int)blockIdx.x >= b.first[which + 1]) ++which;
+  const PrepJob<T>& g = b.j[which];
+  const int part = (int)blockIdx.x - b.first[which], nparts = b.first[which + 1] - b.first[which];
+  int mr = 1, na = 1;
+  for (int q = 0; q < g.nfac; ++q) {
+    mr *= g.m[q];
+    na *= g.n[q];
+  }
+  const int ldd = mr + 1;
   for (int e = tid; e < mr * na; e += nt) {
-    const double v = D[e];
-    sD[e % mr + ldd * (e / mr)] = v;
-    Dc[e] = (T)v;
+    const int r = e % mr, c = e / mr;
+    double v;
+    if (g.nfac == 1) {
+      v = g.F[0][e];
+    } else {
+      v = 1.0;
+      int p = r, j = c;
+      for (int q = 0; q < g.nfac; ++q) {
+        const int pq = p % g.m[q], iq = j % g.n[q];
+        p /= g.m[q];
+        j /= g.n[q];
+        v *= g.F[q][pq + g.m[q] * iq];
+      }
+    }
+    sD[r + ldd * c] = v;
+    if (part == 0) g.Dc[e] = (T)v;
   }
   __syncthreads();
-  for (int e = tid; e < na * na; e += nt) {
+  for (int e = tid + nt * part; e < na * na; e += nt * nparts) {
     const int i = e % na, j = e / na;
     double v = 0.0;
     for (int p = 0; p < mr; ++p) v += sD[p + ldd * i] * sD[p + ldd * j];
-    G64[e] = v;
-    Gc[e] = (T)v;
+    g.Gc[e] = (T)v;
   }
 }
 
@@ -133,41 +174,53 @@ __global__ void rescale_kernel(int side, int n1, int s, int64_t N, const int32_t
 
 constexpr int kRmseThreads = 256;
 
+// Sum of N squared residuals in a fixed order: each workgroup writes its slice's sum, the last one to
+// finish (a counter that it sets back to zero) adds the slices' sums and writes the total, or the
+// RMSE with the trace position moved on.  The slices' sums pass between workgroups by device-scope
+// atomics.  (A second launch whose single lane walked the slices took 4-15 us.)
 template <typename T>
-__global__ void __launch_bounds__(kRmseThreads) rmse_partial_kernel(const T* res2, int64_t N, int nblk, double* part) {
+__global__ void __launch_bounds__(kRmseThreads)
+    res2_sum_kernel(const T* res2, int64_t N, double* part, int* done, double* out, double denom, double* trace, int stride,
+                    int offset, int* counter) {
   __shared__ double red[kRmseThreads];
+  __shared__ int last;
+  const int nblk = gridDim.x, tid = threadIdx.x;
   const int64_t k0 = (N * blockIdx.x) / nblk, k1 = (N * (blockIdx.x + 1)) / nblk;
-  double v = 0.0;
-  for (int64_t k = k0 + threadIdx.x; k < k1; k += kRmseThreads) v += (double)res2[k];
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = kRmseThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  auto block_sum = [&](double v) {
+    red[tid] = v;
     __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ void sum_final_kernel(const double* part, int nblk, double* out) {
-  if (threadIdx.x != 0) return;
+    for (int o = kRmseThreads / 2; o > 0; o >>= 1) {
+      if (tid < o) red[tid] += red[tid + o];
+      __syncthreads();
+    }
+  };
   double v = 0.0;
-  for (int b = 0; b < nblk; ++b) v += part[b];
-  *out = v;
+#pragma unroll 4
+  for (int64_t k = k0 + tid; k < k1; k += kRmseThreads) v += (double)res2[k];
+  block_sum(v);
+  if (tid == 0) {
+    __hip_atomic_store(&part[blockIdx.x], red[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  v = 0.0;
+  for (int b = tid; b < nblk; b += kRmseThreads) v += __hip_atomic_load(&part[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  block_sum(v);
+  if (tid == 0) {
+    *done = 0;
+    if (out) *out = red[0];
+    if (trace) {
+      const int it = *counter;
+      trace[(size_t)it * stride + offset] = denom > 0 ? sqrt(red[0] / denom) : 0.0;
+      *counter = it + 1;
+    }
+  }
 }
 
 __global__ void fill_double_kernel(double* p, int n, double v) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e < n) p[e] = v;
-}
-
-__global__ void rmse_final_kernel(const double* part, int nblk, double denom, double* trace, int stride, int offset,
-                                  int* counter) {
-  if (threadIdx.x != 0) return;
-  double v = 0.0;
-  for (int b = 0; b < nblk; ++b) v += part[b];
-  const int it = *counter;
-  trace[(size_t)it * stride + offset] = denom > 0 ? sqrt(v / denom) : 0.0;
-  *counter = it + 1;
 }
 
 template <typename T>
@@ -187,11 +240,6 @@ __global__ void check_finite_bf16_kernel(const uint16_t* x, int64_t n, int* stat
       return;
     }
   }
-}
-
-__global__ void fill_int_kernel(int* p, int n, int v) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) p[e] = v;
 }
 
 }  // namespace
@@ -225,13 +273,13 @@ hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_tmod_solve(const double* src, int nrow, int ld, double* sums, int mr, int na, double* D, T* Dc,
-                             double* G64, T* Gc, double* w, int* status, unsigned long long* counters,
+                             T* Gc, double* w, int* status, unsigned long long* counters,
                              const RmseOut& r, hipStream_t st) {
   // the reduced sums stay in LDS too when they fit beside the solve's workspace
   const size_t base = solve_lds_bytes(na, mr), with = base + solve_sums_lds_bytes(ld);
   const int in_lds = with <= solve_lds_bytes(SDL_MAX_N, SDL_MAX_M) ? 1 : 0;
   hipLaunchKernelGGL(tmod_solve_kernel<T>, dim3(1), dim3(kSolveThreads), in_lds ? with : base, st, src, nrow, ld,
-                     sums, mr, na, D, Dc, G64, Gc, w, status, counters, r, in_lds);
+                     sums, mr, na, D, Dc, Gc, w, status, counters, r, in_lds);
   return hipGetLastError();
 }
 
@@ -245,9 +293,38 @@ hipError_t tmod_solve_init_device() {
 }
 
 template <typename T>
-hipError_t launch_dict_prep(const double* D, int mr, int na, T* Dc, double* G64, T* Gc, hipStream_t st) {
-  hipLaunchKernelGGL(dict_prep_kernel<T>, dim3(1), dim3(256), 0, st, D, mr, na, Dc, G64, Gc);
-  return hipGetLastError();
+hipError_t launch_call_prep(const PrepJob<T>* jobs, int n, int* const* zero, const int* nzero, int nz, hipStream_t st) {
+  if (nz > kMaxPrepZero) return hipErrorInvalidValue;
+  for (int j0 = 0; j0 < n || j0 == 0; j0 += kMaxPrepJobs) {
+    PrepBatch<T> b{};
+    int blocks = 0;
+    for (int q = 0; q < kMaxPrepJobs; ++q) {
+      b.first[q] = blocks;
+      if (j0 + q >= n) continue;
+      const PrepJob<T>& g = b.j[q] = jobs[j0 + q];
+      int mr = 1, na = 1;
+      for (int d = 0; d < g.nfac; ++d) {
+        mr *= g.m[d];
+        na *= g.n[d];
+      }
+      if ((mr + 1) * na > (SDL_MAX_M + 1) * SDL_MAX_N) return hipErrorInvalidValue;
+      const int parts = (na * na + 511) / 512;
+      blocks += parts < kPrepParts ? parts : kPrepParts;
+    }
+    b.first[kMaxPrepJobs] = blocks;
+    if (j0 == 0 && nz > 0) {
+      for (int z = 0; z < nz; ++z) {
+        b.zero[z] = zero[z];
+        b.nzero[z] = nzero[z];
+      }
+      ++blocks;
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(call_prep_kernel<T>, dim3(blocks), dim3(256), 0, st, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename T>
@@ -268,17 +345,17 @@ int rmse_num_blocks(int64_t N) {
 }
 
 template <typename T>
-hipError_t launch_rmse(const T* res2, int64_t N, double denom, double* part, int nblk, double* trace, int stride,
-                       int offset, int* counter, hipStream_t st) {
-  hipLaunchKernelGGL(rmse_partial_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, nblk, part);
-  hipLaunchKernelGGL(rmse_final_kernel, dim3(1), dim3(64), 0, st, part, nblk, denom, trace, stride, offset, counter);
+hipError_t launch_rmse(const T* res2, int64_t N, double denom, double* part, int nblk, int* done, double* trace,
+                       int stride, int offset, int* counter, hipStream_t st) {
+  hipLaunchKernelGGL(res2_sum_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, part, done, nullptr, denom, trace,
+                     stride, offset, counter);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(rmse_partial_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, nblk, part);
-  hipLaunchKernelGGL(sum_final_kernel, dim3(1), dim3(64), 0, st, part, nblk, out);
+hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, int* done, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(res2_sum_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, part, done, out, 0.0, nullptr, 0, 0,
+                     nullptr);
   return hipGetLastError();
 }
 
@@ -299,21 +376,16 @@ hipError_t launch_check_finite_bf16(const uint16_t* x, int64_t n, int* status, h
   return hipGetLastError();
 }
 
-hipError_t launch_fill_int(int* p, int n, int v, hipStream_t st) {
-  hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n, v);
-  return hipGetLastError();
-}
-
 #define SDL_INST(T)                                                                                            \
-  template hipError_t launch_tmod_solve<T>(const double*, int, int, double*, int, int, double*, T*, double*, T*, \
+  template hipError_t launch_tmod_solve<T>(const double*, int, int, double*, int, int, double*, T*, T*, \
                                            double*, int*, unsigned long long*, const RmseOut&, hipStream_t);  \
-  template hipError_t launch_dict_prep<T>(const double*, int, int, T*, double*, T*, hipStream_t);             \
+  template hipError_t launch_call_prep<T>(const PrepJob<T>*, int, int* const*, const int*, int, hipStream_t);  \
   template hipError_t launch_rescale<T>(int, int, int, int64_t, const int32_t*, T*, const double*,            \
                                         hipStream_t);                                                         \
-  template hipError_t launch_rmse<T>(const T*, int64_t, double, double*, int, double*, int, int, int*,        \
+  template hipError_t launch_rmse<T>(const T*, int64_t, double, double*, int, int*, double*, int, int, int*,  \
                                      hipStream_t);                                                            \
   template hipError_t launch_check_finite<T>(const T*, int64_t, int*, hipStream_t);                          \
-  template hipError_t launch_sum_res2<T>(const T*, int64_t, double*, int, double*, hipStream_t);
+  template hipError_t launch_sum_res2<T>(const T*, int64_t, double*, int, int*, double*, hipStream_t);
 SDL_INST(float)
 SDL_INST(double)
 #undef SDL_INST

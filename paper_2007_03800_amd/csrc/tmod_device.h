@@ -34,7 +34,7 @@ __host__ __device__ inline size_t solve_sums_lds_bytes(int ld) { return ((size_t
 // column keeps the old atom), and D, its compute-type copy and the Gram matrix D^T D
 // are rewritten.  smem: solve_lds_bytes(na, mr) bytes; nt a multiple of 32.
 template <typename T>
-__device__ void solve_update_block(const double* sums, int mr, int na, double* D, T* Dc, double* G64, T* Gc,
+__device__ void solve_update_block(const double* sums, int mr, int na, double* D, T* Dc, T* Gc,
                                    double* w, int* status, unsigned long long* counters, unsigned char* smem,
                                    int tid, int nt) {
   const int ldm = na + mr + 1;
@@ -117,7 +117,6 @@ __device__ void solve_update_block(const double* sums, int mr, int na, double* D
     const int i = e % na, j = e / na;
     double v = 0.0;
     for (int p = 0; p < mr; ++p) v += Dn[p + ldd * i] * Dn[p + ldd * j];
-    G64[e] = v;
     Gc[e] = (T)v;
   }
 }
