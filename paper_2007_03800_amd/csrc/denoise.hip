@@ -6,9 +6,11 @@
 //
 // Image: row-major, pixel (y, x) at y W + x.  Patch k = r C + c (C = W - m2 + 1) holds pixel
 // (r + i, c + j) at its (i, j), stored column-major like every signal of the library.
-// The rebuild is one tiled pass (rebuild_kernel): each output pixel sums its covering patches'
-// estimates in a fixed order, computed on the fly from codes gathered into LDS; nothing adds
-// into the image atomically and the result is reproducible.
+// The rebuild is one tiled pass: each output pixel sums its covering patches' estimates in a fixed
+// order, formed on chip from the codes (rebuild_rows_kernel walks along rows of patches;
+// rebuild_kernel, for patches of more than 256 pixels, goes pixel by pixel over codes gathered into
+// LDS); nothing adds into the image atomically and the result is reproducible.
+#include "lanes.h"
 #include "sdl_internal.h"
 
 namespace sdl {
@@ -155,6 +157,133 @@ __global__ void __launch_bounds__(kTile* kTile) rebuild_kernel(const int32_t* __
   img[(int64_t)y * W + x] = acc / (T)((r1 - r0 + 1) * (c1 - c0 + 1));
 }
 
+// The rebuild for patches of up to 256 pixels (U = ceil(m1 m2 / 64)): sums along a row of patches in
+// registers, across rows of patches in LDS.  A workgroup owns kRowTile x kColTile pixels; each of its
+// waves takes rows r of covering patches and walks along c.  A lane stands for pixel row i of the
+// patch and image columns x = its phase (mod m2): patch c meets it at column j = x - c of the patch,
+// j goes down by one a patch, and when j = 0 the column has met all its patches of the row: the
+// lane's sum goes to LDS as S[r][i][x] and it starts on column x + m2.  At the end pixel (y, x) is
+// the sum over r of S[r][y - r][x] in increasing r, divided by the number of covering patches; each
+// S adds its estimates in increasing c, then slot order, so the result is reproducible.  The codes of
+// two patches come in one load (32 slots each, four loads in flight), a ballot finds the used slots
+// and each is read from its lane, so a patch costs its used slots only.
+// What bounds it: vector-ALU issue and the latency of the two table reads a slot.  Codes are read
+// ((kRowTile + m1 - 1) / kRowTile)((kColTile + m2 - 1) / kColTile) times (1.75 for 8 x 8), mostly
+// from L2.
+constexpr int kRowTile = 16, kColTile = 32, kRowWaves = 8, kRowPairs = 4;
+
+template <typename T>
+size_t rebuild_rows_lds_bytes(int m1, int m2, int n1, int n2) {
+  return sizeof(T) * ((size_t)m1 * n1 + (size_t)m2 * n2 + (size_t)(kRowTile + m1 - 1) * m1 * (kColTile + 1));
+}
+
+template <typename T, int U>
+__global__ void __launch_bounds__(kWave* kRowWaves)
+    rebuild_rows_kernel(const int32_t* __restrict__ supp, const T* __restrict__ coef, const T* __restrict__ D1,
+                        const T* __restrict__ D2, int H, int W, int m1, int m2, int n1, int n2, int s,
+                        T* __restrict__ img) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int R = H - m1 + 1, C = W - m2 + 1, M = m1 * m2;
+  T* sD1 = reinterpret_cast<T*>(smem_raw);  // m1 x n1
+  T* sD2 = sD1 + m1 * n1;                   // m2 x n2
+  T* S = sD2 + m2 * n2;                     // [r - rb][i][x - x0], rows of kColTile + 1
+  const int tid = threadIdx.x, lane = tid % kWave, wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int y0 = blockIdx.y * kRowTile, x0 = blockIdx.x * kColTile;
+  const int y1 = min(y0 + kRowTile, H), x1 = min(x0 + kColTile, W);
+  const int rb = max(0, y0 - m1 + 1), re = min(R - 1, y1 - 1);
+  const int cb = max(0, x0 - m2 + 1), ce = min(C - 1, x1 - 1);
+  const int np = ce - cb + 1;
+  for (int e = tid; e < m1 * n1; e += blockDim.x) sD1[e] = D1[e];
+  for (int e = tid; e < m2 * n2; e += blockDim.x) sD2[e] = D2[e];
+  __syncthreads();
+  const unsigned inv_n1 = ((1u << 20) + (unsigned)n1 - 1u) / (unsigned)n1;  // a / n1 for a < 4096
+  const int half = lane / 32, sl = lane % 32;  // slot sl of the first or second patch of a pair
+  int i[U], j0[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = lane + kWave * u;
+    i[u] = e % m1;
+    j0[u] = e < M ? e / m1 : -1;  // -1: no pixel
+  }
+  for (int r = rb + wv; r <= re; r += kRowWaves) {
+    T acc[U];
+    int j[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc[u] = 0;
+      j[u] = j0[u];
+    }
+    T* Sr = S + (size_t)(r - rb) * m1 * (kColTile + 1);
+    const int64_t k0 = (int64_t)r * C + cb;
+    auto fetch = [&](int p, int& a, T& cf) {  // the codes of patches p and p + 1 of the row
+      a = -1;
+      cf = 0;
+      if (sl < s && p + half < np) {
+        const int64_t o = (k0 + p + half) * s + sl;
+        a = supp[o];
+        cf = coef[o];
+      }
+    };
+    int na[kRowPairs];
+    T nc[kRowPairs];
+#pragma unroll
+    for (int q = 0; q < kRowPairs; ++q) fetch(2 * q, na[q], nc[q]);
+    for (int p0 = 0; p0 < np; p0 += 2 * kRowPairs) {
+#pragma unroll
+      for (int q = 0; q < kRowPairs; ++q) {
+        const int a = na[q], p = p0 + 2 * q;
+        const T cf = nc[q];
+        fetch(p + 2 * kRowPairs, na[q], nc[q]);
+        const unsigned ja = a >= 0 ? ((unsigned)a * inv_n1) >> 20 : 0u;
+        const int off = m1 * (a - n1 * (int)ja) | (m2 * (int)ja) << 16;
+        const unsigned long long used = __ballot(a >= 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (p + h >= np) break;
+          unsigned m = (unsigned)(used >> (32 * h));
+          while (m) {
+            const int t = __builtin_ctz(m) + 32 * h;
+            m &= m - 1;
+            const int o = __builtin_amdgcn_readlane(off, t);
+            const T x = lane_read(cf, t);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const int jj = j[u] < 0 ? 0 : j[u];
+              acc[u] += x * sD1[i[u] + (o & 0xFFFF)] * sD2[jj + (o >> 16)];
+            }
+          }
+          const int x = cb + p + h;  // the column that has met its last patch of this row
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (j[u] == 0) {
+              if (x >= x0) Sr[i[u] * (kColTile + 1) + x - x0] = acc[u];
+              acc[u] = 0;
+              j[u] = m2;
+            }
+            j[u] -= j0[u] < 0 ? 0 : 1;
+          }
+        }
+      }
+    }
+    // columns past the last patch's first
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int x = ce + 1 + j[u];
+      if (j0[u] >= 0 && x >= x0 && x < x1) Sr[i[u] * (kColTile + 1) + x - x0] = acc[u];
+    }
+  }
+  __syncthreads();
+  const int x = x0 + tid % kColTile;
+  for (int y = y0 + tid / kColTile; y < y1; y += kWave * kRowWaves / kColTile) {
+    if (x >= x1) continue;
+    const int r0 = y - m1 + 1 > 0 ? y - m1 + 1 : 0, r1 = y < R - 1 ? y : R - 1;
+    const int c0 = x - m2 + 1 > 0 ? x - m2 + 1 : 0, c1 = x < C - 1 ? x : C - 1;
+    T v = 0;
+    for (int r = r0; r <= r1; ++r) v += S[((size_t)(r - rb) * m1 + (y - r)) * (kColTile + 1) + x - x0];
+    img[(int64_t)y * W + x] = v / (T)((r1 - r0 + 1) * (c1 - c0 + 1));
+  }
+}
+
 // LDS of rebuild_kernel with a pool of `pool` slots
 template <typename T>
 size_t rebuild_lds_bytes(int m1, int m2, int n1, int n2, int pool) {
@@ -179,6 +308,19 @@ template <typename T>
 hipError_t launch_patches_to_image(const int32_t* supp, const T* coef, const T* D1, const T* D2, int H, int W, int m1,
                                    int m2, int n1, int n2, int s, T* img, hipStream_t st) {
   if ((int64_t)H * W <= 0) return hipSuccess;
+  // patches of up to 256 pixels whose row sums leave room for two workgroups a CU walk along rows of
+  // patches (512 x 512 image, 255,025 patches of 8 x 8: 138 -> 74 us); others go pixel by pixel
+  const size_t rows_lds = rebuild_rows_lds_bytes<T>(m1, m2, n1, n2);
+  if (m1 * m2 <= 256 && rows_lds <= 80 * 1024) {
+    const dim3 g((unsigned)((W + kColTile - 1) / kColTile), (unsigned)((H + kRowTile - 1) / kRowTile));
+    if (m1 * m2 <= kWave)
+      hipLaunchKernelGGL((rebuild_rows_kernel<T, 1>), g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W,
+                         m1, m2, n1, n2, s, img);
+    else
+      hipLaunchKernelGGL((rebuild_rows_kernel<T, 4>), g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W,
+                         m1, m2, n1, n2, s, img);
+    return hipGetLastError();
+  }
   // the pool takes what kRebuildLds leaves, and never more than every slot of every patch
   const int64_t pt = (int64_t)(kTile + m1 - 1) * (kTile + m2 - 1);
   const size_t fixed = rebuild_lds_bytes<T>(m1, m2, n1, n2, 0);
@@ -194,11 +336,16 @@ hipError_t launch_patches_to_image(const int32_t* supp, const T* coef, const T* 
 hipError_t denoise_init_device() {
   // the dictionaries and per-patch tables of the largest shapes (64 x 64 patches, FP64) need
   // up to ~90 KiB (then with no pool)
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&rebuild_kernel<float>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&rebuild_kernel<double>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  const void* fs[] = {reinterpret_cast<const void*>(&rebuild_kernel<float>), reinterpret_cast<const void*>(&rebuild_kernel<double>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<float, 1>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<double, 1>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<float, 4>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<double, 4>)};
+  for (const void* f : fs) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template hipError_t launch_image_to_patches<float>(const float*, int, int, int, int, float*, hipStream_t);

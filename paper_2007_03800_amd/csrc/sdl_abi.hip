@@ -1,9 +1,10 @@
 // Host side of the C ABI declared in include/sdl.h: argument validation,
-// workspace, launch sequencing (Algorithm 1), HIP graph replay and timing.
+// workspace, launch sequencing (Algorithm 1) and timing.
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <string>
@@ -48,25 +49,16 @@ struct Ctx {
   int device = 0;
   void* ws = nullptr;
   size_t ws_bytes = 0;
-  hipStream_t side = nullptr;  // internal stream for graph replay (default priority)
   std::vector<hipEvent_t> ev;  // timing events
-  hipEvent_t join_a = nullptr, join_b = nullptr;
-  // graph branches for the problems of one call (default priority, created on first use)
+  // streams for the problems of one sdl_learn call (default priority, created on first use)
   std::vector<hipStream_t> branch;
   std::vector<hipEvent_t> branch_join;
   hipEvent_t fork = nullptr;
-  // the last instantiated learning graph and what it was captured for (see graph_key)
-  std::vector<unsigned char> gkey;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
 };
 
-// Problems of one sdl_learn call run as parallel branches of the captured graph (at
-// most this many streams; problems beyond it share branches round-robin).
+// Problems of one sdl_learn call run on streams of their own (at most this many; problems beyond it
+// share streams round-robin).
 constexpr int kMaxBranches = 8;
-// Algorithm 1 iterations captured per graph (replayed K / this times; the remainder
-// is launched directly).
-constexpr int kItersPerGraph = 4;
 
 std::mutex g_mu;
 std::map<std::pair<int, hipStream_t>, Ctx*> g_ctx;
@@ -867,68 +859,42 @@ int iterate_problem(sdl_problem* p, int q, int K, const Opt& o, const Plan& pl, 
   return SDL_OK;
 }
 
-// One Algorithm 1 iteration of every problem, in order on L's stream.
-template <typename T>
-int one_iteration(sdl_problem* p, int nprob, int K, const Opt& o, const Plan& pl, Launcher& L) {
-  for (int q = 0; q < nprob; ++q) SDL_TRY(iterate_problem<T>(p, q, K, o, pl, L));
-  return SDL_OK;
+// Whether two problems of a call write the same buffer (they then run in order).
+bool share_results(const sdl_problem* p, int nprob) {
+  std::vector<const void*> out;
+  for (int q = 0; q < nprob; ++q) {
+    if (p[q].N == 0) continue;
+    const void* v[] = {p[q].D1, p[q].D2, p[q].supp, p[q].coef, p[q].res2};
+    out.insert(out.end(), v, v + 5);
+  }
+  std::sort(out.begin(), out.end());
+  return std::adjacent_find(out.begin(), out.end()) != out.end();
 }
 
-// The same while L's stream is being captured: the problems are independent (own
-// buffers; shared counters are updated atomically), so each gets a branch of the
-// graph, forked from and joined back into L's stream.
-template <typename T>
-int one_iteration_branched(sdl_problem* p, int nprob, int K, const Opt& o, const Plan& pl, Launcher& L, Ctx* ctx) {
-  int nact = 0;
-  for (int q = 0; q < nprob; ++q) nact += p[q].N > 0;
-  // a proposer's scratch buffers are shared by all problems: those run in order
-  if (nact <= 1 || o.proposer) return one_iteration<T>(p, nprob, K, o, pl, L);
-  const int nb = nact < kMaxBranches ? nact : kMaxBranches;
+// The streams of a call's problems: nb streams that start after what is queued on st ...
+int fork_branches(Ctx* ctx, hipStream_t st, int nb) {
   while ((int)ctx->branch.size() < nb) {
     hipStream_t s;
     hipEvent_t e;
     HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     ctx->branch.push_back(s);
+    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     ctx->branch_join.push_back(e);
   }
   if (!ctx->fork) HIP_TRY(hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
-  HIP_TRY(hipEventRecord(ctx->fork, L.st));
+  HIP_TRY(hipEventRecord(ctx->fork, st));
   for (int i = 0; i < nb; ++i) HIP_TRY(hipStreamWaitEvent(ctx->branch[i], ctx->fork, 0));
-  int slot = 0;
-  for (int q = 0; q < nprob; ++q) {
-    if (p[q].N == 0) continue;
-    Launcher B{ctx->branch[slot % nb], false, ctx, L.marks};
-    SDL_TRY(iterate_problem<T>(p, q, K, o, pl, B));
-    ++slot;
-  }
-  for (int i = 0; i < nb; ++i) {
-    HIP_TRY(hipEventRecord(ctx->branch_join[i], ctx->branch[i]));
-    HIP_TRY(hipStreamWaitEvent(L.st, ctx->branch_join[i], 0));
-  }
   return SDL_OK;
 }
-
-// Everything a captured learning graph bakes in: the problems (pointers and shapes), the
-// iterations per graph and K (the RMSE trace offsets), the options that select kernels or
-// enter kernel arguments, the workspace base and the kernel choices in force.  A later call
-// with an equal key replays the instantiated graph instead of capturing it again.
-std::vector<unsigned char> graph_key(const sdl_problem* p, int nprob, int K, int per, const Opt& o, const void* ws) {
-  std::vector<unsigned char> k;
-  auto put = [&k](const void* v, size_t n) {
-    const unsigned char* b = (const unsigned char*)v;
-    k.insert(k.end(), b, b + n);
-  };
-  put(p, sizeof(sdl_problem) * (size_t)nprob);
-  const long epoch = tuning_epoch();
-  const int ints[] = {nprob, K, per, o.prec, o.schedule, o.kernel, o.method};
-  const double dbl[] = {o.stop_rel, o.dep_eps, o.pivot_fp64, o.tau, o.err2, o.tie_band};
-  put(ints, sizeof(ints));
-  put(dbl, sizeof(dbl));
-  put(&o.proposer, sizeof(o.proposer));
-  put(&ws, sizeof(ws));
-  put(&epoch, sizeof(epoch));
-  return k;
+// ... and that st waits for.
+int join_branches(Ctx* ctx, hipStream_t st, int nb) {
+  int rc = SDL_OK;
+  for (int i = 0; i < nb; ++i) {
+    hipError_t e = hipEventRecord(ctx->branch_join[i], ctx->branch[i]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->branch_join[i], 0);
+    if (e != hipSuccess && rc == SDL_OK) rc = fail(SDL_E_DEVICE, "joining a branch: %s", hipGetErrorString(e));
+  }
+  return rc;
 }
 
 template <typename T>
@@ -952,56 +918,38 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
-  const bool graph = o.use_graph && !timing && K > 1;
-  if (graph) {
-    if (!ctx->side) {
-      HIP_TRY(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
-      HIP_TRY(hipEventCreateWithFlags(&ctx->join_a, hipEventDisableTiming));
-      HIP_TRY(hipEventCreateWithFlags(&ctx->join_b, hipEventDisableTiming));
-    }
-    HIP_TRY(hipEventRecord(ctx->join_a, st));
-    HIP_TRY(hipStreamWaitEvent(ctx->side, ctx->join_a, 0));
-    Launcher G{ctx->side, false, ctx, &marks};
-    const int per = K < kItersPerGraph ? K : kItersPerGraph;
-    std::vector<unsigned char> key = graph_key(p, nprob, K, per, o, wsb);
-    if (!ctx->gexec || key != ctx->gkey) {
-      if (ctx->gexec) (void)hipGraphExecDestroy(ctx->gexec);
-      if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
-      ctx->gexec = nullptr;
-      ctx->graph = nullptr;
-      ctx->gkey.clear();
-      hipGraph_t g = nullptr;
-      HIP_TRY(hipStreamBeginCapture(ctx->side, hipStreamCaptureModeRelaxed));
-      int rc = SDL_OK;
-      for (int it = 0; it < per && rc == SDL_OK; ++it) rc = one_iteration_branched<T>(p, nprob, K, o, pl, G, ctx);
-      hipError_t ce = hipStreamEndCapture(ctx->side, &g);
-      if (rc != SDL_OK) {
-        if (g) (void)hipGraphDestroy(g);
-        return rc;
+  // Every kernel of an iteration runs 8 us and more and takes 3-4 us to launch, so launching them
+  // directly keeps the GPU fed.  (Capturing four iterations as a graph and replaying it cost 0.2 ms a
+  // call whenever the call's buffers were not those of the call before, and gained nothing when they
+  // were: 0.186 ms an iteration of 100,000 8x8 signals replayed, 0.178 ms launched.)  Several problems run
+  // side by side on streams of their own: the tail of one problem's launch, where its last workgroups
+  // leave most of the chip idle, is another's work.  A proposer's buffers are shared by all problems:
+  // those run in order.
+  int nact = 0;
+  for (int q = 0; q < nprob; ++q) nact += p[q].N > 0;
+  const bool side_by_side = o.use_graph && !timing && nact > 1 && !o.proposer && !share_results(p, nprob);
+  const int nb = side_by_side ? (nact < kMaxBranches ? nact : kMaxBranches) : 0;
+  if (nb > 0) SDL_TRY(fork_branches(ctx, st, nb));
+  int lrc = SDL_OK;
+  for (int it = 0; it <= K && lrc == SDL_OK; ++it) {
+    int slot = 0;
+    for (int q = 0; q < nprob && lrc == SDL_OK; ++q) {
+      if (p[q].N == 0) continue;
+      Launcher B{nb > 0 ? ctx->branch[slot++ % nb] : st, timing, ctx, &marks, L.next_ev};
+      if (it < K) {
+        lrc = iterate_problem<T>(p, q, K, o, pl, B);
+      } else {
+        lrc = run_code<T>(p[q], pl.pb[q], o, pl, B);
+        if (lrc == SDL_OK) lrc = run_rmse<T>(p[q], pl.pb[q], pl, q, K, B);
       }
-      HIP_TRY(ce);
-      hipGraphExec_t ge = nullptr;
-      hipError_t ie = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-      if (ie != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        HIP_TRY(ie);
-      }
-      ctx->graph = g;
-      ctx->gexec = ge;
-      ctx->gkey.swap(key);
+      L.next_ev = B.next_ev;
     }
-    for (int it = 0; it + per <= K; it += per) HIP_TRY(hipGraphLaunch(ctx->gexec, ctx->side));
-    for (int it = 0; it < K % per; ++it) SDL_TRY(one_iteration<T>(p, nprob, K, o, pl, G));
-    HIP_TRY(hipEventRecord(ctx->join_b, ctx->side));
-    HIP_TRY(hipStreamWaitEvent(st, ctx->join_b, 0));
-  } else {
-    for (int it = 0; it < K; ++it) SDL_TRY(one_iteration<T>(p, nprob, K, o, pl, L));
   }
-  for (int q = 0; q < nprob; ++q) {
-    if (p[q].N == 0) continue;
-    SDL_TRY(run_code<T>(p[q], pl.pb[q], o, pl, L));
-    SDL_TRY(run_rmse<T>(p[q], pl.pb[q], pl, q, K, L));
+  if (nb > 0) {
+    const int jrc = join_branches(ctx, st, nb);
+    if (lrc == SDL_OK) lrc = jrc;
   }
+  SDL_TRY(lrc);
   int rc = finish_call(st, ctx, pl, o, marks, true);
   if (trace && (rc == SDL_OK || rc == SDL_E_SINGULAR)) {
     std::vector<double> h((size_t)(nprob > 0 ? nprob : 1) * (K + 1), 0.0);

@@ -145,8 +145,6 @@ hipError_t omp_fast_init_device();
 void omp_fast_set_choice(int m1, int m2, int n1, int n2, int s, int id);
 hipError_t autotune_problem(const OmpArgs<float>& a, hipStream_t st, int reps, int* chosen, double* best_ms);
 bool tuned_config(int m1, int m2, int n1, int n2, int s, int* lr, int* lc, int* wpe, int* mfma, double* ms);
-// Counter bumped whenever a kernel choice (autotuned or forced) changes.
-long tuning_epoch();
 // FP64: correlations (padding included) the variant picked for this two-mode shape keeps per signal,
 // 0 if none fits; sizes may exceed the two-mode limits (collapsed n-dimensional problems, at most
 // 4096 signal elements)

@@ -103,8 +103,9 @@ __global__ void __launch_bounds__(kSolveThreads)
 // 1.5 us each and their gaps before, a third of a 64-signal call).  A dictionary may be given as the
 // Kronecker product of several modes' (n-dimensional problems).  Workgroups of one dictionary each
 // stage it in LDS at an odd column stride, so that the Gram entries read LDS without bank conflicts,
-// and share the Gram matrix (512 entries each, at most kPrepParts of them).
-constexpr int kPrepParts = 8;
+// and share the Gram matrix (256 entries each, at most kPrepParts of them; a 72-atom Kronecker factor
+// in 8 parts took 13 us).
+constexpr int kPrepParts = 24;
 
 template <typename T>
 struct PrepBatch {
@@ -308,7 +309,7 @@ hipError_t launch_call_prep(const PrepJob<T>* jobs, int n, int* const* zero, con
         na *= g.n[d];
       }
       if ((mr + 1) * na > (SDL_MAX_M + 1) * SDL_MAX_N) return hipErrorInvalidValue;
-      const int parts = (na * na + 511) / 512;
+      const int parts = (na * na + 255) / 256;
       blocks += parts < kPrepParts ? parts : kPrepParts;
     }
     b.first[kMaxPrepJobs] = blocks;
