@@ -46,6 +46,7 @@ struct GCfg {
   static constexpr int G = LR * LC, NS = kWave / G, E = RI * CJ, P1 = LR * RI, P2 = LC * CJ;
   // waves per SIMD the registers must allow
   static constexpr int WPE = E <= 16 ? 4 : 2;
+  static constexpr int MAXW = 4 * WPE;  // waves per workgroup, at most what a CU's registers hold
   // table rows start on the boundary that a lane's run of RI (CJ) elements is read at
   __host__ __device__ static constexpr int run_align(int n) {
     const int b = n * (int)sizeof(T);
@@ -216,10 +217,8 @@ __device__ inline double rsqrt64(double x) {
 }
 __device__ inline float rsqrt64(float x) { return x; }  // never called
 
-constexpr int kGroupMaxWaves = 8;  // per workgroup
-
 template <class C>
-__global__ void __launch_bounds__(kWave* kGroupMaxWaves) __attribute__((amdgpu_waves_per_eu(C::WPE)))
+__global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_per_eu(C::WPE)))
     omp_group_kernel(OmpArgs<typename C::T> a) {
 #pragma clang fp contract(off)
   using T = typename C::T;

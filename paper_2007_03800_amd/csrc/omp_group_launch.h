@@ -12,7 +12,7 @@ constexpr int kGroupMaxBlocks = 4096;
 
 struct GroupVariant {
   int lanes;     // lanes per signal
-  int nmax1, nmax2, smax, elems;
+  int nmax1, nmax2, smax, elems, maxw;
   size_t (*lds)(int m1, int m2, int n1, int n2, int s, int wpb);
   const void* kernel;
 };
@@ -25,7 +25,7 @@ size_t lds_bytes(int m1, int m2, int n1, int n2, int s, int wpb) {
 
 template <class C>
 GroupVariant variant() {
-  return GroupVariant{C::G, C::P1, C::P2, C::SM, C::E, &lds_bytes<C>, reinterpret_cast<const void*>(&omp_group_kernel<C>)};
+  return GroupVariant{C::G, C::P1, C::P2, C::SM, C::E, C::MAXW, &lds_bytes<C>, reinterpret_cast<const void*>(&omp_group_kernel<C>)};
 }
 
 // Blocks of correlations per lane (RI x CJ).  Sixteen lanes per signal: up to 24 x 24 atoms and 16
@@ -91,14 +91,17 @@ hipError_t group_launch(const OmpArgs<T>& a, hipStream_t st) {
   if (!v) return hipErrorInvalidValue;
   const int ns = kWave / v->lanes;
   const int64_t waves = (a.N + ns - 1) / ns;
-  // waves per workgroup: the most waves per CU that LDS allows (they share one copy of the tables),
-  // but one workgroup per CU before a second wave in any
+  // waves per workgroup: the most waves per CU that LDS and registers allow, the waves of a workgroup
+  // sharing one copy of the tables (8x32 signals with 12x72 atoms in FP64, 62 KB of tables: 310 us
+  // with eight, 229 us with sixteen for 20,000 signals), four where that is no worse; but one
+  // workgroup per CU before a second wave in any
   int wpb = 1, best = 0;
-  for (int w = 1; w <= kGroupMaxWaves; w *= 2) {
+  for (int w = 1; w <= v->maxw; w *= 2) {
     const size_t lds = v->lds(a.m1, a.m2, a.n1, a.n2, a.s, w);
     if (lds > kLdsPerCu) break;
-    const int on = (int)(kLdsPerCu / lds) * w;
-    if (w == 1 || (on > best && (w <= 4 || best < 8))) {
+    int on = (int)(kLdsPerCu / lds) * w;
+    if (on > v->maxw) on = v->maxw;
+    if (on > best || (on == best && w <= 4)) {
       best = on;
       wpb = w;
     }
