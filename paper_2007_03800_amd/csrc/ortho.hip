@@ -187,6 +187,26 @@ __global__ void __launch_bounds__(kWave* kOWaves) ortho_code_kernel(OmpArgs<T> a
   }
 }
 
+// 1 / sqrt(x), 1 <= x <= 2: the hardware's estimate (below 2^-22 relative) and one third-order
+// correction y (1 + e/2 + 3 e^2/8), e = 1 - x y^2
+__device__ inline double inv_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x), e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+__device__ inline double inv_est(double x) {  // 1 / x to about 2^-44: the estimate, corrected once
+  const double y = __builtin_amdgcn_rcp(x);
+  return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+// t = sign(z) / (|z| + sqrt(1 + z^2)), z = num / den, to about 2^-22: it only decides how much of the
+// pair's inner product one rotation leaves.  Written as den / (|num| + sqrt(num^2 + den^2)), both
+// scaled by the larger so that nothing overflows, and with the sign of z
+__device__ inline double rotation_tangent(double num, double den) {
+  const double an = fabs(num), ad = fabs(den), s = inv_est(fmax(an, ad));
+  const double a = an * s, b = ad * s;
+  const double t = b * inv_est(a + __builtin_amdgcn_sqrt(__builtin_fma(a, a, b * b)));
+  return (num >= 0) == (den > 0) || num == 0 ? t : -t;
+}
+
 // One wave: the last stage of the fixed-order reduction of the partial rows (row stride ld),
 // then the polar factor of B (the n x n block of the sums after A) by one-sided Jacobi
 // rotations (n <= 8: four disjoint column pairs at a time in round-robin order; larger n: lane x
@@ -204,15 +224,15 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
   const int x = threadIdx.x;
   const int nent = n * n;
   for (int e = x; e < nent; e += kWave) {
-    // B follows A in the row; eight rows' loads in flight, added in row order
+    // B follows A in the row; sixteen rows' loads in flight, added in row order
     double v = 0.0;
     int b = 0;
-    for (; b + 8 <= nrow; b += 8) {
-      double q[8];
+    for (; b + 16 <= nrow; b += 16) {
+      double q[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] = src[(size_t)(b + u) * ld + nent + e];
+      for (int u = 0; u < 16; ++u) q[u] = src[(size_t)(b + u) * ld + nent + e];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v += q[u];
+      for (int u = 0; u < 16; ++u) v += q[u];
     }
     for (; b < nrow; ++b) v += src[(size_t)b * ld + nent + e];
     W[e] = v;
@@ -241,9 +261,12 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
           if (i > j) { const int tmp = i; i = j; j = tmp; }
         }
         const bool act = j >= 0 && j < n;  // a real pair (the dummy column is n)
-        double pa = 0.0, pb = 0.0, pg = 0.0;
+        double pa = 0.0, pb = 0.0, pg = 0.0, wi = 0.0, wj = 0.0, vi = 0.0, vj = 0.0;
         if (act && r < n) {
-          const double wi = W[r + n * i], wj = W[r + n * j];
+          wi = W[r + n * i];
+          wj = W[r + n * j];
+          vi = V[r + n * i];
+          vj = V[r + n * j];
           pa = wi * wi;
           pb = wj * wj;
           pg = wi * wj;
@@ -258,16 +281,16 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
         pa += dpp_move<kDppHalfMirror>(pa);
         pb += dpp_move<kDppHalfMirror>(pb);
         pg += dpp_move<kDppHalfMirror>(pg);
-        const bool rot = act && !(fabs(pg) <= 1e-15 * sqrt(pa * pb) || pg == 0.0);
+        // Where the rotation's tangent is rounded does not matter as long as c^2 + s^2 = 1: the
+        // hardware's estimates with one correction give it (the chain of full divisions and square
+        // roots was most of a round), and c comes at full precision
+        const bool rot = act && !(fabs(pg) <= 1e-15 * __builtin_amdgcn_sqrt(pa * pb) || pg == 0.0);
         if (rot) {
-          const double zeta = (pb - pa) / (2.0 * pg);
-          const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-          const double c = 1.0 / sqrt(1.0 + t * t), sn = c * t;
+          const double t = rotation_tangent(pb - pa, 2.0 * pg);
+          const double c = inv_sqrt(1.0 + t * t), sn = c * t;
           if (r < n) {
-            const double wi = W[r + n * i], wj = W[r + n * j];
             W[r + n * i] = c * wi - sn * wj;
             W[r + n * j] = sn * wi + c * wj;
-            const double vi = V[r + n * i], vj = V[r + n * j];
             V[r + n * i] = c * vi - sn * vj;
             V[r + n * j] = sn * vi + c * vj;
           }
@@ -331,22 +354,28 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     }
     return;
   }
-  // D[x][c] = sum_i (W[x][i] / sigma_i) V[c][i]
-  if (row)
-    for (int c = 0; c < n; ++c) {
-      double v = 0.0;
-      for (int i = 0; i < n; ++i) v += (W[x + n * i] / sig[i]) * V[c + n * i];
-      Dn[x + n * c] = v;
-      D[x + n * c] = v;
-      Dc[x + n * c] = (T)v;
-    }
+  // D[r][c] = sum_i (W[r][i] / sigma_i) V[c][i] and the Gram matrix, one entry per lane and pass (one
+  // row per lane, with a division per term, took 8 of 28 us at n = 8)
   wave_sync();
-  if (row)
-    for (int c = 0; c < n; ++c) {
-      double v = 0.0;
-      for (int r = 0; r < n; ++r) v += Dn[r + n * x] * Dn[r + n * c];
-      Gc[x + n * c] = (T)v;
-    }
+  if (row) sig[x] = 1.0 / sig[x];
+  wave_sync();
+  for (int e = x; e < nent; e += kWave) {
+    const int r = e % n, c = e / n;
+    double v = 0.0;
+#pragma unroll 4
+    for (int i = 0; i < n; ++i) v += (W[r + n * i] * sig[i]) * V[c + n * i];
+    Dn[e] = v;
+    D[e] = v;
+    Dc[e] = (T)v;
+  }
+  wave_sync();
+  for (int e = x; e < nent; e += kWave) {
+    const int i = e % n, c = e / n;
+    double v = 0.0;
+#pragma unroll 4
+    for (int r = 0; r < n; ++r) v += Dn[r + n * i] * Dn[r + n * c];
+    Gc[e] = (T)v;
+  }
 }
 
 size_t ortho_lds(int m1, int m2, size_t elem) {
