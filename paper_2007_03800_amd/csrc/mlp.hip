@@ -430,12 +430,15 @@ __global__ void __launch_bounds__(256) gather_grad_kernel(const float* part, int
 // A workgroup of eight waves carries 64 signals through all layers with the activations in LDS (one
 // buffer: a layer's results wait in registers, already activated and rounded, until every wave has
 // read its inputs), so only the signals are read and only the logits written; the weights (0.9 MB at
-// 512 units) are read from L2 as MFMA fragments, 16 contiguous bytes a lane, the next slice in flight
-// while the current one multiplies.  A wave owns the 16-column tiles w, w + 8, ... of a layer.
-// What bounds it: the vector-ALU instructions of erff (about 45 a value, 2 x 512 values a signal);
-// two workgroups share a CU so that one's products run beside the other's GELUs.  Same operations as
-// the layer-by-layer kernels in the same order, bit for bit: 65,536 signals, 512 units: 60 + 142 +
-// 70 us for the three layers and 17 us for the normalisation before.
+// 512 units) are read from L2 as MFMA fragments, 16 contiguous bytes a lane.  A wave owns the
+// 16-column tiles w, w + 8, ... of a layer.
+// What bounds it: the vector-ALU instructions of erff (25-45 a value, 2 x 512 values a signal) and the
+// waits between a layer's phases; two workgroups share a CU so that one's products run beside the
+// other's GELUs.  Four waves a SIMD (128 registers) hide the weights' latency better than loading a
+// slice ahead, whose 16 registers spilled (171 against 152 us); one rolled copy of the two hidden
+// layers spilled more.  Same operations as the layer-by-layer kernels in the same order, bit for bit:
+// 65,536 signals, 512 units: 60 + 142 + 70 us for the three layers and 17 us for the normalisation
+// before.
 constexpr int kFwdRows = 64, kFwdWaves = 8;
 
 template <int NT>
@@ -476,23 +479,15 @@ __global__ void __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_pe
     }
     unsigned ob = (unsigned)(r16 * K + 8 * kq);  // this lane's place in a tile
     const __bf16* pa = act + r16 * ld + 8 * kq;
-    bf16x8 b[2][NT];
+    for (int k = 0; k < K; k += 32) {
+      bf16x8 b[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) b[0][j] = *reinterpret_cast<const bf16x8*>(pb[j] + ob);
-    for (int k0 = 0; k0 < K; k0 += 64) {  // K is a multiple of 64: two slices a turn
+      for (int j = 0; j < NT; ++j) b[j] = *reinterpret_cast<const bf16x8*>(pb[j] + (ob + k));
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int k = k0 + 32 * u;
-        if (k + 32 < K) {
+      for (int i = 0; i < 4; ++i) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(pa + 16 * i * ld + k);
 #pragma unroll
-          for (int j = 0; j < NT; ++j) b[1 - u][j] = *reinterpret_cast<const bf16x8*>(pb[j] + (ob + k + 32));
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(pa + 16 * i * ld + k);
-#pragma unroll
-          for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[u][j], acc[i][j], 0, 0, 0);
-        }
+        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[j], acc[i][j], 0, 0, 0);
       }
     }
   };
