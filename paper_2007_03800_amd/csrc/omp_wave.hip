@@ -31,6 +31,7 @@
 // sums kernel.  FP32 shapes compiled in omp_quad.hip are dispatched there instead.
 #include <limits.h>
 
+#include "lanes.h"
 #include "sdl_internal.h"
 
 namespace sdl {
@@ -67,6 +68,19 @@ template <typename U>
 __device__ inline U wave_sum(U v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
+// The same sum (the same pairs added at every stage) without the six LDS permutes: halves and rows
+// swapped by permlane, then rotations and quad swaps inside the rows.
+__device__ inline float wave_sum_lanes(float v) {
+  auto bits = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(bits[0]) + __uint_as_float(bits[1]);
+  bits = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(bits[0]) + __uint_as_float(bits[1]);
+  v += dpp<0x128>(v, v);  // row_ror:8
+  v += dpp<0x124>(v, v);  // row_ror:4
+  v += dpp<kDppXor2>(v, v);
+  v += dpp<kDppXor1>(v, v);
   return v;
 }
 
@@ -613,6 +627,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
   // in every table), so they are never selected
 
   unsigned n_early = 0;  // early-stopped signals of this wave (lane 0), counted once at the end
+  int tprev = S;         // atoms of the signal before (the scratch starts out unknown)
   for (int64_t k = (int64_t)blockIdx.x * C::WPB + wv; k < a.N; k += (int64_t)gridDim.x * C::WPB) {
     float yy = 0.f;
     for (int e = lane; e < M; e += kWave) {
@@ -620,7 +635,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
       ysT[e / M1 + YQ * (e % M1)] = v;
       yy += v * v;
     }
-    const float yy_all = wave_sum(yy);
+    const float yy_all = L::PK ? wave_sum_lanes(yy) : wave_sum(yy);  // (shorter supports: 16 registers more)
     const float ynorm = sqrtf(yy_all);
     float renergy = yy_all;  // ||r||^2 by the OMP recurrence (error-driven stop)
     wave_sync();
@@ -679,7 +694,17 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
         for (int tj = 0; tj < TC; ++tj) acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ti], bv[tj], acc[ti][tj], 0, 0, 0);
     }
     wave_sync();  // W is read: the scratch it aliases is cleared next
-    for (int e = lane; e < L::SCR; e += kWave) LiR[e] = 0.f;
+    if constexpr (L::PK) {
+      // long caps: most of the scratch was never written since the last clear.  The rows and columns
+      // of the signal before (tprev atoms), what W overwrote, and the vectors after the factor
+      const int rows = lrow<L>(tprev), cols = tprev < S ? lcol<L>(tprev) : L::LPK;
+      for (int e = lane; e < (rows > L::WSM ? rows : L::WSM); e += kWave) LiR[e] = 0.f;
+      for (int e = lane; e < cols; e += kWave) LiT[e] = 0.f;
+      for (int e = lane; e < 5 * SP; e += kWave) gam[e] = 0.f;
+      static_assert(L::WSM <= L::LPK || !L::PK, "W lies within the rows of L^{-1}");
+    } else {
+      for (int e = lane; e < L::SCR; e += kWave) LiR[e] = 0.f;
+    }
     wave_sync();
 
     float my_x = 0.f;
@@ -754,6 +779,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
         }
       }
     }
+    tprev = t;
     // explicit residual Y - D1_S diag(x) D2_S^T on the matrix cores: four support terms per
     // 16x16x4 MFMA (terms beyond t have x = 0; support atoms beyond t are atom 0)
     wave_sync();
@@ -800,7 +826,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
             rr += r * r;
           }
         }
-    rr = wave_sum(rr);
+    rr = L::PK ? wave_sum_lanes(rr) : wave_sum(rr);
     if (lane < S) {
       a.supp[k * S + lane] = lane < t ? my_i + N1 * my_j : -1;
       a.coef[k * S + lane] = lane < t ? my_x : 0.f;
