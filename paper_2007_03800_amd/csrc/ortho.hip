@@ -216,7 +216,7 @@ __device__ inline double rotation_tangent(double num, double den) {
 template <typename T>
 __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restrict__ src, int nrow, int ld, int n,
                                                            double* D, T* Dc, T* Gc, int* status,
-                                                           unsigned long long* counters) {
+                                                           unsigned long long* counters, RmseOut ro) {
   __shared__ double W[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];  // column-major n x n
   __shared__ double V[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];
   __shared__ double Dn[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];
@@ -238,6 +238,18 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     W[e] = v;
     V[e] = (e % n) == (e / n) ? 1.0 : 0.0;
   }
+  if (ro.trace) {
+    // the RMSE of the sweep that wrote the rows, from their residual sums
+    double v = 0.0;
+    for (int b = x; b < nrow; b += kWave) v += src[(size_t)b * ld + ro.idx];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    if (x == 0) {
+      const int it = *ro.counter;
+      ro.trace[(size_t)it + ro.offset] = ro.denom > 0 ? sqrt(v / ro.denom) : 0.0;
+      *ro.counter = it + 1;
+    }
+  }
   wave_sync();
   const bool row = x < n;
   if (n <= 8) {
@@ -248,18 +260,18 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     const int np = n + (n & 1), q = x / 8, r = x % 8;
     for (int sweep = 0; sweep < 60; ++sweep) {
       bool rotated = false;
+      // the q-th pair of a round: columns round + q and round - q (mod np - 1), stepped by one a round;
+      // pair 0 is the last column with column `round`
+      int up = q, down = q == 0 ? 0 : np - 1 - q;
       for (int round = 0; round < np - 1; ++round) {
         int i = -1, j = -1;
         if (q < np / 2) {
-          if (q == 0) {
-            i = np - 1;
-            j = round;
-          } else {
-            i = (round + q) % (np - 1);
-            j = (round - q + np - 1) % (np - 1);
-          }
+          i = q == 0 ? np - 1 : up;
+          j = down;
           if (i > j) { const int tmp = i; i = j; j = tmp; }
         }
+        up = up + 1 == np - 1 ? 0 : up + 1;
+        down = down + 1 == np - 1 ? 0 : down + 1;
         const bool act = j >= 0 && j < n;  // a real pair (the dummy column is n)
         double pa = 0.0, pb = 0.0, pg = 0.0, wi = 0.0, wj = 0.0, vi = 0.0, vj = 0.0;
         if (act && r < n) {
@@ -404,9 +416,9 @@ hipError_t launch_ortho_code(const OmpArgs<T>& a, hipStream_t st) {
 
 template <typename T>
 hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, T* Gc,
-                             int* status, unsigned long long* counters, hipStream_t st) {
+                             int* status, unsigned long long* counters, const RmseOut& r, hipStream_t st) {
   hipLaunchKernelGGL(procrustes_kernel<T>, dim3(1), dim3(kWave), 0, st, src, nrow, ld, n, D, Dc, Gc, status,
-                     counters);
+                     counters, r);
   return hipGetLastError();
 }
 
@@ -422,8 +434,8 @@ hipError_t ortho_init_device() {
 template hipError_t launch_ortho_code<float>(const OmpArgs<float>&, hipStream_t);
 template hipError_t launch_ortho_code<double>(const OmpArgs<double>&, hipStream_t);
 template hipError_t launch_procrustes<float>(const double*, int, int, int, double*, float*, float*, int*,
-                                             unsigned long long*, hipStream_t);
+                                             unsigned long long*, const RmseOut&, hipStream_t);
 template hipError_t launch_procrustes<double>(const double*, int, int, int, double*, double*, double*, int*,
-                                              unsigned long long*, hipStream_t);
+                                              unsigned long long*, const RmseOut&, hipStream_t);
 
 }  // namespace sdl

@@ -497,19 +497,17 @@ int run_reduce_solve(int side, const sdl_problem& r, const PBuf& b, const Plan& 
     HIP_TRY(e);
     SDL_TRY(L.end());
   }
+  RmseOut ro{nullptr, nullptr, 0, 0, 0.0};
+  if (rmse_q >= 0) ro = RmseOut{pl.trace, pl.iter + rmse_q, rmse_q * (K + 1), nent, (double)r.N * r.m1 * r.m2};
   if (method == 1) {
     // Remark 1: the orthogonal Procrustes update from the B block of the reduced sums
     SDL_TRY(L.begin(3));
     if (side == 1)
-      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n1, r.D1, (T*)b.Dc1, (T*)b.G1c, pl.status, pl.counters,
-                                   L.st));
+      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n1, r.D1, (T*)b.Dc1, (T*)b.G1c, pl.status, pl.counters, ro, L.st));
     else
-      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n2, r.D2, (T*)b.Dc2, (T*)b.G2c, pl.status, pl.counters,
-                                   L.st));
+      HIP_TRY(launch_procrustes<T>(src, nrow, ld, r.n2, r.D2, (T*)b.Dc2, (T*)b.G2c, pl.status, pl.counters, ro, L.st));
     return L.end();
   }
-  RmseOut ro{nullptr, nullptr, 0, 0, 0.0};
-  if (rmse_q >= 0) ro = RmseOut{pl.trace, pl.iter + rmse_q, rmse_q * (K + 1), nent, (double)r.N * r.m1 * r.m2};
   SDL_TRY(L.begin(3));
   if (side == 1)
     HIP_TRY(launch_tmod_solve<T>(src, nrow, ld, b.sums, r.m1, r.n1, r.D1, (T*)b.Dc1, (T*)b.G1c, b.w,
@@ -839,8 +837,7 @@ int iterate_problem(sdl_problem* p, int q, int K, const Opt& o, const Plan& pl, 
       // Remark 1's variant with the B sums of each Procrustes update in the coding epilogue
       const int rows = (int)ortho_mfma_partial_rows(r.N, r.m1, r.m2, r.s);
       SDL_TRY(run_omp<T>(r, b, o, pl, 1, L));
-      SDL_TRY(run_rmse<T>(r, b, pl, q, K, L));
-      SDL_TRY(run_reduce_solve<T>(1, r, b, pl, rows, true, -1, K, L, 1));
+      SDL_TRY(run_reduce_solve<T>(1, r, b, pl, rows, true, q, K, L, 1));
       SDL_TRY(run_omp<T>(r, b, o, pl, 2, L));
       SDL_TRY(run_reduce_solve<T>(2, r, b, pl, rows, true, -1, K, L, 1));
     } else {

@@ -110,9 +110,10 @@ bool omp_quad_supported(int m1, int m2, int n1, int n2, int s);
 bool ortho_supported(int m1, int m2, int n1, int n2, int s);
 template <typename T>
 hipError_t launch_ortho_code(const OmpArgs<T>& a, hipStream_t st);
+struct RmseOut;
 template <typename T>
-hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, T* Gc,
-                             int* status, unsigned long long* counters, hipStream_t st);
+hipError_t launch_procrustes(const double* src, int nrow, int ld, int n, double* D, T* Dc, T* Gc, int* status,
+                             unsigned long long* counters, const RmseOut& r, hipStream_t st);
 hipError_t ortho_init_device();
 // SDL_MIXED_BF16 sparse coding (omp_mixed.hip): correlations D1^T R D2 on the BF16 matrix
 // cores every step, near-ties re-scored in FP32; shapes it is compiled for.
