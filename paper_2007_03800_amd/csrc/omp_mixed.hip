@@ -26,6 +26,10 @@
 //    key is within the band may hold a third candidate that is not re-scored; such steps are
 //    counted.  The winner's exact correlation drives the coefficient update, so the
 //    coefficients do not see BF16 rounding.
+//    What bounds it: vector instructions (about 1,000 a step for 16 signals of 576 atoms, 80% of the
+//    issue slots at the two waves a SIMD that the registers allow; three waves spill and lose 8%).
+//    1,000,000 signals, 12x12 patches, 24x24 atoms, 12 steps: 2.06 ms before the keys' fused maxima
+//    (two_largest), atoms carried as (j, i) and candidates re-scored in any order; 1.86-1.91 ms with them.
 //  * Cholesky factor, coefficient updates, small-pivot FP64 path, implicit masking and the
 //    branch-free step (results committed with selects) as in omp_mfma.hip.
 #include <limits.h>
@@ -96,6 +100,18 @@ constexpr int tri(int k, int l) { return k * (k + 1) / 2 + l; }
 
 // middle of three (compiles to v_med3_u32)
 __device__ inline unsigned umed3(unsigned a, unsigned b, unsigned c) { return max(min(a, b), min(max(a, b), c)); }
+// (a1, a2) <- the two largest of {a1, a2, x, y}, a1 >= a2: med3, max, max3.  The empty statement keeps
+// the compiler from sharing max(a1, x) between the two, which costs the fused forms.
+__device__ inline void two_largest(unsigned& a1, unsigned& a2, unsigned x, unsigned y) {
+  unsigned mid = umed3(a1, x, y);
+  asm("" : "+v"(mid), "+v"(x));
+  a2 = max(a2, mid);
+  a1 = max(a1, max(x, y));
+}
+
+// Atoms are carried as j << 8 | i: ordered like i + n1 j, and split without a division.
+__device__ inline int atom_i(int atom) { return atom & 0xFF; }
+__device__ inline int atom_j(int atom) { return atom >> 8; }
 
 // atom of a packed key held by lane c of its signal.  Low 8 bits of a key: (3 - pair) << 6 |
 // (63 - local), where the tile column bj = 2 pair + bl and local = (bl TI + bi) 4 + v, so larger
@@ -106,17 +122,14 @@ __device__ inline int key_atom(unsigned key, int c) {
   const int bl = local / (4 * C::TI), rem = local % (4 * C::TI);
   const int v = rem & 3, bi = rem >> 2;
   const int bj = min(2 * pair + bl, C::TJ - 1);  // in range for any key
-  return (4 * bi + v) + C::N1 * (4 * bj + c);
+  return (4 * bi + v) + ((4 * bj + c) << 8);
 }
 
-// (key, atom) of the quad's lanes merged: larger key, ties to the smaller atom
-template <int CTRL>
-__device__ inline void quad_argmax_stage(unsigned& key, int& atom) {
-  const unsigned ok = (unsigned)dpp<CTRL>((int)key);
-  const int oa = dpp<CTRL>(atom);
-  const bool take = ok > key || (ok == key && oa < atom);
-  key = take ? ok : key;
-  atom = take ? oa : atom;
+// maximum over the four lanes of a signal
+template <typename I>
+__device__ inline I quad_max(I v) {
+  v = max(v, (I)dpp<0xB1>((int)v));
+  return max(v, (I)dpp<0x4E>((int)v));
 }
 
 // Exact FP32 correlation of atom (i, j) with the signal's residual: this lane's rows
@@ -146,7 +159,7 @@ template <class C>
 struct Wave {
   f32x4 rt[C::TQ][C::TP];  // R^T tiles (see the file comment)
   float x[C::S];           // coefficients in selection order
-  int at[C::S];            // atoms a = i + n1 j in selection order
+  int at[C::S];            // atoms (j << 8 | i) in selection order
   float* L;                // this signal's inverse Cholesky factor, rows with the diagonal (LDS)
   bool active;
   int nsel;
@@ -202,10 +215,8 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
           const unsigned k2v = (__float_as_uint(al[2]) & 0x7FFFFF00u) | (61u - e0);
           const unsigned k3v = (__float_as_uint(al[3]) & 0x7FFFFF00u) | (60u - e0);
           // two largest of {la1, la2, k0v, k1v}: the second is max(la2, med3(la1, k0v, k1v))
-          la2 = max(la2, umed3(la1, k0v, k1v));
-          la1 = max(la1, max(k0v, k1v));
-          lb2 = max(lb2, umed3(lb1, k2v, k3v));
-          lb1 = max(lb1, max(k2v, k3v));
+          two_largest(la1, la2, k0v, k1v);
+          two_largest(lb1, lb2, k2v, k3v);
         }
       }
     }
@@ -222,36 +233,32 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
   }
   const unsigned m1 = max(ka1, kb1), m2 = max(min(ka1, kb1), max(ka2, kb2));
 
-  // ---- the signal's largest BF16 |corr| and the band of near-ties
-  unsigned mkey = m1 & ~0xFFu;
-  int matom = key_atom<C>(m1, c);
-  quad_argmax_stage<0xB1>(mkey, matom);
-  quad_argmax_stage<0x4E>(mkey, matom);
+  // ---- the signal's largest BF16 |corr| (ties to the smaller atom) and the band of near-ties
+  const unsigned v1 = m1 & ~0xFFu, v2 = m2 & ~0xFFu;
+  const int a1 = key_atom<C>(m1, c), a2 = key_atom<C>(m2, c);
+  const unsigned mkey = quad_max(v1);
+  const int matom = -quad_max(v1 == mkey ? -a1 : -0xFFFF);
   const unsigned thr = __float_as_uint(__uint_as_float(mkey) * keep) & ~0xFFu;
 
-  // ---- re-score the candidates within the band in FP32; the pick is the largest exact |corr|.
-  // First the signal's BF16 maximum (its atom is known to the four lanes), then, while some
-  // signal of the wave has candidates left, each signal's largest remaining one: the quad's
-  // argmax over its lanes' remaining keys, whose owner lane then drops it.
-  float best_cor = exact_corr<C>(w.rt, sD1, sD2c, matom % N1, matom / N1, c);
+  // ---- re-score the candidates within the band in FP32; the pick is the largest exact |corr|
+  // (ties: smaller atom), whichever order they come in: first the BF16 maximum, then, while some
+  // signal of the wave has candidates left, each signal's largest remaining atom number, which the
+  // lane that holds it drops.  (Taking them in key order cost 45 more instructions a candidate.)
+  float best_cor = exact_corr<C>(w.rt, sD1, sD2c, atom_i(matom), atom_j(matom), c);
   float best_abs = fabsf(best_cor);
   int best_atom = matom, ncand = 1;
   best_abs = best_abs == best_abs ? best_abs : -1.f;  // NaN: no valid candidate
-  unsigned c1 = ((m1 & ~0xFFu) >= thr && key_atom<C>(m1, c) != matom) ? m1 : 0u;
-  unsigned c2 = (m2 & ~0xFFu) >= thr ? m2 : 0u;
-  const bool overflow = c2 != 0u;  // a third candidate of this lane may exist
-  while (__any((c1 | c2) != 0u)) {
-    const unsigned ck = max(c1, c2);
-    unsigned kq = ck;
-    int aq = ck ? key_atom<C>(ck, c) : INT_MAX;
-    quad_argmax_stage<0xB1>(kq, aq);
-    quad_argmax_stage<0x4E>(kq, aq);
-    if (ck && key_atom<C>(ck, c) == aq) {  // this lane owned it
-      if (c1 == ck) c1 = 0u; else c2 = 0u;
-    }
-    const bool cand = kq != 0u;
+  // a stopped signal has no candidates: its pick is not used
+  int c1 = w.active && v1 >= thr && m1 != 0u && a1 != matom ? a1 : -1;
+  int c2 = w.active && v2 >= thr && m2 != 0u ? a2 : -1;
+  const bool overflow = c2 >= 0;  // a third candidate of this lane may exist
+  while (__any(max(c1, c2) >= 0)) {
+    const int aq = quad_max(max(c1, c2));
+    c1 = c1 == aq ? -1 : c1;
+    c2 = c2 == aq ? -1 : c2;
+    const bool cand = aq >= 0;
     const int at = cand ? aq : matom;
-    const float e = exact_corr<C>(w.rt, sD1, sD2c, at % N1, at / N1, c);
+    const float e = exact_corr<C>(w.rt, sD1, sD2c, atom_i(at), atom_j(at), c);
     const float ae = fabsf(e);
     const bool take = cand && (ae > best_abs || (ae == best_abs && at < best_atom));
     best_abs = take ? ae : best_abs;
@@ -271,7 +278,7 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
   }
   // a non-finite signal: best_abs < 0 stops it
   const int ba = best_atom;
-  const int it = ba % N1, jt = ba / N1;
+  const int it = atom_i(ba), jt = atom_j(ba);
   const float cor = best_cor;
   bool stop = !(best_abs > w.stop_thr);
 #pragma unroll
@@ -284,7 +291,7 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
   float* Li = w.L;
   float gv[S > 1 ? S - 1 : 1], wv[S > 1 ? S - 1 : 1];
 #pragma unroll
-  for (int k = 0; k < T; ++k) gv[k] = sG1[w.at[k] % N1 + N1 * it] * sG2[w.at[k] / N1 + N2 * jt];
+  for (int k = 0; k < T; ++k) gv[k] = sG1[atom_i(w.at[k]) + N1 * it] * sG2[atom_j(w.at[k]) + N2 * jt];
   const float gaa = sG1[it + N1 * it] * sG2[jt + N2 * jt];
   float d2;
   {
@@ -300,15 +307,19 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
     d2 = gaa - ww;
     if (w.active && d2 < piv * gaa) {
       // small pivot: w and |w|^2 again in FP64 (cancellation in G_aa - |w|^2)
-      double accd = 0.0;
+      double accd = 0.0, gd[S > 1 ? S - 1 : 1];
 #pragma unroll
-      for (int k = 0; k < T; ++k) {
+      for (int l = 0; l < T; ++l)
+        gd[l] = (double)sG1[atom_i(w.at[l]) + N1 * it] * (double)sG2[atom_j(w.at[l]) + N2 * jt];
+#pragma unroll 1
+      for (int k = 0; k < T; ++k) {  // rolled: unrolled, it alone set the kernel's registers
+        const float* row = Li + k * (k + 1) / 2;
         double b = 0.0;
 #pragma unroll
-        for (int l = 0; l <= k; ++l)
-          b += (double)Li[tri(k, l)] *
-               ((double)sG1[w.at[l] % N1 + N1 * it] * (double)sG2[w.at[l] / N1 + N2 * jt]);
-        wv[k] = (float)b;
+        for (int l = 0; l < T; ++l)
+          if (l <= k) b += (double)row[l] * gd[l];
+#pragma unroll
+        for (int l = 0; l < T; ++l) wv[l] = l == k ? (float)b : wv[l];
         accd += b * b;
       }
       d2 = (float)((double)gaa - accd);
@@ -343,7 +354,7 @@ __device__ __forceinline__ void mixed_step(Wave<C>& w, const OmpArgs<float>& a, 
     for (int k = 0; k <= T; ++k) {
       const float gk = !w.active ? 0.f : k == T ? -cst : cst * vv[k < T ? k : 0];
       const int ak = k == T ? ba : w.at[k];
-      const int ik = ak % N1, jk = ak / N1;
+      const int ik = atom_i(ak), jk = atom_j(ak);
       float av[TQ], bv[TP];
 #pragma unroll
       for (int bq = 0; bq < TQ; ++bq) av[bq] = gk * sD2[(4 * bq + c) + C::LD2 * jk];
@@ -470,7 +481,7 @@ __global__ void __launch_bounds__(kWave* kXWaves) __attribute__((amdgpu_waves_pe
 #pragma unroll
       for (int t = 0; t < S; ++t) {
         if (t % kXLanes == c) {
-          a.supp[k * S + t] = t < w.nsel ? w.at[t] : -1;
+          a.supp[k * S + t] = t < w.nsel ? atom_i(w.at[t]) + N1 * atom_j(w.at[t]) : -1;
           a.coef[k * S + t] = t < w.nsel ? w.x[t] : 0.f;
         }
       }
