@@ -862,7 +862,8 @@ bool share_results(const sdl_problem* p, int nprob) {
   for (int q = 0; q < nprob; ++q) {
     if (p[q].N == 0) continue;
     const void* v[] = {p[q].D1, p[q].D2, p[q].supp, p[q].coef, p[q].res2};
-    out.insert(out.end(), v, v + 5);
+    for (const void* b : v)
+      if (b) out.push_back(b);
   }
   std::sort(out.begin(), out.end());
   return std::adjacent_find(out.begin(), out.end()) != out.end();
