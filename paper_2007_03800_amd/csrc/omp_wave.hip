@@ -635,7 +635,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
       ysT[e / M1 + YQ * (e % M1)] = v;
       yy += v * v;
     }
-    const float yy_all = L::PK ? wave_sum_lanes(yy) : wave_sum(yy);  // (shorter supports: 16 registers more)
+    const float yy_all = wave_sum(yy);
     const float ynorm = sqrtf(yy_all);
     float renergy = yy_all;  // ||r||^2 by the OMP recurrence (error-driven stop)
     wave_sync();
@@ -826,7 +826,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
             rr += r * r;
           }
         }
-    rr = L::PK ? wave_sum_lanes(rr) : wave_sum(rr);
+    rr = L::PK ? wave_sum_lanes(rr) : wave_sum(rr);  // (shorter supports: 16 registers more)
     if (lane < S) {
       a.supp[k * S + lane] = lane < t ? my_i + N1 * my_j : -1;
       a.coef[k * S + lane] = lane < t ? my_x : 0.f;
