@@ -187,32 +187,162 @@ __global__ void __launch_bounds__(kWave* kOWaves) ortho_code_kernel(OmpArgs<T> a
   }
 }
 
-// 1 / sqrt(x), 1 <= x <= 2: the hardware's estimate (below 2^-22 relative) and one third-order
-// correction y (1 + e/2 + 3 e^2/8), e = 1 - x y^2
-__device__ inline double inv_sqrt(double x) {
-  const double y = __builtin_amdgcn_rsq(x), e = __builtin_fma(-(x * y), y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+__device__ inline double wave_sum(double v) {
+  v = row16_sum(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
-__device__ inline double inv_est(double x) {  // 1 / x to about 2^-44: the estimate, corrected once
-  const double y = __builtin_amdgcn_rcp(x);
+__device__ inline double reciprocal(double x) {  // the hardware's estimate, corrected twice
+  double y = __builtin_amdgcn_rcp(x);
+  y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
   return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
 }
-// t = sign(z) / (|z| + sqrt(1 + z^2)), z = num / den, to about 2^-22: it only decides how much of the
-// pair's inner product one rotation leaves.  Written as den / (|num| + sqrt(num^2 + den^2)), both
-// scaled by the larger so that nothing overflows, and with the sign of z
-__device__ inline double rotation_tangent(double num, double den) {
-  const double an = fabs(num), ad = fabs(den), s = inv_est(fmax(an, ad));
-  const double a = an * s, b = ad * s;
-  const double t = b * inv_est(a + __builtin_amdgcn_sqrt(__builtin_fma(a, a, b * b)));
-  return (num >= 0) == (den > 0) || num == 0 ? t : -t;
+// the magnitude's leading bits with the row in the low five, rows already used last
+__device__ inline unsigned pivot_key(double v, int row, bool used) {
+  const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32);
+  return used ? 0u : 0x80000000u | (hi & 0x7FFFFFE0u) | (unsigned)row;
 }
 
-// One wave: the last stage of the fixed-order reduction of the partial rows (row stride ld),
-// then the polar factor of B (the n x n block of the sums after A) by one-sided Jacobi
-// rotations (n <= 8: four disjoint column pairs at a time in round-robin order; larger n: lane x
-// holds row x, pairs in cyclic row order as the oracle), and the new dictionary D = U V^T with
-// its compute-type copy and Gram matrix.  A rank-deficient B
-// leaves the dictionary unchanged and sets the singular status.
+// Polar factor of the n x n matrix W (column-major, LDS) by Newton's iteration
+// X <- (mu X + X^-T / mu) / 2, mu = sqrt(|X^-1|_F / |X|_F) (Higham), each inverse by Gauss-Jordan in
+// place with row pivoting.  False, W unchanged, where |X|_F |X^-1|_F exceeds 1e6 or the iteration does
+// not settle: the caller then takes the singular values themselves.  R: n x n scratch, buf: 64 doubles,
+// perm: 64 ints.  What bounds it: the chain of one wave, about 200 cycles a pivot at n <= 8, where
+// entry (i, j) of X stays in lane i + 8 j and rows and columns are broadcast by lane permutes.  Five to
+// seven inverses replace about 45 rounds of Jacobi rotations: 128,000 signals, n = 8: 23 -> 15 us a launch.
+constexpr double kPolarCond = 1e6, kPolarDone = 2e-16;  // the last step's change squared: error below 1e-16
+__device__ inline bool polar_newton8(double* W, int n) {
+  const int x = threadIdx.x, i = x % 8, j = x / 8;
+  const bool in = i < n && j < n;
+  const double eye = i == j ? 1.0 : 0.0;
+  double X = in ? W[i + n * j] : 0.0;
+  const double f = wave_sum(X * X);
+  if (!(f > 0.0) || !(f < 1e300) || !(f > 1e-300)) return false;
+  X = in ? X * (sqrt((double)n) / sqrt(f)) : eye;  // lanes beyond n x n hold the identity throughout
+  bool scaled = true;
+  for (int it = 0; it < 24; ++it) {
+    double R = X;
+    unsigned used = 0xFFu & ~((1u << n) - 1u), prow = 0x76543210u, pinv = 0x76543210u;
+    for (int k = 0; k < n; ++k) {
+      const double c = __shfl(R, i + 8 * k, kWave);
+      unsigned key = pivot_key(c, i, (used >> i) & 1u);
+      key = max(key, (unsigned)dpp_int<kDppX1>((int)key));
+      key = max(key, (unsigned)dpp_int<kDppX2>((int)key));
+      key = max(key, (unsigned)dpp_int<kDppHalfMirror>((int)key));
+      const int p = __builtin_amdgcn_readfirstlane((int)(key & 7u));
+      const double pv = lane_value(R, p + 8 * k);
+      if (!(fabs(pv) > 1e-200)) return false;
+      const double rp = reciprocal(pv), row = __shfl(R, p + 8 * j, kWave) * rp;
+      used |= 1u << p;
+      prow = (prow & ~(15u << (4 * k))) | ((unsigned)p << (4 * k));
+      pinv = (pinv & ~(15u << (4 * p))) | ((unsigned)k << (4 * p));
+      const double v = j == k ? -c * rp : __builtin_fma(-c, row, R);
+      const double w = j == k ? rp : row;
+      R = i == p ? w : v;
+    }
+    // row p_k of R is row k of the inverse, its column l belongs to row p_l of X
+    const double Y = __shfl(R, (int)((prow >> (4 * j)) & 7u) + 8 * (int)((pinv >> (4 * i)) & 7u), kWave);
+    const double fx = wave_sum(in ? X * X : 0.0), fy = wave_sum(in ? Y * Y : 0.0);
+    if (!(fx * fy <= kPolarCond * kPolarCond)) return false;
+    const double mu = scaled ? sqrt(sqrt(fy / fx)) : 1.0;
+    const double Z = in ? 0.5 * (mu * X + Y * reciprocal(mu)) : eye;
+    const double d = wave_sum((Z - X) * (Z - X));
+    X = Z;
+    if (d <= kPolarDone) {
+      if (in) W[i + n * j] = X;
+      wave_sync();
+      return true;
+    }
+    scaled = d > 1e-2;
+  }
+  return false;
+}
+__device__ inline bool polar_newton(double* W, double* R, double* X, double* buf, int* perm, int n) {
+  const int x = threadIdx.x, nent = n * n;
+  double f = 0.0;
+  for (int e = x; e < nent; e += kWave) f += W[e] * W[e];
+  f = wave_sum(f);
+  if (!(f > 0.0) || !(f < 1e300) || !(f > 1e-300)) return false;
+  const double f1 = sqrt((double)n) / sqrt(f);
+  for (int e = x; e < nent; e += kWave) X[e] = W[e] * f1;
+  wave_sync();
+  const int di = kWave % n, dj = kWave / n;
+  double *col = buf, *row = buf + 32;
+  int *prow = perm, *pinv = perm + 32;
+  bool scaled = true;
+  for (int it = 0; it < 24; ++it) {
+    for (int e = x; e < nent; e += kWave) R[e] = X[e];
+    bool used = x >= n;
+    wave_sync();
+    for (int k = 0; k < n; ++k) {
+      const double c = x < n ? R[x + n * k] : 0.0;
+      unsigned key = pivot_key(c, x, used);
+      key = max(key, (unsigned)dpp_int<kDppX1>((int)key));
+      key = max(key, (unsigned)dpp_int<kDppX2>((int)key));
+      key = max(key, (unsigned)dpp_int<kDppHalfMirror>((int)key));
+      key = max(key, (unsigned)dpp_int<kDppMirror>((int)key));
+      const int p = (int)(max((unsigned)__builtin_amdgcn_readlane((int)key, 0),
+                              (unsigned)__builtin_amdgcn_readlane((int)key, 16)) & 31u);
+      const double pv = lane_value(c, p);
+      if (!(fabs(pv) > 1e-200)) return false;
+      const double rp = reciprocal(pv);
+      if (x < n) {
+        col[x] = c;
+        row[x] = R[p + n * x] * rp;
+      }
+      if (x == 0) {
+        prow[k] = p;
+        pinv[p] = k;
+      }
+      used = used || x == p;
+      wave_sync();
+      int i = x % n, j = x / n;
+      for (int e = x; e < nent; e += kWave) {
+        const double ci = col[i], rj = row[j], r = R[e];
+        const double v = j == k ? -ci * rp : __builtin_fma(-ci, rj, r);
+        const double w = j == k ? rp : rj;
+        R[e] = i == p ? w : v;
+        i += di;
+        j += dj;
+        if (i >= n) {
+          i -= n;
+          ++j;
+        }
+      }
+      wave_sync();
+    }
+    double fx = 0.0, fy = 0.0;
+    for (int e = x; e < nent; e += kWave) {
+      fx += X[e] * X[e];
+      fy += R[e] * R[e];
+    }
+    fx = wave_sum(fx);
+    fy = wave_sum(fy);
+    if (!(fx * fy <= kPolarCond * kPolarCond)) return false;
+    const double mu = scaled ? sqrt(sqrt(fy / fx)) : 1.0, rmu = reciprocal(mu);
+    double d = 0.0;
+    for (int e = x; e < nent; e += kWave) {
+      const double v = X[e], z = 0.5 * (mu * v + R[prow[e / n] + n * pinv[e % n]] * rmu);
+      d += (z - v) * (z - v);
+      X[e] = z;
+    }
+    d = wave_sum(d);
+    wave_sync();
+    if (d <= kPolarDone) {
+      for (int e = x; e < nent; e += kWave) W[e] = X[e];
+      wave_sync();
+      return true;
+    }
+    scaled = d > 1e-2;
+  }
+  return false;
+}
+
+// One wave: the last stage of the fixed-order reduction of the partial rows (row stride ld), then
+// the polar factor of B (the n x n block of the sums after A), which is the new dictionary, with its
+// compute-type copy and Gram matrix.  Newton's iteration gives it directly; where B is too far from
+// well conditioned for that, one-sided Jacobi rotations (lane x holds row x, pairs in cyclic row order
+// as the oracle) give the singular vectors and values, D = U V^T, and a rank-deficient B leaves the
+// dictionary unchanged and sets the singular status.
 template <typename T>
 __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restrict__ src, int nrow, int ld, int n,
                                                            double* D, T* Dc, T* Gc, int* status,
@@ -220,6 +350,8 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
   __shared__ double W[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];  // column-major n x n
   __shared__ double V[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];
   __shared__ double Dn[SDL_ORTHO_MAX_N * SDL_ORTHO_MAX_N];
+  __shared__ double buf[64];
+  __shared__ int perm[64];
   __shared__ double sig[SDL_ORTHO_MAX_N];
   const int x = threadIdx.x;
   const int nent = n * n;
@@ -236,7 +368,6 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     }
     for (; b < nrow; ++b) v += src[(size_t)b * ld + nent + e];
     W[e] = v;
-    V[e] = (e % n) == (e / n) ? 1.0 : 0.0;
   }
   if (ro.trace) {
     // the RMSE of the sweep that wrote the rows, from their residual sums
@@ -252,67 +383,11 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
   }
   wave_sync();
   const bool row = x < n;
-  if (n <= 8) {
-    // Up to four disjoint column pairs rotated at once (round-robin order: n' - 1 rounds of n' / 2
-    // pairs cover every pair once per sweep, n' = n rounded up to even, pairs with the dummy
-    // column n skipped); lane 8 q + r holds row r for the q-th pair of the round.  The polar
-    // factor is unique for a full-rank B, so the order of the rotations changes only rounding.
-    const int np = n + (n & 1), q = x / 8, r = x % 8;
+  const bool direct = n <= 8 ? polar_newton8(W, n) : polar_newton(W, V, Dn, buf, perm, n);
+  if (!direct) {
+    for (int e = x; e < nent; e += kWave) V[e] = (e % n) == (e / n) ? 1.0 : 0.0;
+    wave_sync();
     for (int sweep = 0; sweep < 60; ++sweep) {
-      bool rotated = false;
-      // the q-th pair of a round: columns round + q and round - q (mod np - 1), stepped by one a round;
-      // pair 0 is the last column with column `round`
-      int up = q, down = q == 0 ? 0 : np - 1 - q;
-      for (int round = 0; round < np - 1; ++round) {
-        int i = -1, j = -1;
-        if (q < np / 2) {
-          i = q == 0 ? np - 1 : up;
-          j = down;
-          if (i > j) { const int tmp = i; i = j; j = tmp; }
-        }
-        up = up + 1 == np - 1 ? 0 : up + 1;
-        down = down + 1 == np - 1 ? 0 : down + 1;
-        const bool act = j >= 0 && j < n;  // a real pair (the dummy column is n)
-        double pa = 0.0, pb = 0.0, pg = 0.0, wi = 0.0, wj = 0.0, vi = 0.0, vj = 0.0;
-        if (act && r < n) {
-          wi = W[r + n * i];
-          wj = W[r + n * j];
-          vi = V[r + n * i];
-          vj = V[r + n * j];
-          pa = wi * wi;
-          pb = wj * wj;
-          pg = wi * wj;
-        }
-        // sums over the pair's eight lanes (quad swaps and the half-row mirror)
-        pa += dpp_move<kDppX1>(pa);
-        pb += dpp_move<kDppX1>(pb);
-        pg += dpp_move<kDppX1>(pg);
-        pa += dpp_move<kDppX2>(pa);
-        pb += dpp_move<kDppX2>(pb);
-        pg += dpp_move<kDppX2>(pg);
-        pa += dpp_move<kDppHalfMirror>(pa);
-        pb += dpp_move<kDppHalfMirror>(pb);
-        pg += dpp_move<kDppHalfMirror>(pg);
-        // Where the rotation's tangent is rounded does not matter as long as c^2 + s^2 = 1: the
-        // hardware's estimates with one correction give it (the chain of full divisions and square
-        // roots was most of a round), and c comes at full precision
-        const bool rot = act && !(fabs(pg) <= 1e-15 * __builtin_amdgcn_sqrt(pa * pb) || pg == 0.0);
-        if (rot) {
-          const double t = rotation_tangent(pb - pa, 2.0 * pg);
-          const double c = inv_sqrt(1.0 + t * t), sn = c * t;
-          if (r < n) {
-            W[r + n * i] = c * wi - sn * wj;
-            W[r + n * j] = sn * wi + c * wj;
-            V[r + n * i] = c * vi - sn * vj;
-            V[r + n * j] = sn * vi + c * vj;
-          }
-        }
-        rotated = rotated || rot;
-        wave_sync();
-      }
-      if (__ballot(rotated) == 0ull) break;
-    }
-  } else for (int sweep = 0; sweep < 60; ++sweep) {
     int rotated = 0;
     for (int i = 0; i < n - 1; ++i)
       for (int j = i + 1; j < n; ++j) {
@@ -366,16 +441,18 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     }
     return;
   }
-  // D[r][c] = sum_i (W[r][i] / sigma_i) V[c][i] and the Gram matrix, one entry per lane and pass (one
-  // row per lane, with a division per term, took 8 of 28 us at n = 8)
+  }
+  // D (D[r][c] = sum_i (W[r][i] / sigma_i) V[c][i] after the rotations) and its Gram matrix, one entry
+  // per lane and pass
   wave_sync();
-  if (row) sig[x] = 1.0 / sig[x];
+  if (!direct && row) sig[x] = 1.0 / sig[x];
   wave_sync();
   for (int e = x; e < nent; e += kWave) {
     const int r = e % n, c = e / n;
-    double v = 0.0;
+    double v = direct ? W[e] : 0.0;
+    if (!direct)
 #pragma unroll 4
-    for (int i = 0; i < n; ++i) v += (W[r + n * i] * sig[i]) * V[c + n * i];
+      for (int i = 0; i < n; ++i) v += (W[r + n * i] * sig[i]) * V[c + n * i];
     Dn[e] = v;
     D[e] = v;
     Dc[e] = (T)v;

@@ -311,3 +311,33 @@ def test_learn_side_by_side_equals_in_order(shared, rng):
     for a, b in zip(outs[0][1], outs[1][1]):
         for u, v in zip(a, b):
             np.testing.assert_array_equal(u, v)
+
+
+# ---- Procrustes updates: sizes around the eight-lane form and the largest, B from well conditioned
+# (Newton's iteration) to beyond what it takes (Jacobi rotations).  B differs by rounding, 1e-15 n of its
+# norm, which moves the polar factor by up to the condition number times that: ten times as much is allowed
+
+@pytest.mark.parametrize("power", [0, 3, 8])
+@pytest.mark.parametrize("m1,m2", [(1, 2), (7, 8), (9, 16), (17, 15), (31, 8), (8, 32)])
+def test_procrustes_sizes(m1, m2, power, rng):
+    N, s = 400, min(3, m1 * m2)
+    d1, d2 = (np.linalg.qr(rng.standard_normal((m, m)))[0] for m in (m1, m2))
+    t1, t2 = (np.linalg.qr(rng.standard_normal((m, m)))[0] for m in (m1, m2))
+    supp = np.argsort(rng.random((N, m1 * m2)), axis=1)[:, :s].astype(np.int32)
+    i, j = supp % m1, supp // m1
+    # energies of the atoms spread over 10^-power on each side, so B's singular values are too
+    coef = rng.choice([-1.0, 1.0], (N, s)) * 10.0 ** (-power / 2 * (i / max(1, m1 - 1) + j / max(1, m2 - 1)))
+    X = oracle.densify(supp, coef, m1, m2)
+    Y = np.einsum("pi,kij,qj->kpq", t1, X, t2)
+    for side in (1, 2):
+        pr = api.Problem.from_math(Y, d1, d2, s, dtype=torch.float64)
+        pr.supp.copy_(torch.from_numpy(supp))
+        pr.coef.copy_(torch.from_numpy(coef))
+        api.tmod_update(pr, sides=side, method=1)
+        torch.cuda.synchronize()
+        e = oracle.procrustes_update(side, Y, d1, d2, supp, coef)[side - 1]
+        B = sum(y @ d2 @ x.T if side == 1 else y.T @ d1 @ x for y, x in zip(Y, X))
+        g, kappa = (pr.d1(), pr.d2())[side - 1], np.linalg.cond(B)
+        print(m1, m2, side, "cond %.1e, diff %.1e" % (kappa, np.abs(g - e).max()))
+        assert np.abs(g - e).max() <= 1e-14 * len(B) * kappa
+        np.testing.assert_allclose(g.T @ g, np.eye(len(B)), atol=1e-12)
