@@ -532,11 +532,14 @@ TmodArgs<T> tmod_args(int side, const sdl_problem& r, const PBuf& b, const Plan&
 }
 
 // one TMOD half-step from the codes in supp/coef: standalone sums -> reduce -> solve (+ rescale)
-// Standalone sums of one side into b.part; returns the number of partial rows.  SDL_MIXED_BF16
-// runs them on the BF16 matrix cores where that kernel is compiled for the shape.
+// Standalone sums of one side (and with_res2 the residual sum) into b.part; returns the number of
+// partial rows.  SDL_MIXED_BF16 runs them on the BF16 matrix cores where that kernel is compiled for
+// the shape.
 template <typename T>
-int run_sums(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, const Opt& o, Launcher& L, int* rows) {
-  const TmodArgs<T> a = tmod_args<T>(side, r, b, pl);
+int run_sums(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, const Opt& o, bool with_res2, Launcher& L,
+             int* rows) {
+  TmodArgs<T> a = tmod_args<T>(side, r, b, pl);
+  if (with_res2) a.res2 = (const T*)r.res2;
   bool bf16 = false;
   if constexpr (sizeof(T) == 4) bf16 = o.prec == SDL_MIXED_BF16 && tmod_sums_bf16_supported(r.m1, r.m2, r.n1, r.n2, r.s);
   if (bf16) {
@@ -557,11 +560,13 @@ int run_sums(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, cons
   return L.end();
 }
 
+// (rmse_q >= 0: also the RMSE of the codes' sweep, for problem rmse_q's trace of K + 1 entries)
 template <typename T>
-int run_update(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, const Opt& o, bool rescale, Launcher& L) {
+int run_update(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, const Opt& o, bool rescale, int rmse_q,
+               int K, Launcher& L) {
   int nblk = 0;
-  SDL_TRY(run_sums<T>(side, r, b, pl, o, L, &nblk));
-  SDL_TRY(run_reduce_solve<T>(side, r, b, pl, nblk, false, -1, 0, L, o.method));
+  SDL_TRY(run_sums<T>(side, r, b, pl, o, rmse_q >= 0, L, &nblk));
+  SDL_TRY(run_reduce_solve<T>(side, r, b, pl, nblk, rmse_q >= 0, rmse_q, K, L, o.method));
   if (rescale && o.method == 0) {
     SDL_TRY(L.begin(6));
     HIP_TRY(launch_rescale<T>(side, r.n1, r.s, r.N, r.supp, (T*)r.coef, b.w, L.st));
@@ -727,8 +732,8 @@ int tmod_update_impl(sdl_problem* p, int nprob, uint32_t sides, const Opt& o, hi
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
   for (int q = 0; q < nprob; ++q) {
-    if (sides & 1u) SDL_TRY(run_update<T>(1, p[q], pl.pb[q], pl, o, true, L));
-    if (sides & 2u) SDL_TRY(run_update<T>(2, p[q], pl.pb[q], pl, o, true, L));
+    if (sides & 1u) SDL_TRY(run_update<T>(1, p[q], pl.pb[q], pl, o, true, -1, 0, L));
+    if (sides & 2u) SDL_TRY(run_update<T>(2, p[q], pl.pb[q], pl, o, true, -1, 0, L));
   }
   return finish_call(st, ctx, pl, o, marks, true);
 }
@@ -774,12 +779,11 @@ int sparse_code_sums_impl(const sdl_problem* p, int side, double* sums, const Op
   } else {
     SDL_TRY(run_omp<T>(r, b, o, pl, 0, L));
     int nblk = 0;
-    SDL_TRY(run_sums<T>(side, r, b, pl, o, L, &nblk));
+    SDL_TRY(run_sums<T>(side, r, b, pl, o, true, L, &nblk));
     SDL_TRY(L.begin(2));
-    const int nrow = launch_reduce_stage1(b.part, nblk, nent, b.stage, &src, st, &e);
+    const int nrow = launch_reduce_stage1(b.part, nblk, nent + 1, b.stage, &src, st, &e);
     HIP_TRY(e);
-    HIP_TRY(launch_reduce_final(src, nrow, nent, nent, sums, st));
-    HIP_TRY(launch_sum_res2<T>((const T*)r.res2, r.N, b.rpart, b.rblk, pl.done, sums + nent, st));
+    HIP_TRY(launch_reduce_final(src, nrow, nent + 1, nent + 1, sums, st));
     SDL_TRY(L.end());
   }
   return finish_call(st, ctx, pl, o, marks, false);
@@ -821,10 +825,9 @@ int iterate_problem(sdl_problem* p, int q, int K, const Opt& o, const Plan& pl, 
     const PBuf& b = pl.pb[q];
     if (o.proposer) {
       SDL_TRY(run_code<T>(r, b, o, pl, L));
-      SDL_TRY(run_rmse<T>(r, b, pl, q, K, L));
-      SDL_TRY(run_update<T>(1, r, b, pl, o, false, L));
+      SDL_TRY(run_update<T>(1, r, b, pl, o, false, q, K, L));
       SDL_TRY(run_code<T>(r, b, o, pl, L));
-      SDL_TRY(run_update<T>(2, r, b, pl, o, false, L));
+      SDL_TRY(run_update<T>(2, r, b, pl, o, false, -1, K, L));
     } else if (o.schedule == 0 && use_fast<T>(r, o)) {
       // Algorithm 1 with the sums (and the RMSE) computed in the sparse-coding epilogue
       const int rows = omp_fast_partial_rows(r.N, r.m1, r.m2, r.n1, r.n2, r.s);
@@ -842,14 +845,13 @@ int iterate_problem(sdl_problem* p, int q, int K, const Opt& o, const Plan& pl, 
       SDL_TRY(run_reduce_solve<T>(2, r, b, pl, rows, true, -1, K, L, 1));
     } else {
       SDL_TRY(run_omp<T>(r, b, o, pl, 0, L));
-      SDL_TRY(run_rmse<T>(r, b, pl, q, K, L));
       if (o.schedule == 0) {
-        SDL_TRY(run_update<T>(1, r, b, pl, o, false, L));
+        SDL_TRY(run_update<T>(1, r, b, pl, o, false, q, K, L));
         SDL_TRY(run_omp<T>(r, b, o, pl, 0, L));
-        SDL_TRY(run_update<T>(2, r, b, pl, o, false, L));
+        SDL_TRY(run_update<T>(2, r, b, pl, o, false, -1, K, L));
       } else {
-        SDL_TRY(run_update<T>(2, r, b, pl, o, true, L));
-        SDL_TRY(run_update<T>(1, r, b, pl, o, false, L));
+        SDL_TRY(run_update<T>(2, r, b, pl, o, true, q, K, L));
+        SDL_TRY(run_update<T>(1, r, b, pl, o, false, -1, K, L));
       }
     }
   }

@@ -67,7 +67,21 @@ struct TmodArgs {
   const T* Dother;  // compute-type copy of the dictionary that stays fixed
   const int32_t* supp;
   const T* coef;
+  const T* res2 = nullptr;  // non-null: each partial row ends with the sum of its signals' residual energies
 };
+
+// Sum of the residual energies of signals [k0, k1) that this wave's threads take (in every lane, in
+// scalar registers), each workgroup's threads striding over them.
+template <typename T>
+__device__ inline double wave_res2(const T* res2, int64_t k0, int64_t k1) {
+  double v = 0.0;
+  for (int64_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) v += (double)res2[k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll)), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
 
 // bfloat16 bit pattern -> FP32 (exact: the pattern is the upper half of the FP32 encoding)
 __device__ inline float bf16_to_float(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -178,10 +192,6 @@ int launch_reduce_stage1(const double* part, int P, int ld, double* stage, const
 int reduce_stage_rows(int P);
 // The last stage alone: out[e] = row-order sum of the nrow rows at src (stride ld), e < n.
 hipError_t launch_reduce_final(const double* src, int nrow, int ld, int n, double* out, hipStream_t st);
-// *out = sum of res2[0 .. N-1] in a fixed order (nblk = rmse_num_blocks(N) partials in part;
-// *done: zero, left zero).
-template <typename T>
-hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, int* done, double* out, hipStream_t st);
 hipError_t launch_fill_double(double* p, int n, double v, hipStream_t st);
 // Optional RMSE output of the solve kernel: trace[*counter + offset] = sqrt(sums[idx] / denom), then ++*counter.
 struct RmseOut {

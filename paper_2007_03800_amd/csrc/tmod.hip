@@ -176,13 +176,13 @@ __global__ void rescale_kernel(int side, int n1, int s, int64_t N, const int32_t
 constexpr int kRmseThreads = 256;
 
 // Sum of N squared residuals in a fixed order: each workgroup writes its slice's sum, the last one to
-// finish (a counter that it sets back to zero) adds the slices' sums and writes the total, or the
-// RMSE with the trace position moved on.  The slices' sums pass between workgroups by device-scope
+// finish (a counter that it sets back to zero) adds the slices' sums, writes the RMSE and moves the
+// trace position on.  (Sweeps that an update follows leave this to the update's sums.)  The slices' sums pass between workgroups by device-scope
 // atomics.  (A second launch whose single lane walked the slices took 4-15 us.)
 template <typename T>
 __global__ void __launch_bounds__(kRmseThreads)
-    res2_sum_kernel(const T* res2, int64_t N, double* part, int* done, double* out, double denom, double* trace, int stride,
-                    int offset, int* counter) {
+    res2_sum_kernel(const T* res2, int64_t N, double* part, int* done, double denom, double* trace, int stride, int offset,
+                    int* counter) {
   __shared__ double red[kRmseThreads];
   __shared__ int last;
   const int nblk = gridDim.x, tid = threadIdx.x;
@@ -210,12 +210,9 @@ __global__ void __launch_bounds__(kRmseThreads)
   block_sum(v);
   if (tid == 0) {
     *done = 0;
-    if (out) *out = red[0];
-    if (trace) {
-      const int it = *counter;
-      trace[(size_t)it * stride + offset] = denom > 0 ? sqrt(red[0] / denom) : 0.0;
-      *counter = it + 1;
-    }
+    const int it = *counter;
+    trace[(size_t)it * stride + offset] = denom > 0 ? sqrt(red[0] / denom) : 0.0;
+    *counter = it + 1;
   }
 }
 
@@ -348,15 +345,8 @@ int rmse_num_blocks(int64_t N) {
 template <typename T>
 hipError_t launch_rmse(const T* res2, int64_t N, double denom, double* part, int nblk, int* done, double* trace,
                        int stride, int offset, int* counter, hipStream_t st) {
-  hipLaunchKernelGGL(res2_sum_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, part, done, nullptr, denom, trace,
+  hipLaunchKernelGGL(res2_sum_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, part, done, denom, trace,
                      stride, offset, counter);
-  return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_sum_res2(const T* res2, int64_t N, double* part, int nblk, int* done, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(res2_sum_kernel<T>, dim3(nblk), dim3(kRmseThreads), 0, st, res2, N, part, done, out, 0.0, nullptr, 0, 0,
-                     nullptr);
   return hipGetLastError();
 }
 
@@ -385,8 +375,7 @@ hipError_t launch_check_finite_bf16(const uint16_t* x, int64_t n, int* status, h
                                         hipStream_t);                                                         \
   template hipError_t launch_rmse<T>(const T*, int64_t, double, double*, int, int*, double*, int, int, int*,  \
                                      hipStream_t);                                                            \
-  template hipError_t launch_check_finite<T>(const T*, int64_t, int*, hipStream_t);                          \
-  template hipError_t launch_sum_res2<T>(const T*, int64_t, double*, int, int*, double*, hipStream_t);
+  template hipError_t launch_check_finite<T>(const T*, int64_t, int*, hipStream_t);
 SDL_INST(float)
 SDL_INST(double)
 #undef SDL_INST

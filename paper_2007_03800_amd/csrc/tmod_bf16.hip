@@ -84,6 +84,7 @@ __global__ void __launch_bounds__(kWave* kBWaves) tmod_sums_bf16_kernel(TmodArgs
   __syncthreads();
   const int64_t k0 = (a.N * blockIdx.x) / nblk, k1 = (a.N * (blockIdx.x + 1)) / nblk;
   const int64_t nbatch = (k1 - k0 + bs - 1) / bs;
+  const double res2 = a.res2 ? wave_res2(a.res2, k0, k1) : 0.0;
 
   f32x4 accP[TP][TP], accR[TR][TP];
 #pragma unroll
@@ -168,7 +169,7 @@ __global__ void __launch_bounds__(kWave* kBWaves) tmod_sums_bf16_kernel(TmodArgs
 
   // fixed-order reduction of the four waves' tiles, then one FP64 partial per workgroup
   __syncthreads();
-  const int nent = na * na + mr * na;
+  const int nent = na * na + mr * na, ld = nent + (a.res2 ? 1 : 0);
   float* red = reinterpret_cast<float*>(smem_raw);  // [kBWaves][nent]
   {
     const int col = lane % 16;
@@ -199,7 +200,14 @@ __global__ void __launch_bounds__(kWave* kBWaves) tmod_sums_bf16_kernel(TmodArgs
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < kBWaves; ++q) v += (double)red[q * nent + e];
-    part[(size_t)blockIdx.x * nent + e] = v;
+    part[(size_t)blockIdx.x * ld + e] = v;
+  }
+  if (a.res2) {
+    __syncthreads();
+    double* rs = reinterpret_cast<double*>(smem_raw);
+    if (lane == 0) rs[w] = res2;
+    __syncthreads();
+    if (tid == 0) part[(size_t)blockIdx.x * ld + nent] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
   }
 }
 

@@ -75,6 +75,8 @@ __global__ void __launch_bounds__(kWave* kWaves) tmod_sums_kernel(TmodArgs<T> a,
   __syncthreads();
   const int64_t k0 = (a.N * blockIdx.x) / nblk, k1 = (a.N * (blockIdx.x + 1)) / nblk;
   const int64_t nbatch = (k1 - k0 + bs - 1) / bs;
+  // (a launch of its own for the residual sum took 5 us of each iteration of 2,000 FP64 signals' 72)
+  const double res2 = a.res2 ? wave_res2(a.res2, k0, k1) : 0.0;
 
   V accP[TP][TP], accR[TR][TP];
 #pragma unroll
@@ -144,7 +146,7 @@ __global__ void __launch_bounds__(kWave* kWaves) tmod_sums_kernel(TmodArgs<T> a,
 
   // fixed-order reduction of the four waves' tiles, then one FP64 partial per workgroup
   __syncthreads();
-  const int nent = na * na + mr * na;
+  const int nent = na * na + mr * na, ld = nent + (a.res2 ? 1 : 0);
   T* red = smem;  // [kWaves][nent]
   {
     const int col = lane % 16;
@@ -175,7 +177,14 @@ __global__ void __launch_bounds__(kWave* kWaves) tmod_sums_kernel(TmodArgs<T> a,
     double v = 0.0;
 #pragma unroll
     for (int q = 0; q < kWaves; ++q) v += (double)red[q * nent + e];
-    part[(size_t)blockIdx.x * nent + e] = v;
+    part[(size_t)blockIdx.x * ld + e] = v;
+  }
+  if (a.res2) {
+    __syncthreads();
+    double* rs = reinterpret_cast<double*>(smem_raw);
+    if (lane == 0) rs[w] = res2;
+    __syncthreads();
+    if (tid == 0) part[(size_t)blockIdx.x * ld + nent] = (rs[0] + rs[1]) + (rs[2] + rs[3]);
   }
 }
 
