@@ -433,7 +433,12 @@ struct MLay {
   static constexpr bool PK = C::S >= 24;             // packed copies of L^{-1}
   // waves per SIMD the registers must allow: with packed copies LDS allows 6, and the
   // compiler's own choice lands one register above that (12 bytes per lane spill instead)
-  static constexpr int MINW = PK ? 6 : 1;
+  // waves per workgroup: from 512 pixels on the tables (27 KB at 48 x 36 atoms) and a wave's buffer
+  // (9 KB) leave room for two workgroups of four a CU, but for twelve waves that share one copy, three
+  // on every SIMD (20,000 signals alone: 614 -> 570 us; five a workgroup load the SIMDs unevenly)
+  static constexpr bool BIG = C::M >= 512;
+  static constexpr int WPB = BIG ? 12 : C::WPB;
+  static constexpr int MINW = PK ? 6 : BIG ? 3 : 1;
   static constexpr int LPK = PK ? 8 * C4 * (C4 + 1) : C::S * SP;  // one copy (rows or columns)
   static constexpr int SCR = 2 * LPK + 5 * SP;       // L^{-1} by rows and by columns, gam, supi, supj, g, w
   static constexpr int UNI = ((WSM > SCR ? WSM : SCR) + 3) / 4 * 4;  // W staging aliases the scratch
@@ -575,7 +580,7 @@ __device__ inline bool append_atom_sq(int t, int lane, int ia, int ja, float bs,
 }
 
 template <class C>
-__global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per_eu(MLay<C>::MINW)))
+__global__ void __launch_bounds__(kWave* MLay<C>::WPB) __attribute__((amdgpu_waves_per_eu(MLay<C>::MINW)))
     omp_wave_mfma_kernel(OmpArgs<float> a) {
   using L = MLay<C>;
   constexpr int M1 = C::M1, M2 = C::M2, N1 = C::N1, N2 = C::N2, S = C::S, M = C::M, SP = C::SP;
@@ -584,7 +589,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
   __shared__ __align__(16) float sD2T[P2 * M2];  // D2[q, j] at j + P2 q, zero for j >= n2
   __shared__ __align__(16) float sG1P[P1 * N1];  // G1[i, ik] at i + P1 ik, zero for i >= n1
   __shared__ __align__(16) float sG2P[P2 * N2];  // G2[jk, j] at j + P2 jk, zero for j >= n2
-  __shared__ __align__(16) float sW[C::WPB][L::PW];
+  __shared__ __align__(16) float sW[L::WPB][L::PW];
 
   const int tid = threadIdx.x, wv = tid / kWave, lane = tid % kWave;
   const int r16 = lane % 16, k4 = lane / 16;
@@ -628,7 +633,7 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
 
   unsigned n_early = 0;  // early-stopped signals of this wave (lane 0), counted once at the end
   int tprev = S;         // atoms of the signal before (the scratch starts out unknown)
-  for (int64_t k = (int64_t)blockIdx.x * C::WPB + wv; k < a.N; k += (int64_t)gridDim.x * C::WPB) {
+  for (int64_t k = (int64_t)blockIdx.x * L::WPB + wv; k < a.N; k += (int64_t)gridDim.x * L::WPB) {
     float yy = 0.f;
     for (int e = lane; e < M; e += kWave) {
       const float v = a.Yh ? bf16_to_float(a.Yh[k * M + e]) : a.Y[k * M + e];
@@ -838,12 +843,12 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
     wave_sync();
   }
   // one atomic per workgroup: atomics on one address from every wave serialise
-  __shared__ unsigned sEarly[C::WPB];
+  __shared__ unsigned sEarly[L::WPB];
   if (lane == 0) sEarly[wv] = n_early;
   __syncthreads();
   if (tid == 0) {
     unsigned tot = 0;
-    for (int w = 0; w < C::WPB; ++w) tot += sEarly[w];
+    for (int w = 0; w < L::WPB; ++w) tot += sEarly[w];
     if (tot) atomicAdd(&a.counters[kCtrEarlyStop], (unsigned long long)tot);
   }
 }
@@ -852,10 +857,11 @@ __global__ void __launch_bounds__(kWave* C::WPB) __attribute__((amdgpu_waves_per
 // static striding leaves waves idle at the end).
 template <typename T, class C>
 hipError_t launch_wcfg(const OmpArgs<T>& a, hipStream_t st) {
-  int64_t blocks = (a.N + C::WPB - 1) / C::WPB;
+  constexpr int wpb = sizeof(T) == 4 && C::MF ? MLay<C>::WPB : C::WPB;
+  int64_t blocks = (a.N + wpb - 1) / wpb;
   if (blocks > kWaveMaxBlocks) blocks = kWaveMaxBlocks;
   if constexpr (sizeof(T) == 4 && C::MF)
-    hipLaunchKernelGGL((omp_wave_mfma_kernel<C>), dim3((unsigned)blocks), dim3(kWave * C::WPB), 0, st, a);
+    hipLaunchKernelGGL((omp_wave_mfma_kernel<C>), dim3((unsigned)blocks), dim3(kWave * wpb), 0, st, a);
   else
     hipLaunchKernelGGL((omp_wave_kernel<T, C>), dim3((unsigned)blocks), dim3(kWave * C::WPB), 0, st, a);
   return hipGetLastError();
