@@ -158,7 +158,7 @@ def learned_vs_plain(args, api, oracle, synth):
             pr.D2.copy_(D2)
             api.learn(pr, K, **kw)
 
-        run()  # warm-up (captures the learning graph)
+        run()  # warm-up
         dt, _, _ = timed_runs(run, 3)
         s_o, _, r_o = oracle.omp(Ysub, pr.d1(), pr.d2(), w.s, p=min(16, os.cpu_count() or 1))
         r_g = pr.res2[:nsub].double().cpu().numpy()
@@ -193,9 +193,8 @@ def device_signals(synth, w, dtype, k0=0, k1=None, chunk=100_000):
 
 
 def timed_learn(api, fresh, K, reps=3, **opts):
-    """Autotune, one untimed run of K iterations (it also captures the learning graph), then the
-    median of reps timed runs of K graph-replayed iterations of Algorithm 1, each from the initial
-    dictionaries on the same buffers; returns (problems, trace, seconds)."""
+    """Autotune, one untimed run of K iterations (a warm-up), then the median of reps timed runs
+    of K iterations of Algorithm 1, each from the initial dictionaries on the same buffers; returns (problems, trace, seconds)."""
     import torch
     api.autotune(fresh(), reps=3)
     probs = fresh()
@@ -580,8 +579,7 @@ def main():
     if args.warmup > 0:
         api.learn(pr, args.warmup)
     torch.cuda.synchronize()
-    # the timed problem keeps its buffers across runs (the library replays the learning graph it
-    # captured for them); each run starts again from the initial dictionaries
+    # the timed problem keeps its buffers across runs; each run starts again from the initial dictionaries
     D1_0, D2_0 = pr.D1.clone(), pr.D2.clone()
     traces = []
 
@@ -590,7 +588,7 @@ def main():
         pr.D2.copy_(D2_0)
         traces.append(api.learn(pr, args.steps)[0])
 
-    run()  # captures the graph for K = steps (not timed)
+    run()  # warm-up for K = steps (not timed)
     elapsed, elapsed_ev, all_runs = timed_runs(run, args.runs)
     trace = traces[-1]
     value = w.N * args.steps / elapsed

@@ -64,7 +64,6 @@ struct sdl_proposer {
   float* Dc2 = nullptr;
   float* G1c = nullptr;
   float* G2c = nullptr;
-  double* G64 = nullptr;
   unsigned long long* ctr = nullptr;
 };
 
@@ -320,7 +319,7 @@ void sdl_proposer_destroy(sdl_proposer* P) {
   if (!P) return;
   void* bufs[] = {P->p, P->m, P->v, P->g, P->pc, P->X, P->Z1, P->H1, P->Z2, P->H2, P->Z3, P->Zl, P->part, P->dZ3, P->dZ2, P->dZ1,
                   P->loss_part, P->loss, P->idx, P->accept, P->list, P->blk, P->count, P->Dc1, P->Dc2, P->G1c,
-                  P->G2c, P->G64, P->ctr};
+                  P->G2c, P->ctr};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete P;
