@@ -633,7 +633,7 @@ int64_t mfma_partial_rows(int64_t N, int wpe) { return mfma_blocks(N, wpe); }
 // Remark 1's orthonormal variant on the same layout: first correlation on the matrix cores,
 // exact top-s selection, explicit residual, and the update sums in the epilogue (the B block
 // is what the Procrustes update reads).  (m1, m2, s, waves per SIMD); n1 = m1, n2 = m2.
-// Three waves per SIMD fit its registers (149) and, with the epilogue in two passes, its LDS:
+// Three waves per SIMD fit its registers (129) and, with the epilogue in two passes, its LDS:
 // 6% faster per orthonormal iteration than two.
 #define SDL_ORTHO_MFMA_VARIANTS(X) X(8, 8, 8, 3)
 
