@@ -346,6 +346,10 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
       }
       T bs;
       int code;
+      // At most two passes: a signal that goes on has a value above the threshold (at least 0), so an
+      // element was found, and once its support is masked no element found is in it.  The threshold
+      // has to come before the repeat: where every correlation left is exactly zero (a signal that fewer
+      // than s atoms represent exactly) the merge gives value 0 and code 0, masked or not.
       for (;;) {
         bs = 0;
         int be = 0;
@@ -362,6 +366,9 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
           }
         code = base_code + ((be / RI) << 8 | (be % RI));
         signal_argmax<C>(bs, code);
+        const bool small_corr = !(gabs(bs) > thr);
+        early |= active && small_corr;
+        active = active && !small_corr;
         // a chosen atom's correlation is zero up to rounding after the re-fit, so it comes up
         // again only when every correlation is at rounding level: only then is the support masked
         const bool again = active && ((__ballot(l < t && my_code == code) & gmask) != 0ull);
@@ -373,9 +380,6 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
           for (int e = 0; e < E; ++e) al[e] = again && ((e / RI) << 8 | (e % RI)) == cq ? T(__builtin_nanf("")) : al[e];
         }
       }
-      const bool small_corr = !(gabs(bs) > thr);
-      early |= active && small_corr;
-      active = active && !small_corr;
       if (__ballot(active) == 0ull) break;
       const int ia = code & 255, ja = code >> 8;
       const int off_a = (ia * ld1) | (ja * ld2) << 16;
