@@ -387,8 +387,9 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
       const T* g2a = sG2 + ja * ld2;
       const T a1 = g1a[ia], a2 = g2a[ja];
       const T gaa = a1 * a2;
-      // new Cholesky row: L w = G_{S,a}, lane k < t holding entry k
-      const int mc = l < t ? my_code : 0;
+      // new Cholesky row: L w = G_{S,a}, lane k < t holding entry k (a signal that stopped before the
+      // others of its wave has fewer than t atoms: its other lanes read atom 0's entry, which is not used)
+      const int mc = l < t && my_code >= 0 ? my_code : 0;
       T b = g1a[mc & 255] * g2a[mc >> 8], w = 0, ww = 0, v = 0;
       if constexpr (F64) {
         upward<C>(t, [&](auto q) __attribute__((always_inline)) { w = gfma(Lr[ls * ldl + q], from_lane<C>(b, q), w); });

@@ -67,6 +67,13 @@ def search(signals, thr):
                     s.masked[code & 255, code >> 8] = True
 
 
+def held(signal, l, t):
+    """The code whose Gram entry lane l of a signal reads while atom t is appended, in every signal of the
+    wave: the lane's own atom, atom 0 in a lane that holds none."""
+    code = signal.atoms[l] if l < len(signal.atoms) else -1
+    return code if l < t and code >= 0 else 0
+
+
 def code_wave(Y, d1, d2, s, grid, stop_rel=1e-14):
     """Codes of the signals that share a wave (at most 64 / lanes per signal of them)."""
     n1 = d1.shape[1]
@@ -75,6 +82,9 @@ def code_wave(Y, d1, d2, s, grid, stop_rel=1e-14):
     thr = [stop_rel * np.linalg.norm(y) for y in Y]
     for t in range(s):
         picks, _ = search(sig, thr)
+        for x, (_, code) in zip(sig, picks):  # every signal's lanes read the tables while one goes on
+            for c in [code] + [held(x, l, t) for l in range(grid[0] * grid[1])]:
+                assert 0 <= (c & 255) < n1 and 0 <= c >> 8 < d2.shape[1], "a table read out of range"
         for x, y, (bs, code), th in zip(sig, Y, picks, thr):
             x.active = x.active and abs(bs) > th
             if not x.active:
