@@ -463,6 +463,15 @@ PrepJob<T> prep_job(const double* D, int mr, int na, void* Dc, void* Gc) {
   return j;
 }
 
+// One problem's dictionaries prepared (again).
+template <typename T>
+int prepare(const sdl_problem& r, const PBuf& b, Launcher& L) {
+  const PrepJob<T> jobs[] = {prep_job<T>(r.D1, r.m1, r.n1, b.Dc1, b.G1c), prep_job<T>(r.D2, r.m2, r.n2, b.Dc2, b.G2c)};
+  SDL_TRY(L.begin(4));
+  HIP_TRY(launch_call_prep<T>(jobs, 2, nullptr, nullptr, 0, L.st));
+  return L.end();
+}
+
 // The start of a call, one launch: its status words and counters zeroed and the dictionaries of its
 // problems prepared (with skip_empty only those of problems with signals).
 template <typename T>
@@ -478,6 +487,27 @@ int start_call(const sdl_problem* p, int nprob, const Plan& pl, bool skip_empty,
   SDL_TRY(L.begin(4));
   HIP_TRY(launch_call_prep<T>(jobs.data(), (int)jobs.size(), zero, nzero, 4, L.st));
   return L.end();
+}
+
+// Whether [a, a + na) and [b, b + nb) have a byte in common.
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return a && b && (const char*)a < (const char*)b + nb && (const char*)b < (const char*)a + na;
+}
+
+// Whether an update of one of the problems before q writes memory of q's dictionaries (its dictionaries
+// and, in place, its codes' coefficients of elem bytes).
+bool dictionaries_rewritten(const sdl_problem* p, int q, size_t elem) {
+  const struct {
+    const double* D;
+    size_t bytes;
+  } mine[] = {{p[q].D1, sizeof(double) * p[q].m1 * p[q].n1}, {p[q].D2, sizeof(double) * p[q].m2 * p[q].n2}};
+  for (int e = 0; e < q; ++e)
+    for (const auto& d : mine)
+      if (overlap(d.D, d.bytes, p[e].D1, sizeof(double) * p[e].m1 * p[e].n1) ||
+          overlap(d.D, d.bytes, p[e].D2, sizeof(double) * p[e].m2 * p[e].n2) ||
+          overlap(d.D, d.bytes, p[e].coef, elem * (size_t)p[e].N * p[e].s))
+        return true;
+  return false;
 }
 
 // reduce the partial rows of one side's sums (plus the res2 entry when fused) and solve;
@@ -732,6 +762,8 @@ int tmod_update_impl(sdl_problem* p, int nprob, uint32_t sides, const Opt& o, hi
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
   for (int q = 0; q < nprob; ++q) {
+    // the copies prepared at the start are the dictionaries as they were then
+    if (dictionaries_rewritten(p, q, sizeof(T))) SDL_TRY(prepare<T>(p[q], pl.pb[q], L));
     if (sides & 1u) SDL_TRY(run_update<T>(1, p[q], pl.pb[q], pl, o, true, -1, 0, L));
     if (sides & 2u) SDL_TRY(run_update<T>(2, p[q], pl.pb[q], pl, o, true, -1, 0, L));
   }
@@ -1300,9 +1332,9 @@ int patches_to_image_impl(const sdl_problem* p, int H, int W, const Opt& o, void
   void* wsb = nullptr;
   SDL_TRY(acquire_ws(ctx, o, pl.bytes, st, &wsb));
   layout(p, 1, sizeof(T), 0, wsb, &pl);
-  const PrepJob<T> jobs[] = {prep_job<T>(p->D1, p->m1, p->n1, pl.pb[0].Dc1, pl.pb[0].G1c),
-                             prep_job<T>(p->D2, p->m2, p->n2, pl.pb[0].Dc2, pl.pb[0].G2c)};
-  HIP_TRY(launch_call_prep<T>(jobs, 2, nullptr, nullptr, 0, st));
+  std::vector<std::pair<int, int>> marks;
+  Launcher L{st, false, ctx, &marks};
+  SDL_TRY(prepare<T>(p[0], pl.pb[0], L));
   HIP_TRY(launch_patches_to_image<T>(p->supp, (const T*)p->coef, (const T*)pl.pb[0].Dc1, (const T*)pl.pb[0].Dc2, H, W,
                                      p->m1, p->m2, p->n1, p->n2, p->s, (T*)image, st));
   return SDL_OK;

@@ -1,0 +1,50 @@
+"""Problems of one call that share memory: the results are those of the problems one after the other,
+bit for bit (the same kernels on the same values)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2007_03800_amd import api
+from tests.conftest import planted, rand_dicts
+
+pytestmark = pytest.mark.gpu
+
+
+def results(probs):
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for p in probs for t in (p.D1, p.D2, p.supp, p.coef, p.res2)]
+
+
+def equal(a, b):
+    for u, v in zip(a, b):
+        np.testing.assert_array_equal(u, v)
+
+
+# ---- an update of several problems: each one sees the dictionaries as the problems before it left them
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("sides", [1, 2, 3])
+@pytest.mark.parametrize("share", ["D1", "D2", "both", "part"])
+def test_update_of_problems_that_share_a_dictionary(share, sides, dtype, rng):
+    m1, m2, n1, n2, s = 5, 4, 7, 6, 3
+    dicts = [rand_dicts(rng, m1, m2, n1, n2) for _ in range(3)]
+    data = [planted(rng, 200 + 30 * q, *dicts[q], s, noise=0.1)[0] for q in range(3)]
+
+    def problems():
+        out = [api.Problem.from_math(Y, *d, s, dtype=dtype) for Y, d in zip(data, dicts)]
+        api.sparse_code(out)  # codes at each problem's own dictionaries
+        if share == "part":   # problem 1's D2 begins one atom into problem 0's
+            whole = torch.cat([out[0].D2, out[0].D2[:1]])
+            out[0].D2, out[1].D2 = whole[:n2], whole[1:]
+        for q in (1, 2):
+            if share in ("D1", "both"):
+                out[q].D1 = out[0].D1
+            if share in ("D2", "both"):
+                out[q].D2 = out[0].D2
+        return out
+
+    together, alone = problems(), problems()
+    api.tmod_update(together, sides=sides)
+    for p in alone:
+        api.tmod_update(p, sides=sides)
+    equal(results(together), results(alone))
