@@ -110,7 +110,9 @@ typedef struct sdl_options {
   int32_t prec;             /* sdl_prec, default SDL_FP64 */
   int32_t schedule;         /* sdl_learn: 0 = Algorithm 1 (OMP, D1, OMP, D2), 1 = (OMP, D2, D1) */
   int32_t use_graph;        /* sdl_learn: run the problems of a batch side by side on internal streams (default 1;
-                               0: in order).  Named for the graph replay that did this before; same results */
+                               0: in order).  Named for the graph replay that did this before; same results:
+                               problems of which one writes memory (D1, D2, supp, coef, res2) that another reads
+                               or writes run in order either way */
   int32_t check_finite;     /* scan Y and dictionaries for NaN/Inf first (default 0) */
   int32_t timing;           /* fill stats->kernel_ms (eager launches with events; default 0) */
   int32_t kernel;           /* sparse-coding kernel: 0 auto, 1 generic, 2 register-resident multi-signal

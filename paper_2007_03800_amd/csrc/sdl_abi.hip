@@ -890,17 +890,37 @@ int iterate_problem(sdl_problem* p, int q, int K, const Opt& o, const Plan& pl, 
   return SDL_OK;
 }
 
-// Whether two problems of a call write the same buffer (they then run in order).
-bool share_results(const sdl_problem* p, int nprob) {
-  std::vector<const void*> out;
+// Whether one problem of a call may write memory that another one reads or writes (they then run in
+// order).  Sorted by their first byte, two ranges overlap where one begins before the furthest end so far;
+// ranges that are only read (signals) may.  Overlap within one problem counts too: its own order is kept
+// either way.
+bool share_memory(const sdl_problem* p, int nprob, size_t yelem, size_t elem) {
+  struct Range {
+    const char *begin, *end;
+    bool written;
+  };
+  std::vector<Range> v;
+  auto add = [&v](const void* b, size_t bytes, bool written) {
+    if (b && bytes) v.push_back({(const char*)b, (const char*)b + bytes, written});
+  };
   for (int q = 0; q < nprob; ++q) {
-    if (p[q].N == 0) continue;
-    const void* v[] = {p[q].D1, p[q].D2, p[q].supp, p[q].coef, p[q].res2};
-    for (const void* b : v)
-      if (b) out.push_back(b);
+    const sdl_problem& r = p[q];
+    if (r.N == 0) continue;
+    add(r.Y, yelem * (size_t)r.N * r.m1 * r.m2, false);
+    add(r.D1, sizeof(double) * r.m1 * r.n1, true);
+    add(r.D2, sizeof(double) * r.m2 * r.n2, true);
+    add(r.supp, sizeof(int32_t) * (size_t)r.N * r.s, true);
+    add(r.coef, elem * (size_t)r.N * r.s, true);
+    add(r.res2, elem * (size_t)r.N, true);
   }
-  std::sort(out.begin(), out.end());
-  return std::adjacent_find(out.begin(), out.end()) != out.end();
+  std::sort(v.begin(), v.end(), [](const Range& a, const Range& b) { return a.begin < b.begin; });
+  const char *any = nullptr, *written = nullptr;  // the furthest ends so far
+  for (const Range& r : v) {
+    if (r.begin < (r.written ? any : written)) return true;
+    any = std::max(any, r.end);
+    if (r.written) written = std::max(written, r.end);
+  }
+  return false;
 }
 
 // The streams of a call's problems: nb streams that start after what is queued on st ...
@@ -959,7 +979,8 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
   // those run in order.
   int nact = 0;
   for (int q = 0; q < nprob; ++q) nact += p[q].N > 0;
-  const bool side_by_side = o.use_graph && !timing && nact > 1 && !o.proposer && !share_results(p, nprob);
+  const bool side_by_side = o.use_graph && !timing && nact > 1 && !o.proposer &&
+                            !share_memory(p, nprob, pl.ybf16 ? 2 : sizeof(T), sizeof(T));
   const int nb = side_by_side ? (nact < kMaxBranches ? nact : kMaxBranches) : 0;
   if (nb > 0) SDL_TRY(fork_branches(ctx, st, nb));
   int lrc = SDL_OK;

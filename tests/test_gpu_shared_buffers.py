@@ -48,3 +48,33 @@ def test_update_of_problems_that_share_a_dictionary(share, sides, dtype, rng):
     for p in alone:
         api.tmod_update(p, sides=sides)
     equal(results(together), results(alone))
+
+
+# ---- learning side by side: problems of which one writes what another reads or writes run in order, also
+# where their buffers begin at different addresses
+
+@pytest.mark.parametrize("K", [1, 3])
+@pytest.mark.parametrize("share", ["dictionaries", "codes and signals", "residuals and signals"])
+def test_learning_with_overlapping_buffers(share, K, rng):
+    m1, m2, n1, n2, s = 4, 5, 6, 7, 3
+    data = []
+    for q in range(5):
+        d1, d2 = rand_dicts(rng, m1, m2, n1, n2)
+        data.append((planted(rng, 120 + 40 * q, d1, d2, s, noise=0.05)[0], d1, d2, s))
+    outs = []
+    for use_graph in (0, 1):
+        probs = [api.Problem.from_math(*d, dtype=torch.float64) for d in data]
+        a, b = probs[0], probs[3]
+        if share == "dictionaries":  # one atom further in the same buffer
+            whole = torch.cat([a.D1, a.D1[:1]])
+            a.D1, b.D1 = whole[:n1], whole[1:]
+        else:  # the first signals of problem 0 are what problem 3 writes, shifted by one element
+            Y = torch.cat([a.Y.flatten(), a.Y.flatten()[:8]])
+            if share == "codes and signals":
+                b.coef = Y[1:1 + b.N * s].view(b.N, s)
+            else:
+                b.res2 = Y[1:1 + b.N]
+            a.Y = Y[:a.Y.numel()].view(a.Y.shape)
+        traces = api.learn(probs, K, use_graph=use_graph)
+        outs.append([traces] + results(probs))
+    equal(*outs)
