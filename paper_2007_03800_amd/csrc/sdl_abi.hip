@@ -257,6 +257,7 @@ struct PBuf {
   double* sums;   // reduced [A | B | sum res2]
   double* w;
   double* rpart;
+  int* done;      // finished workgroups of the residual sum
   int nblk, rblk, nent;
 };
 
@@ -265,7 +266,6 @@ struct Plan {
   int* status;
   unsigned long long* counters;
   int* iter;     // per-problem RMSE counters
-  int* done;     // per-problem workgroup counters of the residual sums (null: codes only)
   int nprob = 1;
   bool ybf16 = false;  // signals are bfloat16 (SDL_BF16, SDL_MIXED_BF16)
   double* trace; // device trace
@@ -280,7 +280,6 @@ void layout(const sdl_problem* p, int nprob, size_t elem, int K, void* base, Pla
   pl->status = b.take<int>(4);
   pl->counters = b.take<unsigned long long>(kNumCounters);
   pl->iter = b.take<int>(nprob > 0 ? nprob : 1);
-  pl->done = codes_only ? nullptr : b.take<int>(nprob > 0 ? nprob : 1);
   pl->nprob = nprob > 0 ? nprob : 1;
   pl->trace = b.take<double>((size_t)(nprob > 0 ? nprob : 1) * (K + 1));
   for (int q = 0; q < nprob; ++q) {
@@ -288,10 +287,11 @@ void layout(const sdl_problem* p, int nprob, size_t elem, int K, void* base, Pla
     PBuf& x = pl->pb[q];
     x.Dc1 = b.take<char>(elem * r.m1 * r.n1);
     x.Dc2 = b.take<char>(elem * r.m2 * r.n2);
-    // 8 bytes per Gram entry beside its compute-type copy: part of the size that the interface states
-    // for a problem's scratch, so what fits a given buffer stays as it was
-    b.take<double>((size_t)r.n1 * r.n1);
-    b.take<double>((size_t)r.n2 * r.n2);
+    // 8 bytes per Gram entry beside its compute-type copy, the first matrix's rounded up: part of the size
+    // that the interface states for a problem's scratch, so what fits a given buffer stays as it was.  The
+    // first word is used.
+    const size_t g1 = (sizeof(double) * r.n1 * r.n1 + 255) & ~size_t(255);
+    x.done = (int*)b.take<char>(g1 + sizeof(double) * r.n2 * r.n2);
     x.G1c = b.take<char>(elem * r.n1 * r.n1);
     x.G2c = b.take<char>(elem * r.n2 * r.n2);
     if (codes_only) {
@@ -480,12 +480,13 @@ int start_call(const sdl_problem* p, int nprob, const Plan& pl, bool skip_empty,
   for (int q = 0; q < nprob; ++q) {
     if (skip_empty && p[q].N == 0) continue;
     jobs.push_back(prep_job<T>(p[q].D1, p[q].m1, p[q].n1, pl.pb[q].Dc1, pl.pb[q].G1c));
+    jobs.back().zero = pl.pb[q].done;
     jobs.push_back(prep_job<T>(p[q].D2, p[q].m2, p[q].n2, pl.pb[q].Dc2, pl.pb[q].G2c));
   }
-  int* const zero[] = {pl.status, (int*)pl.counters, pl.iter, pl.done};
-  const int nzero[] = {4, 2 * kNumCounters, pl.nprob, pl.done ? pl.nprob : 0};
+  int* const zero[] = {pl.status, (int*)pl.counters, pl.iter};
+  const int nzero[] = {4, 2 * kNumCounters, pl.nprob};
   SDL_TRY(L.begin(4));
-  HIP_TRY(launch_call_prep<T>(jobs.data(), (int)jobs.size(), zero, nzero, 4, L.st));
+  HIP_TRY(launch_call_prep<T>(jobs.data(), (int)jobs.size(), zero, nzero, 3, L.st));
   return L.end();
 }
 
@@ -608,7 +609,7 @@ int run_update(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, co
 template <typename T>
 int run_rmse(const sdl_problem& r, const PBuf& b, const Plan& pl, int q, int K, Launcher& L) {
   SDL_TRY(L.begin(5));
-  HIP_TRY(launch_rmse<T>((const T*)r.res2, r.N, (double)r.N * r.m1 * r.m2, b.rpart, b.rblk, pl.done + q, pl.trace, 1,
+  HIP_TRY(launch_rmse<T>((const T*)r.res2, r.N, (double)r.N * r.m1 * r.m2, b.rpart, b.rblk, b.done, pl.trace, 1,
                          q * (K + 1), pl.iter + q, L.st));
   return L.end();
 }
@@ -1051,6 +1052,7 @@ struct TPlan {
   void* Dc[kTensorMaxModes];
   void* Gc[kTensorMaxModes];
   double *part, *stage, *sums, *w, *rpart;
+  int* done;  // finished workgroups of the residual sum
   int rows, rblk, nent;
   // Problems coded by a two-mode kernel: modes 0 .. split-1 and split .. form one Kronecker factor
   // each (mk x nk; compute-type copy and Gram; a factor of one mode is that mode's own
@@ -1098,7 +1100,7 @@ void tensor_ws_layout(const sdl_tensor_problem* p, size_t elem, int K, void* bas
   tp->pl.status = b.take<int>(4);
   tp->pl.counters = b.take<unsigned long long>(kNumCounters);
   tp->pl.iter = b.take<int>(1);
-  tp->pl.done = b.take<int>(1);
+  tp->done = b.take<int>(1);
   tp->pl.trace = b.take<double>((size_t)K + 1);
   int nmax = 1, nent = 1;
   for (int d = 0; d < p->nmodes; ++d) {
@@ -1220,7 +1222,7 @@ template <typename T>
 int tensor_start(const sdl_tensor_problem* p, const TPlan& tp, hipStream_t st) {
   PrepJob<T> jobs[kTensorMaxModes];
   for (int d = 0; d < p->nmodes; ++d) jobs[d] = tensor_prep_job<T>(p, d, d + 1, tp.Dc[d], tp.Gc[d]);
-  int* const zero[] = {tp.pl.status, (int*)tp.pl.counters, tp.pl.iter, tp.pl.done};
+  int* const zero[] = {tp.pl.status, (int*)tp.pl.counters, tp.pl.iter, tp.done};
   const int nzero[] = {4, 2 * kNumCounters, 1, 1};
   HIP_TRY(launch_call_prep<T>(jobs, p->nmodes, zero, nzero, 4, st));
   return SDL_OK;
@@ -1323,14 +1325,14 @@ int tensor_impl(const sdl_tensor_problem* p, int call, int mode, int K, double* 
     for (int d = 0; d < p->nmodes; ++d) {
       SDL_TRY(tensor_code<T>(p, tp, o, st));
       if (d == 0 && p->res2)
-        HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.done, tp.pl.trace, 1,
+        HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.done, tp.pl.trace, 1,
                                0, tp.pl.iter, st));
       SDL_TRY(tensor_update_mode<T>(p, tp, o, d, false, st));
     }
   if (p->N > 0) {
     SDL_TRY(tensor_code<T>(p, tp, o, st));
     if (p->res2)
-      HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.pl.done, tp.pl.trace, 1,
+      HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.done, tp.pl.trace, 1,
                                0, tp.pl.iter, st));
   }
   int rc = finish_call(st, ctx, tp.pl, o, marks, true);

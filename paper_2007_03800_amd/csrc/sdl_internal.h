@@ -221,6 +221,7 @@ struct PrepJob {
   int nfac, m[4], n[4];
   const double* F[4];
   T *Dc, *Gc;
+  int* zero;  // a word set to zero beside it (null: none)
 };
 constexpr int kMaxPrepJobs = 8;  // dictionaries per launch
 constexpr int kMaxPrepZero = 4;  // ranges of ints set to zero

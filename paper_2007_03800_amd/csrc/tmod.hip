@@ -129,6 +129,7 @@ __global__ void __launch_bounds__(256) call_prep_kernel(PrepBatch<T> b) {
   while (which < kMaxPrepJobs - 1 && (int)blockIdx.x >= b.first[which + 1]) ++which;
   const PrepJob<T>& g = b.j[which];
   const int part = (int)blockIdx.x - b.first[which], nparts = b.first[which + 1] - b.first[which];
+  if (part == 0 && tid == 0 && g.zero) *g.zero = 0;
   int mr = 1, na = 1;
   for (int q = 0; q < g.nfac; ++q) {
     mr *= g.m[q];
