@@ -105,7 +105,6 @@ int dalloc(F** ptr, size_t n) {
 constexpr int kGradSplits = 8;  // partial gradients at most (one per 256 signals of the batch)
 
 int ensure_batch(sdl_proposer* P, int64_t B) {
-  if (!P->fp32 && !P->part) ST(dalloc(&P->part, (size_t)kGradSplits * P->np));
   if (B <= P->cap) return SDL_OK;
   const int64_t c = B;
   ST(dalloc((char**)&P->X, (size_t)c * P->M * P->elem));
@@ -121,6 +120,12 @@ int ensure_batch(sdl_proposer* P, int64_t B) {
   ST(dalloc(&P->loss, 1));
   P->cap = c;
   return SDL_OK;
+}
+
+// the same for training, which also needs the partial gradients
+int ensure_training(sdl_proposer* P, int64_t B) {
+  if (!P->fp32 && !P->part) ST(dalloc(&P->part, (size_t)kGradSplits * P->np));
+  return ensure_batch(P, B);
 }
 
 template <typename T>
@@ -352,7 +357,7 @@ int sdl_proposer_gradient(sdl_proposer* P, const float* Y, const int32_t* supp, 
   ST(check_shape(P, s));
   if (B <= 0 || B % 64) return abi_fail(SDL_E_SHAPE, "batch must be a positive multiple of 64");
   hipStream_t st = (hipStream_t)stream;
-  ST(ensure_batch(P, B));
+  ST(ensure_training(P, B));
   if (P->fp32) {
     HT(launch_prep_input<float>(Y, nullptr, B, P->M, (float*)P->X, nullptr, st));
     ST(forward<float>(P, B, true, st));
@@ -375,7 +380,7 @@ int sdl_proposer_train(sdl_proposer* P, const float* Y, const int32_t* supp, int
   if (batch <= 0 || batch % 64 || N < batch || epochs < 0) return abi_fail(SDL_E_SHAPE, "need N >= batch, batch % 64 == 0");
   if (N > INT32_MAX) return abi_fail(SDL_E_SHAPE, "N > 2^31 - 1 (batch indices are 32-bit)");
   hipStream_t st = (hipStream_t)stream;
-  ST(ensure_batch(P, batch));
+  ST(ensure_training(P, batch));
   if (P->idx_cap < N) {
     ST(dalloc(&P->idx, (size_t)N));
     P->idx_cap = N;
