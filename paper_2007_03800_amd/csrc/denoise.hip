@@ -8,8 +8,8 @@
 // (r + i, c + j) at its (i, j), stored column-major like every signal of the library.
 // The rebuild is one tiled pass: each output pixel sums its covering patches' estimates in a fixed
 // order, formed on chip from the codes (rebuild_rows_kernel walks along rows of patches;
-// rebuild_kernel, for patches of more than 256 pixels, goes pixel by pixel over codes gathered into
-// LDS); nothing adds into the image atomically and the result is reproducible.
+// rebuild_kernel, for patches of up to 40 and of more than 256 pixels, goes pixel by pixel over codes
+// gathered into LDS); nothing adds into the image atomically and the result is reproducible.
 #include "lanes.h"
 #include "sdl_internal.h"
 
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kTile* kTile) rebuild_kernel(const int32_t* __
   img[(int64_t)y * W + x] = acc / (T)((r1 - r0 + 1) * (c1 - c0 + 1));
 }
 
-// The rebuild for patches of up to 256 pixels (U = ceil(m1 m2 / 64)): sums along a row of patches in
+// The rebuild for patches of 41 to 256 pixels (U = 1, 2 or 4 of them a lane): sums along a row of patches in
 // registers, across rows of patches in LDS.  A workgroup owns kRowTile x kColTile pixels; each of its
 // waves takes rows r of covering patches and walks along c.  A lane stands for pixel row i of the
 // patch and image columns x = its phase (mod m2): patch c meets it at column j = x - c of the patch,
@@ -308,17 +308,18 @@ template <typename T>
 hipError_t launch_patches_to_image(const int32_t* supp, const T* coef, const T* D1, const T* D2, int H, int W, int m1,
                                    int m2, int n1, int n2, int s, T* img, hipStream_t st) {
   if ((int64_t)H * W <= 0) return hipSuccess;
-  // patches of up to 256 pixels whose row sums leave room for two workgroups a CU walk along rows of
-  // patches (512 x 512 image, 255,025 patches of 8 x 8: 138 -> 74 us); others go pixel by pixel
+  // Patches of 41 to 256 pixels whose row sums leave room for two workgroups a CU walk along rows of
+  // patches; others go pixel by pixel.  A patch costs a wave the same up to 64 pixels, so small ones
+  // waste its lanes: pixel by pixel against rows, 128 x 128 FP32 images with a tenth of the slots used: 4 x 4 patches
+  // 16 / 25 us, 6 x 6 45 / 37 (FP64 with three tenths used: 62 / 68), 7 x 7 56 / 43, 8 x 8 77 / 49;
+  // 512 x 512 image, 255,025 patches of 8 x 8: 138 / 74.  The same holds for lanes of four values below 129
+  // pixels: 5 x 13 patches with two values a lane 68 us, with four 108, pixel by pixel 79.
   const size_t rows_lds = rebuild_rows_lds_bytes<T>(m1, m2, n1, n2);
-  if (m1 * m2 <= 256 && rows_lds <= 80 * 1024) {
+  const int M = m1 * m2;
+  if (M > 40 && M <= 4 * kWave && rows_lds <= 80 * 1024) {
     const dim3 g((unsigned)((W + kColTile - 1) / kColTile), (unsigned)((H + kRowTile - 1) / kRowTile));
-    if (m1 * m2 <= kWave)
-      hipLaunchKernelGGL((rebuild_rows_kernel<T, 1>), g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W,
-                         m1, m2, n1, n2, s, img);
-    else
-      hipLaunchKernelGGL((rebuild_rows_kernel<T, 4>), g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W,
-                         m1, m2, n1, n2, s, img);
+    const auto k = M <= kWave ? rebuild_rows_kernel<T, 1> : M <= 2 * kWave ? rebuild_rows_kernel<T, 2> : rebuild_rows_kernel<T, 4>;
+    hipLaunchKernelGGL(k, g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W, m1, m2, n1, n2, s, img);
     return hipGetLastError();
   }
   // the pool takes what kRebuildLds leaves, and never more than every slot of every patch
@@ -339,6 +340,8 @@ hipError_t denoise_init_device() {
   const void* fs[] = {reinterpret_cast<const void*>(&rebuild_kernel<float>), reinterpret_cast<const void*>(&rebuild_kernel<double>),
                       reinterpret_cast<const void*>(&rebuild_rows_kernel<float, 1>),
                       reinterpret_cast<const void*>(&rebuild_rows_kernel<double, 1>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<float, 2>),
+                      reinterpret_cast<const void*>(&rebuild_rows_kernel<double, 2>),
                       reinterpret_cast<const void*>(&rebuild_rows_kernel<float, 4>),
                       reinterpret_cast<const void*>(&rebuild_rows_kernel<double, 4>)};
   for (const void* f : fs) {
