@@ -445,9 +445,10 @@ struct MLay {
   static constexpr bool PK = C::S >= 24;             // packed copies of L^{-1}
   // waves per SIMD the registers must allow: with packed copies LDS allows 6, and the
   // compiler's own choice lands one register above that (12 bytes per lane spill instead)
-  // waves per workgroup: from 512 pixels on the tables (27 KB at 48 x 36 atoms) and a wave's buffer
-  // (9 KB) leave room for two workgroups of four a CU, but for twelve waves that share one copy, three
-  // on every SIMD (20,000 signals alone: 614 -> 570 us; five a workgroup load the SIMDs unevenly)
+  // waves per workgroup, at most: from 512 pixels on the tables (27 KB at 48 x 36 atoms) and a wave's
+  // buffer (9 KB) leave room for two workgroups of four a CU, but for twelve waves that share one copy,
+  // three on every SIMD (20,000 signals alone: 614 -> 570 us; five a workgroup load the SIMDs unevenly).
+  // big_waves picks fewer for few signals.
   static constexpr bool BIG = C::M >= 512;
   static constexpr int WPB = BIG ? 12 : C::WPB;
   static constexpr int MINW = PK ? 6 : BIG ? 3 : 1;
@@ -604,6 +605,7 @@ __global__ void __launch_bounds__(kWave* MLay<C>::WPB) __attribute__((amdgpu_wav
   __shared__ __align__(16) float sW[L::WPB][L::PW];
 
   const int tid = threadIdx.x, wv = tid / kWave, lane = tid % kWave;
+  const int wpb = L::BIG ? blockDim.x / kWave : L::WPB;
   const int r16 = lane % 16, k4 = lane / 16;
   for (int e = tid; e < P1 * M1; e += blockDim.x) {
     const int i = e % P1, p = e / P1;
@@ -645,7 +647,7 @@ __global__ void __launch_bounds__(kWave* MLay<C>::WPB) __attribute__((amdgpu_wav
 
   unsigned n_early = 0;  // early-stopped signals of this wave (lane 0), counted once at the end
   int tprev = S;         // atoms of the signal before (the scratch starts out unknown)
-  for (int64_t k = (int64_t)blockIdx.x * L::WPB + wv; k < a.N; k += (int64_t)gridDim.x * L::WPB) {
+  for (int64_t k = (int64_t)blockIdx.x * wpb + wv; k < a.N; k += (int64_t)gridDim.x * wpb) {
     float yy = 0.f;
     for (int e = lane; e < M; e += kWave) {
       const float v = a.Yh ? bf16_to_float(a.Yh[k * M + e]) : a.Y[k * M + e];
@@ -887,22 +889,43 @@ __global__ void __launch_bounds__(kWave* MLay<C>::WPB) __attribute__((amdgpu_wav
   __syncthreads();
   if (tid == 0) {
     unsigned tot = 0;
-    for (int w = 0; w < L::WPB; ++w) tot += sEarly[w];
+    for (int w = 0; w < wpb; ++w) tot += sEarly[w];
     if (tot) atomicAdd(&a.counters[kCtrEarlyStop], (unsigned long long)tot);
   }
+}
+
+// Waves per workgroup of the shapes of 512 pixels and more, one workgroup a CU: four, eight or twelve,
+// whichever ends first.  A round of 256 workgroups takes about 60, 66 and 81 us with one, two and
+// three waves a SIMD (48 x 36 atoms): 1,024 signals 60, 70 and 84 us, 2,048: 113, 71 and 85 us, 3,072: 165,
+// 133 and 87 us, 4,096: 217, 135 and 161 us, 20,000: 1073, 661 and 567 us.  (Four always: 71, 87, 128, 151
+// and 649 us when two such workgroups shared a CU.)
+int big_waves(int64_t N) {
+  const int round_us[] = {60, 66, 81};
+  int best = 0;
+  int64_t best_us = 0;
+  for (int i = 0; i < 3; ++i) {
+    const int w = 4 * (i + 1);
+    const int64_t us = (N + 256 * w - 1) / (256 * w) * round_us[i];
+    if (best == 0 || us < best_us) {
+      best = w;
+      best_us = us;
+    }
+  }
+  return best;
 }
 
 // One signal per wave up to kWaveMaxBlocks workgroups (a persistent grid measured slower:
 // static striding leaves waves idle at the end).
 template <typename T, class C>
 hipError_t launch_wcfg(const OmpArgs<T>& a, hipStream_t st) {
-  constexpr int wpb = sizeof(T) == 4 && C::MF ? MLay<C>::WPB : C::WPB;
+  int wpb = C::WPB;
+  if constexpr (sizeof(T) == 4 && C::MF) wpb = MLay<C>::BIG ? big_waves(a.N) : MLay<C>::WPB;
   int64_t blocks = (a.N + wpb - 1) / wpb;
   if (blocks > kWaveMaxBlocks) blocks = kWaveMaxBlocks;
   if constexpr (sizeof(T) == 4 && C::MF)
     hipLaunchKernelGGL((omp_wave_mfma_kernel<C>), dim3((unsigned)blocks), dim3(kWave * wpb), 0, st, a);
   else
-    hipLaunchKernelGGL((omp_wave_kernel<T, C>), dim3((unsigned)blocks), dim3(kWave * C::WPB), 0, st, a);
+    hipLaunchKernelGGL((omp_wave_kernel<T, C>), dim3((unsigned)blocks), dim3(kWave * wpb), 0, st, a);
   return hipGetLastError();
 }
 
