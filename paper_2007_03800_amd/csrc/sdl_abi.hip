@@ -57,8 +57,13 @@ struct Ctx {
 };
 
 // Problems of one sdl_learn call run on streams of their own (at most this many; problems beyond it
-// share streams round-robin).
-constexpr int kMaxBranches = 8;
+// share streams round-robin): as many as HIP has hardware queues per process by default.  Streams that
+// share a queue run one after the other, so these four have to be on four queues.  A new stream goes to the
+// queue with the fewest streams, a new queue while there are fewer than four: once there are four, four streams
+// made in a row take one each, whatever other streams there are.  Three spare streams come first
+// for that.  (50 signals a problem, 20 iterations: four problems 1.7 ms; 3.1 ms where two of them
+// shared a queue, with the first four or eight streams made.)
+constexpr int kMaxBranches = 4, kSpareBranches = 3;
 
 std::mutex g_mu;
 std::map<std::pair<int, hipStream_t>, Ctx*> g_ctx;
@@ -924,26 +929,29 @@ bool share_memory(const sdl_problem* p, int nprob, size_t yelem, size_t elem) {
   return false;
 }
 
-// The streams of a call's problems: nb streams that start after what is queued on st ...
+// The streams of a call's problems: branch[kSpareBranches ..] start after what is queued on st ...
 int fork_branches(Ctx* ctx, hipStream_t st, int nb) {
-  while ((int)ctx->branch.size() < nb) {
+  if (!ctx->fork) HIP_TRY(hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
+  HIP_TRY(hipEventRecord(ctx->fork, st));
+  while ((int)ctx->branch.size() < kSpareBranches + kMaxBranches) {
     hipStream_t s;
-    hipEvent_t e;
     HIP_TRY(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
     ctx->branch.push_back(s);
+    HIP_TRY(hipStreamWaitEvent(s, ctx->fork, 0));  // (a stream may get its queue when it is first used)
+  }
+  while ((int)ctx->branch_join.size() < kMaxBranches) {
+    hipEvent_t e;
     HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     ctx->branch_join.push_back(e);
   }
-  if (!ctx->fork) HIP_TRY(hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
-  HIP_TRY(hipEventRecord(ctx->fork, st));
-  for (int i = 0; i < nb; ++i) HIP_TRY(hipStreamWaitEvent(ctx->branch[i], ctx->fork, 0));
+  for (int i = 0; i < nb; ++i) HIP_TRY(hipStreamWaitEvent(ctx->branch[kSpareBranches + i], ctx->fork, 0));
   return SDL_OK;
 }
 // ... and that st waits for.
 int join_branches(Ctx* ctx, hipStream_t st, int nb) {
   int rc = SDL_OK;
   for (int i = 0; i < nb; ++i) {
-    hipError_t e = hipEventRecord(ctx->branch_join[i], ctx->branch[i]);
+    hipError_t e = hipEventRecord(ctx->branch_join[i], ctx->branch[kSpareBranches + i]);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->branch_join[i], 0);
     if (e != hipSuccess && rc == SDL_OK) rc = fail(SDL_E_DEVICE, "joining a branch: %s", hipGetErrorString(e));
   }
@@ -989,7 +997,7 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
     int slot = 0;
     for (int q = 0; q < nprob && lrc == SDL_OK; ++q) {
       if (p[q].N == 0) continue;
-      Launcher B{nb > 0 ? ctx->branch[slot++ % nb] : st, timing, ctx, &marks, L.next_ev};
+      Launcher B{nb > 0 ? ctx->branch[kSpareBranches + slot++ % nb] : st, timing, ctx, &marks, L.next_ev};
       if (it < K) {
         lrc = iterate_problem<T>(p, q, K, o, pl, B);
       } else {

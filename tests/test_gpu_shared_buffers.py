@@ -78,3 +78,22 @@ def test_learning_with_overlapping_buffers(share, K, rng):
         traces = api.learn(probs, K, use_graph=use_graph)
         outs.append([traces] + results(probs))
     equal(*outs)
+
+
+# ---- more problems than internal streams, on the caller's own stream: results as in order on the default one,
+# and complete for work queued on the caller's stream afterwards
+
+def test_learning_side_by_side_on_a_stream(rng):
+    data = []
+    for q in range(7):
+        d1, d2 = rand_dicts(rng, 8, 8, 16, 16)
+        data.append((planted(rng, 300 + 500 * (q % 3), d1, d2, 8, noise=0.05)[0], d1, d2, 8))
+    outs = []
+    for use_graph, stream in ((0, torch.cuda.current_stream()), (1, torch.cuda.Stream())):
+        probs = [api.Problem.from_math(*d, dtype=torch.float32) for d in data]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            traces = [api.learn(probs, 3, use_graph=use_graph) for _ in range(2)]
+            copies = [p.coef.clone() for p in probs]
+        outs.append(traces + results(probs) + [c.cpu().numpy() for c in copies])
+    equal(*outs)
