@@ -158,12 +158,13 @@ typedef struct sdl_options {
                                D1^T Y_k D2 of largest magnitude (ties: smaller atom; listed in decreasing
                                magnitude; res2 from the explicit residual); sdl_tmod_update replaces D1 by the
                                orthogonal Procrustes solution U V^T of sum_k Y_k D2 X_k^T = U S V^T (D2 likewise from
-                               sum_k Y_k^T D1 X_k; FP64 one-sided Jacobi SVD; the codes are not rescaled; a rank-
-                               deficient sum leaves the dictionary and reports SDL_E_SINGULAR); sdl_learn iterates
-                               these as Algorithm 1 does.  Reading of the paper's printed update, which multiplies
-                               the sum by sum_k X_k X_k^T before the SVD: the polar factor of the sum alone, the
-                               minimiser of eq. (1) over orthonormal dictionaries for fixed codes.  FP32 or FP64;
-                               the caller's dictionaries must be orthonormal */
+                               sum_k Y_k^T D1 X_k; in FP64, by Newton's iteration for the polar factor up to a
+                               condition number of 1e6 and one-sided Jacobi rotations beyond; the codes are not
+                               rescaled; a rank-deficient sum leaves the dictionary and reports SDL_E_SINGULAR);
+                               sdl_learn iterates these as Algorithm 1 does.  Reading of the paper's printed update,
+                               which multiplies the sum by sum_k X_k X_k^T before the SVD: the polar factor of the
+                               sum alone, the minimiser of eq. (1) over orthonormal dictionaries for fixed codes.
+                               FP32 or FP64; the caller's dictionaries must be orthonormal */
   int32_t reserved1;        /* must be 0 */
 } sdl_options;
 
@@ -248,9 +249,10 @@ int sdl_image_to_patches(const void* image, int32_t H, int32_t W, int32_t m1, in
  * coef and N = (H-m1+1)(W-m2+1); Y and res2 unused): every pixel is the plain average, over the patches
  * covering it, of D1 X_k D2^T at that pixel (a reading: the paper does not say how overlapping
  * estimates are combined).  options->prec (SDL_FP32 or SDL_FP64) is the type of coef and image.
- * Unused support slots (-1) may sit anywhere in a code.  The estimates are formed on chip, pixel
- * by pixel, and never stored: with options->workspace that buffer must hold what
- * sdl_workspace_bytes reports for sparse coding (call 0) of p (SDL_E_NOMEM otherwise).
+ * Unused support slots (-1) may sit anywhere in a code.  The estimates are formed on chip, along rows
+ * of patches (41 to 256 pixels a patch) or pixel by pixel, and never stored: with options->workspace
+ * that buffer must hold what sdl_workspace_bytes reports for sparse coding (call 0) of p (SDL_E_NOMEM
+ * otherwise).
  * Asynchronous on `stream`. */
 int sdl_patches_to_image(const sdl_problem* p, int32_t H, int32_t W, const sdl_options* o, void* image,
                          void* stream);

@@ -26,8 +26,9 @@
 //    key is within the band may hold a third candidate that is not re-scored; such steps are
 //    counted.  The winner's exact correlation drives the coefficient update, so the
 //    coefficients do not see BF16 rounding.
-//    What bounds it: vector instructions (about 1,000 a step for 16 signals of 576 atoms, 80% of the
-//    issue slots at the two waves a SIMD that the registers allow; three waves spill and lose 8%).
+//    What bounds it: vector instructions (about 1,000 a step for 16 signals of 576 atoms; vector ALUs
+//    busy 69% of the time, matrix cores another 29%, at the two waves a SIMD that the registers allow;
+//    three waves spill and lose 8%).
 //    1,000,000 signals, 12x12 patches, 24x24 atoms, 12 steps: 2.06 ms before the keys' fused maxima
 //    (two_largest), atoms carried as (j, i) and candidates re-scored in any order; 1.86-1.91 ms with them.
 //  * Cholesky factor, coefficient updates, small-pivot FP64 path, implicit masking and the

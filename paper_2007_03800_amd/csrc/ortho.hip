@@ -2,7 +2,8 @@
 // (n1 = m1, n2 = m2).  Sparse coding needs no least squares: X_k = T_s(D1^T Y_k D2), the s
 // entries of largest magnitude.  The dictionary update is the orthogonal Procrustes solution:
 // the polar factor U V^T of the update's B sum (sum_k Y_k D2 X_k^T for D1, sum_k Y_k^T D1 X_k
-// for D2), here by one-sided Jacobi rotations on one wave in FP64.
+// for D2), on one wave in FP64 by Newton's iteration, by one-sided Jacobi rotations where the sum is too
+// far from well conditioned for that.
 //
 // Codes: a wave codes four signals, sixteen lanes per signal.  The signals are staged in LDS;
 // V = Y D2 and C = D1^T V are formed entry by entry (lane l of the signal owns entries
@@ -388,59 +389,59 @@ __global__ void __launch_bounds__(kWave) procrustes_kernel(const double* __restr
     for (int e = x; e < nent; e += kWave) V[e] = (e % n) == (e / n) ? 1.0 : 0.0;
     wave_sync();
     for (int sweep = 0; sweep < 60; ++sweep) {
-    int rotated = 0;
-    for (int i = 0; i < n - 1; ++i)
-      for (int j = i + 1; j < n; ++j) {
-        double pa = 0.0, pb = 0.0, pg = 0.0;
-        if (row) {
-          const double wi = W[x + n * i], wj = W[x + n * j];
-          pa = wi * wi;
-          pb = wj * wj;
-          pg = wi * wj;
+      int rotated = 0;
+      for (int i = 0; i < n - 1; ++i)
+        for (int j = i + 1; j < n; ++j) {
+          double pa = 0.0, pb = 0.0, pg = 0.0;
+          if (row) {
+            const double wi = W[x + n * i], wj = W[x + n * j];
+            pa = wi * wi;
+            pb = wj * wj;
+            pg = wi * wj;
+          }
+          // sums over the n <= 32 rows in a fixed order: each 16-lane row by DPP, then rows 0 and
+          // 1 added from their first lanes (uniform values: every lane takes the same decision)
+          pa = row16_sum(pa);
+          pb = row16_sum(pb);
+          pg = row16_sum(pg);
+          pa = n > 16 ? lane_value(pa, 0) + lane_value(pa, 16) : lane_value(pa, 0);
+          pb = n > 16 ? lane_value(pb, 0) + lane_value(pb, 16) : lane_value(pb, 0);
+          pg = n > 16 ? lane_value(pg, 0) + lane_value(pg, 16) : lane_value(pg, 0);
+          if (fabs(pg) <= 1e-15 * sqrt(pa * pb) || pg == 0.0) continue;
+          rotated = 1;
+          const double zeta = (pb - pa) / (2.0 * pg);
+          const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
+          const double c = 1.0 / sqrt(1.0 + t * t), sn = c * t;
+          if (row) {
+            const double wi = W[x + n * i], wj = W[x + n * j];
+            W[x + n * i] = c * wi - sn * wj;
+            W[x + n * j] = sn * wi + c * wj;
+            const double vi = V[x + n * i], vj = V[x + n * j];
+            V[x + n * i] = c * vi - sn * vj;
+            V[x + n * j] = sn * vi + c * vj;
+          }
+          wave_sync();
         }
-        // sums over the n <= 32 rows in a fixed order: each 16-lane row by DPP, then rows 0 and
-        // 1 added from their first lanes (uniform values: every lane takes the same decision)
-        pa = row16_sum(pa);
-        pb = row16_sum(pb);
-        pg = row16_sum(pg);
-        pa = n > 16 ? lane_value(pa, 0) + lane_value(pa, 16) : lane_value(pa, 0);
-        pb = n > 16 ? lane_value(pb, 0) + lane_value(pb, 16) : lane_value(pb, 0);
-        pg = n > 16 ? lane_value(pg, 0) + lane_value(pg, 16) : lane_value(pg, 0);
-        if (fabs(pg) <= 1e-15 * sqrt(pa * pb) || pg == 0.0) continue;
-        rotated = 1;
-        const double zeta = (pb - pa) / (2.0 * pg);
-        const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-        const double c = 1.0 / sqrt(1.0 + t * t), sn = c * t;
-        if (row) {
-          const double wi = W[x + n * i], wj = W[x + n * j];
-          W[x + n * i] = c * wi - sn * wj;
-          W[x + n * j] = sn * wi + c * wj;
-          const double vi = V[x + n * i], vj = V[x + n * j];
-          V[x + n * i] = c * vi - sn * vj;
-          V[x + n * j] = sn * vi + c * vj;
-        }
-        wave_sync();
-      }
-    if (!rotated) break;
-  }
-  wave_sync();
-  if (row) {
-    double v = 0.0;
-    for (int r = 0; r < n; ++r) v += W[r + n * x] * W[r + n * x];
-    sig[x] = sqrt(v);
-  }
-  wave_sync();
-  double smax = 0.0;
-  for (int i = 0; i < n; ++i) smax = fmax(smax, sig[i]);
-  bool ok = true;
-  for (int i = 0; i < n; ++i) ok = ok && sig[i] > 1e-12 * smax;
-  if (!ok) {
-    if (x == 0) {
-      atomicOr(status, kStatusSingular);
-      atomicAdd(&counters[kCtrSingular], 1ull);
+      if (!rotated) break;
     }
-    return;
-  }
+    wave_sync();
+    if (row) {
+      double v = 0.0;
+      for (int r = 0; r < n; ++r) v += W[r + n * x] * W[r + n * x];
+      sig[x] = sqrt(v);
+    }
+    wave_sync();
+    double smax = 0.0;
+    for (int i = 0; i < n; ++i) smax = fmax(smax, sig[i]);
+    bool ok = true;
+    for (int i = 0; i < n; ++i) ok = ok && sig[i] > 1e-12 * smax;
+    if (!ok) {
+      if (x == 0) {
+        atomicOr(status, kStatusSingular);
+        atomicAdd(&counters[kCtrSingular], 1ull);
+      }
+      return;
+    }
   }
   // D (D[r][c] = sum_i (W[r][i] / sigma_i) V[c][i] after the rotations) and its Gram matrix, one entry
   // per lane and pass

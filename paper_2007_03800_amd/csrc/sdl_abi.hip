@@ -567,7 +567,6 @@ TmodArgs<T> tmod_args(int side, const sdl_problem& r, const PBuf& b, const Plan&
   return a;
 }
 
-// one TMOD half-step from the codes in supp/coef: standalone sums -> reduce -> solve (+ rescale)
 // Standalone sums of one side (and with_res2 the residual sum) into b.part; returns the number of
 // partial rows.  SDL_MIXED_BF16 runs them on the BF16 matrix cores where that kernel is compiled for
 // the shape.
@@ -596,7 +595,8 @@ int run_sums(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, cons
   return L.end();
 }
 
-// (rmse_q >= 0: also the RMSE of the codes' sweep, for problem rmse_q's trace of K + 1 entries)
+// One TMOD half-step from the codes in supp/coef: standalone sums -> reduce -> solve (+ rescale)
+// (rmse_q >= 0: also the RMSE of the codes' sweep, for problem rmse_q's trace of K + 1 entries).
 template <typename T>
 int run_update(int side, const sdl_problem& r, const PBuf& b, const Plan& pl, const Opt& o, bool rescale, int rmse_q,
                int K, Launcher& L) {
@@ -979,10 +979,11 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
     SDL_TRY(run_check_finite<T>(p, nprob, pl, st));
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
-  // Every kernel of an iteration runs 8 us and more and takes 3-4 us to launch, so launching them
-  // directly keeps the GPU fed.  (Capturing four iterations as a graph and replaying it cost 0.2 ms a
+  // A kernel of an iteration runs 4-12 us at the least (first-stage reductions 4, update sums 5-10, solves
+  // 10-11, coding 12 and more) and takes 3-4 us to launch, so launching them directly keeps the GPU fed.  (Capturing four iterations as a graph and replaying it cost 0.2 ms a
   // call whenever the call's buffers were not those of the call before, and gained nothing when they
-  // were: 0.186 ms an iteration of 100,000 8x8 signals replayed, 0.178 ms launched.)  Several problems run
+  // were: 0.186 ms an iteration of 100,000 8x8 signals replayed, 0.178 ms launched; sixteen problems of 50
+  // signals on the same buffers, where the launches themselves set the pace, 6.6 and 6.9 ms.)  Several problems run
   // side by side on streams of their own: the tail of one problem's launch, where its last workgroups
   // leave most of the chip idle, is another's work.  A proposer's buffers are shared by all problems:
   // those run in order.
