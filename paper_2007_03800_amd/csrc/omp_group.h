@@ -511,9 +511,12 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
       }
       group_sync();  // the new row of L is visible
     }
-    // explicit residual Y - sum_q x_q d1_{i_q} d2_{j_q}^T (x_q = 0 beyond a signal's atoms)
-    const int mi = my_code < 0 ? 0 : my_code & 255, mj = my_code < 0 ? 0 : my_code >> 8;
+    // explicit residual Y - sum_q x_q d1_{i_q} d2_{j_q}^T.  Beyond a signal's atoms x_q = 0 with the signal's
+    // first atom, which was chosen and so is finite (atom 0 may hold NaN); a signal without atoms keeps Y.
+    const int first = from_lane<C>(my_code, IntC<0>{}), mc0 = my_code < 0 ? first : my_code;
+    const int mi = mc0 < 0 ? 0 : mc0 & 255, mj = mc0 < 0 ? 0 : mc0 >> 8;
     const int my_pix = mi * ldd | (mj << 16);
+    const bool bare = __ballot(valid && nt == 0) != 0ull;
     T rp[4] = {0, 0, 0, 0};
     for (int e0 = 0; e0 < M; e0 += kWave) {
       T r[NS];
@@ -533,6 +536,11 @@ __global__ void __launch_bounds__(kWave* C::MAXW) __attribute__((amdgpu_waves_pe
         for (int u = 0; u < NS; ++u)
           r[u] = gfma(-(x * sD1[p1[u] + (o & 0xFFFF)]), sD2[p2[u] + (o >> 16)], r[u]);
       });
+      if (bare) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u)
+          if (nt == 0) r[u] = ys[e0 + G * u + l < M ? e0 + G * u + l : M - 1];
+      }
 #pragma unroll
       for (int u = 0; u < NS; ++u)
         if (e0 + G * u + l < M) rp[u] = gfma(r[u], r[u], rp[u]);

@@ -100,3 +100,23 @@ def test_exact_tensors_stop(kind, ms, s):
     np.testing.assert_array_equal(cg[::2], co[::2])
     agree, ties, bad, err = compare_codes(Y, None, None, sg, cg, so, co, 1e-9, K=kron_all(T))
     assert bad == 0 and ties <= 1 and err <= 1e-10
+
+
+# ---- atoms that hold NaN (the first of each dictionary): never chosen, and the residuals of signals with
+# fewer than s atoms, or none, stay those of a dictionary with zeros in their place
+@DTYPES
+@pytest.mark.parametrize("m,s", [(4, 3), (9, 6), (8, 17)])
+def test_nan_atoms_leave_residuals_alone(m, s, dtype):
+    d, Y, _ = batch("identity", m, dtype)
+    z1, z2 = d.copy(), d.copy()
+    z1[:, 0], z2[:, 0] = 0.0, 0.0
+    n1, n2 = d.copy(), d.copy()
+    n1[0, 0], n2[1, 0] = np.nan, np.nan
+    pr = api.Problem.from_math(Y, n1, n2, s, dtype=dtype)
+    api.sparse_code(pr, kernel=1)
+    torch.cuda.synchronize()
+    so, co, ro = oracle.omp(Y, z1, z2, s)
+    np.testing.assert_array_equal(pr.supp.cpu().numpy(), so)
+    np.testing.assert_array_equal(pr.coef.cpu().double().numpy(), co)
+    np.testing.assert_allclose(pr.res2.cpu().double().numpy(), ro, rtol=1e-12 if dtype == torch.float64 else 1e-5)
+    assert (so[:, -1] < 0).any() and (so[:, 0] < 0).any()
