@@ -1265,11 +1265,16 @@ int tensor_code(const sdl_tensor_problem* p, const TPlan& tp, const Opt& o, hipS
     HIP_TRY(launch_tensor_omp<T>(tensor_args<T>(p, tp, o), st));
     return SDL_OK;
   }
+  // (FP64: from the modes' copies, which an update of another mode with the same dictionary buffer does not
+  // reach)
   PrepJob<T> jobs[2];
   int nj = 0;
   for (int f = 0; f < 2; ++f) {
     const int q0 = f == 0 ? 0 : tp.split, q1 = f == 0 ? tp.split : p->nmodes;
-    if (q1 - q0 > 1) jobs[nj++] = tensor_prep_job<T>(p, q0, q1, tp.Dkc[f], tp.Gkc[f]);
+    if (q1 - q0 == 1) continue;
+    PrepJob<T>& j = jobs[nj++] = tensor_prep_job<T>(p, q0, q1, tp.Dkc[f], tp.Gkc[f]);
+    if constexpr (sizeof(T) == 8)
+      for (int d = q0; d < q1; ++d) j.F[d - q0] = (const double*)tp.Dc[d];
   }
   HIP_TRY(launch_call_prep<T>(jobs, nj, nullptr, nullptr, 0, st));
   OmpArgs<T> a{};

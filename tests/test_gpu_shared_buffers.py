@@ -97,3 +97,24 @@ def test_learning_side_by_side_on_a_stream(rng):
             copies = [p.coef.clone() for p in probs]
         outs.append(traces + results(probs) + [c.cpu().numpy() for c in copies])
     equal(*outs)
+
+
+# ---- n modes that share a dictionary buffer: in FP64 every mode works with its own copy, made at the start of the
+# call and renewed by its own updates, so codes and trace are those of modes with buffers of their own
+
+@pytest.mark.parametrize("ms,ns,shared", [((4, 4, 4), (6, 6, 6), (0, 2)), ((4, 4, 4), (6, 6, 6), (1, 2)),
+                                          ((4, 4, 3), (6, 6, 5), (0, 1)), ((3, 4, 4, 2), (4, 5, 5, 3), (1, 2))])
+def test_tensor_modes_that_share_a_dictionary(ms, ns, shared, rng):
+    T = [rng.standard_normal((m, n)) for m, n in zip(ms, ns)]
+    T = [d / np.linalg.norm(d, axis=0) for d in T]
+    T[shared[1]] = T[shared[0]]
+    Y = rng.standard_normal((400, *ms))
+    outs = []
+    for same in (False, True):
+        pr = api.TensorProblem.from_math(Y, T, 4, dtype=torch.float64)
+        if same:
+            pr.Ds[shared[1]] = pr.Ds[shared[0]]
+        trace = api.tensor_learn(pr, 2)
+        torch.cuda.synchronize()
+        outs.append([trace] + [t.cpu().numpy() for t in (pr.supp, pr.coef, pr.res2)])
+    equal(*outs)
