@@ -1226,14 +1226,34 @@ PrepJob<T> tensor_prep_job(const sdl_tensor_problem* p, int q0, int q1, void* Dc
   return j;
 }
 
-// The start of a call, one launch: status words and counters zeroed, every mode's dictionary prepared
+// The Kronecker factors of several modes of a problem that is cut in two (at most two jobs).  In FP64 a
+// later sweep takes them from the modes' copies, which an update of another mode with the same dictionary
+// buffer does not reach.
 template <typename T>
-int tensor_start(const sdl_tensor_problem* p, const TPlan& tp, hipStream_t st) {
-  PrepJob<T> jobs[kTensorMaxModes];
-  for (int d = 0; d < p->nmodes; ++d) jobs[d] = tensor_prep_job<T>(p, d, d + 1, tp.Dc[d], tp.Gc[d]);
+int tensor_factor_jobs(const sdl_tensor_problem* p, const TPlan& tp, bool from_copies, PrepJob<T>* jobs) {
+  int n = 0;
+  for (int f = 0; f < 2 && tp.split > 0; ++f) {
+    const int q0 = f == 0 ? 0 : tp.split, q1 = f == 0 ? tp.split : p->nmodes;
+    if (q1 - q0 == 1) continue;
+    jobs[n] = tensor_prep_job<T>(p, q0, q1, tp.Dkc[f], tp.Gkc[f]);
+    if constexpr (sizeof(T) == 8)
+      for (int d = q0; from_copies && d < q1; ++d) jobs[n].F[d - q0] = (const double*)tp.Dc[d];
+    ++n;
+  }
+  return n;
+}
+
+// The start of a call, one launch: status words and counters zeroed, every mode's dictionary prepared
+// and, for a call that codes, the factors of its first sweep
+template <typename T>
+int tensor_start(const sdl_tensor_problem* p, const TPlan& tp, bool codes, hipStream_t st) {
+  PrepJob<T> jobs[kTensorMaxModes + 2];
+  int n = p->nmodes;
+  for (int d = 0; d < n; ++d) jobs[d] = tensor_prep_job<T>(p, d, d + 1, tp.Dc[d], tp.Gc[d]);
+  if (codes && p->N > 0) n += tensor_factor_jobs<T>(p, tp, false, jobs + n);
   int* const zero[] = {tp.pl.status, (int*)tp.pl.counters, tp.pl.iter, tp.done};
   const int nzero[] = {4, 2 * kNumCounters, 1, 1};
-  HIP_TRY(launch_call_prep<T>(jobs, p->nmodes, zero, nzero, 4, st));
+  HIP_TRY(launch_call_prep<T>(jobs, n, zero, nzero, 4, st));
   return SDL_OK;
 }
 
@@ -1258,25 +1278,18 @@ int tensor_update_mode(const sdl_tensor_problem* p, const TPlan& tp, const Opt& 
 
 // sparse coding of every signal: a two-mode kernel on the two Kronecker factors where the problem is
 // cut in two (the same atoms in the same order: a = j + n1 j', j and j' the indices within the
-// factors), else the n-mode kernel
+// factors), else the n-mode kernel.  first: the factors are those of the call's start
 template <typename T>
-int tensor_code(const sdl_tensor_problem* p, const TPlan& tp, const Opt& o, hipStream_t st) {
+int tensor_code(const sdl_tensor_problem* p, const TPlan& tp, const Opt& o, bool first, hipStream_t st) {
   if (p->N == 0 || tp.split == 0) {
     HIP_TRY(launch_tensor_omp<T>(tensor_args<T>(p, tp, o), st));
     return SDL_OK;
   }
-  // (FP64: from the modes' copies, which an update of another mode with the same dictionary buffer does not
-  // reach)
-  PrepJob<T> jobs[2];
-  int nj = 0;
-  for (int f = 0; f < 2; ++f) {
-    const int q0 = f == 0 ? 0 : tp.split, q1 = f == 0 ? tp.split : p->nmodes;
-    if (q1 - q0 == 1) continue;
-    PrepJob<T>& j = jobs[nj++] = tensor_prep_job<T>(p, q0, q1, tp.Dkc[f], tp.Gkc[f]);
-    if constexpr (sizeof(T) == 8)
-      for (int d = q0; d < q1; ++d) j.F[d - q0] = (const double*)tp.Dc[d];
+  if (!first) {
+    PrepJob<T> jobs[2];
+    const int n = tensor_factor_jobs<T>(p, tp, true, jobs);
+    HIP_TRY(launch_call_prep<T>(jobs, n, nullptr, nullptr, 0, st));
   }
-  HIP_TRY(launch_call_prep<T>(jobs, nj, nullptr, nullptr, 0, st));
   OmpArgs<T> a{};
   a.m1 = tp.mk[0]; a.m2 = tp.mk[1]; a.n1 = tp.nk[0]; a.n2 = tp.nk[1]; a.s = p->s; a.N = p->N;
   a.Y = (const T*)p->Y;
@@ -1320,14 +1333,14 @@ int tensor_impl(const sdl_tensor_problem* p, int call, int mode, int K, double* 
   SDL_TRY_WS(ensure_ws(ctx, tp.bytes, st));
   tensor_ws_layout(p, sizeof(T), K, ctx->ws, &tp);
   std::vector<std::pair<int, int>> marks;
-  SDL_TRY(tensor_start<T>(p, tp, st));
+  SDL_TRY(tensor_start<T>(p, tp, call != 1, st));
   if (o.check_finite) {
     SDL_TRY(tensor_check_finite<T>(p, tp, st));
     SDL_TRY(finish_call(st, ctx, tp.pl, o, marks, true));
   }
   const double denom = (double)p->N * (double)tensor_elems(p->m, p->nmodes);
   if (call == 0) {
-    SDL_TRY(tensor_code<T>(p, tp, o, st));
+    SDL_TRY(tensor_code<T>(p, tp, o, true, st));
     return finish_call(st, ctx, tp.pl, o, marks, false);
   }
   if (call == 1) {
@@ -1337,14 +1350,14 @@ int tensor_impl(const sdl_tensor_problem* p, int call, int mode, int K, double* 
   // Algorithm 1 with one sweep per mode: codes, then that mode's dictionary
   for (int it = 0; it < K && p->N > 0; ++it)
     for (int d = 0; d < p->nmodes; ++d) {
-      SDL_TRY(tensor_code<T>(p, tp, o, st));
+      SDL_TRY(tensor_code<T>(p, tp, o, it == 0 && d == 0, st));
       if (d == 0 && p->res2)
         HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.done, tp.pl.trace, 1,
                                0, tp.pl.iter, st));
       SDL_TRY(tensor_update_mode<T>(p, tp, o, d, false, st));
     }
   if (p->N > 0) {
-    SDL_TRY(tensor_code<T>(p, tp, o, st));
+    SDL_TRY(tensor_code<T>(p, tp, o, K == 0, st));
     if (p->res2)
       HIP_TRY(launch_rmse<T>((const T*)p->res2, p->N, denom, tp.rpart, tp.rblk, tp.done, tp.pl.trace, 1,
                                0, tp.pl.iter, st));
