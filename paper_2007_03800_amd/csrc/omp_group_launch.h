@@ -93,8 +93,9 @@ hipError_t group_launch(const OmpArgs<T>& a, hipStream_t st) {
   const int64_t waves = (a.N + ns - 1) / ns;
   // waves per workgroup: the most waves per CU that LDS and registers allow, the waves of a workgroup
   // sharing one copy of the tables (8x32 signals with 12x72 atoms in FP64, 62 KB of tables: 310 us
-  // with eight, 229 us with sixteen for 20,000 signals), four where that is no worse; but one
-  // workgroup per CU before a second wave in any
+  // with eight, 229 us with sixteen for 20,000 signals), four where that is no worse.  Few signals spread
+  // over the CUs, a workgroup each, whose waves still load the tables together (a call of one signal
+  // 6x6x2 with 12x16x6 atoms in FP64, 85 KB of tables: 57 us with one wave a workgroup, 24 us so)
   int wpb = 1, best = 0;
   for (int w = 1; w <= v->maxw; w *= 2) {
     const size_t lds = v->lds(a.m1, a.m2, a.n1, a.n2, a.s, w);
@@ -106,8 +107,8 @@ hipError_t group_launch(const OmpArgs<T>& a, hipStream_t st) {
       wpb = w;
     }
   }
-  while (wpb > 1 && waves < 256 * (int64_t)wpb) wpb /= 2;
   int64_t grid = (waves + wpb - 1) / wpb;
+  if (grid < 256) grid = waves < 256 ? waves : 256;
   if (grid > kGroupMaxBlocks) grid = kGroupMaxBlocks;
   OmpArgs<T> args = a;
   void* p[] = {&args};
