@@ -23,11 +23,11 @@
 // What bounds it: the issue of vector-ALU instructions (the step loop's compares and multiply-adds)
 // with the LDS reads of the refresh close behind; four signals per wave share every instruction of
 // the serial parts of a step (argmax merge, solves), which is why 16 lanes take a signal wherever its
-// block of correlations fits their registers.  Vector ALUs busy 70% of the time in FP64, 98% in FP32
+// block of correlations fits their registers.  Vector ALUs busy 83% of the time in FP64, 99% in FP32
 // (100,000 signals 8x8, 16x16 atoms, s = 8).  Against the earlier form
 // of this path (one wave per signal, correlations in LDS, an integer division per element and term):
 // 100,000 FP64 signals 8x8, 16x16 atoms, s = 8: 1676 -> 154 us; 20,011 FP32 signals 9x7, 13x11 atoms,
-// s = 6: 148 -> 29 us; 20,000 FP64 signals 8x32, 12x72 atoms, s = 8 (three modes before): 1630 -> 225 us.
+// s = 6: 147 -> 28 us; 20,000 FP64 signals 8x32, 12x72 atoms, s = 8 (three modes before): 1630 -> 225 us.
 //
 // FP32 runs exactly the operations of that earlier form in its order, element by element (each
 // multiply-add fused or not as written below), so FP32 codes are the same bit for bit; FP64

@@ -342,7 +342,7 @@ __device__ inline bool polar_newton(double* W, double* R, double* X, double* buf
 // column pairs rotated at once (round-robin order: n' - 1 rounds of n' / 2 pairs cover every pair once
 // per sweep, n' = n rounded up to even, pairs with the dummy column n skipped); lane 8 q + r holds row r
 // for the q-th pair of the round.  The polar factor is unique for a full-rank B, so the order of the
-// rotations changes only rounding.  (A dictionary update with an ill-conditioned B at n = 8: 76 us a call, 105
+// rotations changes only rounding.  (A dictionary update with an ill-conditioned B at n = 8: 75 us a call, 102
 // with one pair at a time as above eight columns.)
 __device__ inline void jacobi8(double* W, double* V, int n) {
   const int x = threadIdx.x, np = n + (n & 1), q = x / 8, r = x % 8;
