@@ -318,7 +318,9 @@ hipError_t launch_patches_to_image(const int32_t* supp, const T* coef, const T* 
   const int M = m1 * m2;
   if (M > 40 && M <= 4 * kWave && rows_lds <= 80 * 1024) {
     const dim3 g((unsigned)((W + kColTile - 1) / kColTile), (unsigned)((H + kRowTile - 1) / kRowTile));
-    const auto k = M <= kWave ? rebuild_rows_kernel<T, 1> : M <= 2 * kWave ? rebuild_rows_kernel<T, 2> : rebuild_rows_kernel<T, 4>;
+    const auto k = M <= kWave       ? rebuild_rows_kernel<T, 1>
+                   : M <= 2 * kWave ? rebuild_rows_kernel<T, 2>
+                                    : rebuild_rows_kernel<T, 4>;
     hipLaunchKernelGGL(k, g, dim3(kWave * kRowWaves), rows_lds, st, supp, coef, D1, D2, H, W, m1, m2, n1, n2, s, img);
     return hipGetLastError();
   }

@@ -980,13 +980,13 @@ int learn_impl(sdl_problem* p, int nprob, int K, double* trace, const Opt& o, hi
     SDL_TRY(finish_call(st, ctx, pl, o, marks, true));
   }
   // A kernel of an iteration runs 4-12 us at the least (first-stage reductions 4, update sums 5-10, solves
-  // 10-11, coding 12 and more) and takes 3-4 us to launch, so launching them directly keeps the GPU fed.  (Capturing four iterations as a graph and replaying it cost 0.2 ms a
-  // call whenever the call's buffers were not those of the call before, and gained nothing when they
-  // were: 0.186 ms an iteration of 100,000 8x8 signals replayed, 0.178 ms launched; sixteen problems of 50
-  // signals on the same buffers, where the launches themselves set the pace, 6.6 and 6.9 ms.)  Several problems run
-  // side by side on streams of their own: the tail of one problem's launch, where its last workgroups
-  // leave most of the chip idle, is another's work.  A proposer's buffers are shared by all problems:
-  // those run in order.
+  // 10-11, coding 12 and more) and takes 3-4 us to launch, so launching them directly keeps the GPU fed.
+  // (Capturing four iterations as a graph and replaying it cost 0.2 ms a call whenever the call's buffers
+  // were not those of the call before, and gained nothing when they were: 0.186 ms an iteration of 100,000
+  // 8x8 signals replayed, 0.178 ms launched; sixteen problems of 50 signals on the same buffers, where the
+  // launches themselves set the pace, 6.6 and 6.9 ms.)  Several problems run side by side on streams of their
+  // own: the tail of one problem's launch, where its last workgroups leave most of the chip idle, is
+  // another's work.  A proposer's buffers are shared by all problems: those run in order.
   int nact = 0;
   for (int q = 0; q < nprob; ++q) nact += p[q].N > 0;
   const bool side_by_side = o.use_graph && !timing && nact > 1 && !o.proposer &&
